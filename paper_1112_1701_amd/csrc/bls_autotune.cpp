@@ -227,35 +227,8 @@ TileChoice tune(bls_plan *p, const Bucket &bk, const CurveShape &rep, bool weigh
 
 }  // namespace
 
-// Box evaluations of a call below which it is not worth tuning for
-// (about 20 ms of search at the measured 3e12 evaluations per second).
-constexpr double kTuneMinEvals = 6e10;
-
-TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted) {
-  TileChoice tc = default_tiles(weighted);
-  bool env = false;
-  if (const char *s = getenv("BLS_LDS_BUDGET")) tc.lds_budget = atoi(s), env = true;
-  if (const char *s = getenv("BLS_TILE_CAP")) tc.tile_cap = atoi(s), env = true;
-  if (const char *s = getenv("BLS_OCCUPANCY")) tc.occupancy = atoi(s), env = true;
-  if (env || (p->cfg.flags & BLS_NO_AUTOTUNE) || shapes.empty()) return tc;
-  // Tuning a new shape costs about 0.1 s of device time; a call with less
-  // work than that many box evaluations keeps the built-in table.
-  double evals = 0.0;
-  for (const CurveShape &s : shapes)
-    evals += (double)s.nbins * (double)(s.kmax - s.kmin + 1) * (double)s.nperiods;
-  if (evals < kTuneMinEvals) {
-    // The built-in table, with the tile cut so that the call has work items
-    // for two workgroups per CU.  Tiles any smaller only add per-item work:
-    // one 1000-point curve x 5000 periods (200 bins) took 69 / 50 / 62 /
-    // 93 us with tiles of 18 / 8 / 4 / 2 periods.
-    int64_t periods = 0;
-    for (const CurveShape &s : shapes) periods += s.nperiods;
-    const int64_t cap = std::max<int64_t>(1, periods / (2 * (int64_t)std::max(p->num_cus, 1)));
-    tc.tile_cap = (int)std::min<int64_t>(tc.tile_cap, cap);
-    return tc;
-  }
-
-  // Dominant shape: median points, bins and widths over the batch.
+// Dominant shape: median points, bins and widths over the batch.
+static CurveShape median_shape(const std::vector<CurveShape> &shapes) {
   std::vector<int64_t> ns;
   std::vector<int> nbs, kms;
   for (const CurveShape &s : shapes) {
@@ -268,6 +241,40 @@ TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool
   rep.nbins = median_of(nbs);
   rep.kmax = median_of(kms);
   rep.kmin = std::min(rep.kmin, rep.kmax);
+  return rep;
+}
+
+// Box evaluations of a call below which it is not worth tuning for
+// (about 20 ms of search at the measured 3e12 evaluations per second).
+constexpr double kTuneMinEvals = 6e10;
+
+TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted) {
+  TileChoice tc = default_tiles(weighted);
+  bool env = false;
+  if (const char *s = getenv("BLS_LDS_BUDGET")) tc.lds_budget = atoi(s), env = true;
+  if (const char *s = getenv("BLS_TILE_CAP")) tc.tile_cap = atoi(s), env = true;
+  if (const char *s = getenv("BLS_OCCUPANCY")) tc.occupancy = atoi(s), env = true;
+  if (env || shapes.empty()) return tc;
+  int64_t periods = 0;
+  for (const CurveShape &s : shapes) periods += s.nperiods;
+  const CurveShape rep = median_shape(shapes);
+  tc.lds_budget = untuned_lds_budget(rep, periods, weighted, p->num_cus);
+  if (p->cfg.flags & BLS_NO_AUTOTUNE) return tc;
+  // Tuning a new shape costs about 0.1 s of device time; a call with less
+  // work than that many box evaluations keeps the built-in table.
+  double evals = 0.0;
+  for (const CurveShape &s : shapes)
+    evals += (double)s.nbins * (double)(s.kmax - s.kmin + 1) * (double)s.nperiods;
+  if (evals < kTuneMinEvals) {
+    // The built-in table, with the tile cut so that the call has work items
+    // for two workgroups per CU.  Tiles any smaller only add per-item work:
+    // one 1000-point curve x 5000 periods (200 bins) took 69 / 50 / 62 /
+    // 93 us with tiles of 18 / 8 / 4 / 2 periods.
+    const int64_t cap = std::max<int64_t>(1, periods / (2 * (int64_t)std::max(p->num_cus, 1)));
+    tc.tile_cap = (int)std::min<int64_t>(tc.tile_cap, cap);
+    return tc;
+  }
+
   Bucket bk;
   bk.n_log2 = (int)ceil(log2((double)rep.n));
   bk.nbins_b = (rep.nbins + 31) / 32;

@@ -161,6 +161,12 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   const int64_t cap = periods / (2 * (int64_t)(ds.num_cus > 0 ? ds.num_cus : 1));
   tc.tile_cap = (int)(cap < 1 ? 1 : cap < tc.tile_cap ? cap : tc.tile_cap);
 
+  // the LDS budget follows the widest curve
+  int widest = 0;
+  for (int c = 1; c < nc; ++c)
+    if (shapes[c].nbins > shapes[widest].nbins) widest = c;
+  tc.lds_budget = untuned_lds_budget(shapes[widest], periods, weighted, ds.num_cus);
+
   CurveDesc desc[kNaCurves];
   double cost[kNaCurves];
   int64_t items_of[kNaCurves];

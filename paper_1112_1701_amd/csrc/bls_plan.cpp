@@ -635,6 +635,23 @@ TileChoice default_tiles(bool weighted) {
   return tc;
 }
 
+// Calls with many periods per workgroup keep the chip full whatever the tile,
+// and are fastest with the tile that lets eight unit-weight (or six weighted)
+// workgroups share a CU; smaller calls gain more from fewer, larger items.
+// Search kernel, 32 KB against 21 KB (weighted 25 KB): 192 curves x 2000
+// points x 20000 periods x 300 bins 11.34 / 8.51 ms; 384 x 600 x 20000 x 300
+// 20.4 / 14.6; 64 x 600 x 5000 x 300 1.04 / 0.87; 128 x 600 x 20000 x 200
+// 4.56 / 3.55; weighted 64 x 250 x 12000 x 200 2.06 / 1.77, 64 x 2000 x 12000
+// x 350 4.61 / 3.78; but 16 x 600 x 5000 x 300 0.371 / 0.399, weighted 16 x
+// 2000 x 5000 x 200 0.403 / 0.442, and 64 x 2000 x 2000 x 500 0.638 / 0.660.
+// Wide grids, whose tile would drop below four periods, keep 32 KB (weighted
+// 166 x 1106 x 2787 x 402 took 3.46 ms with it, 3.63 with tiles of three).
+int untuned_lds_budget(const CurveShape &rep, int64_t periods, bool weighted, int num_cus) {
+  const int small = weighted ? 25000 : 21200, wide = default_tiles(weighted).lds_budget;
+  if (periods < (int64_t)1024 * std::max(num_cus, 1)) return wide;
+  return small / (hist_words(rep.nbins, rep.kmax) * 8 * (weighted ? 2 : 1)) >= 4 ? small : wide;
+}
+
 double last_kernel_ms(bls_plan *p) {
   if (p->k_recorded == 0) return 0.0;
   const int slot = (int)((p->k_recorded - 1) % bls_plan::kTimeRing);

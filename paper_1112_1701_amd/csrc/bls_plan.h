@@ -246,5 +246,8 @@ void fit_tile(int nbins, int kmax, int64_t nperiods, int lds_budget, int tile_ca
 TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted);
 // The built-in table the tuner starts from.
 TileChoice default_tiles(bool weighted);
+// The built-in table's LDS budget for a call of `periods` trial periods whose
+// typical curve is `rep`.
+int untuned_lds_budget(const CurveShape &rep, int64_t periods, bool weighted, int num_cus);
 
 }  // namespace bls
