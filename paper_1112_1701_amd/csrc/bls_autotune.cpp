@@ -135,6 +135,8 @@ double time_candidate(bls_plan *p, std::vector<CurveShape> &shapes, bool weighte
   a.kwidth = ks;
   a.best_key = keys;
   a.hist_bytes = pb.hist_bytes;
+  a.scr_bytes = pb.scr_bytes;
+  a.scr_offset = pb.scr_offset;
   a.ucap = 0;
   a.uws = nullptr;
   a.uws_stride = 0;
@@ -254,7 +256,15 @@ TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool
   if (const char *s = getenv("BLS_LDS_BUDGET")) tc.lds_budget = atoi(s), env = true;
   if (const char *s = getenv("BLS_TILE_CAP")) tc.tile_cap = atoi(s), env = true;
   if (const char *s = getenv("BLS_OCCUPANCY")) tc.occupancy = atoi(s), env = true;
-  if (env || shapes.empty()) return tc;
+  if (shapes.empty()) return tc;
+  tc.block = block_batch(shapes.data(), (int)shapes.size(), weighted, p->max_lds);
+  if (env) return tc;
+  if (tc.block) {
+    // The block search's tile follows from its LDS (block_tile).
+    tc.tile_cap = 4;
+    tc.lds_budget = block_lds_budget(median_shape(shapes), weighted, p->max_lds);
+    return tc;
+  }
   int64_t periods = 0;
   for (const CurveShape &s : shapes) periods += s.nperiods;
   const CurveShape rep = median_shape(shapes);

@@ -68,6 +68,16 @@ struct CurveDesc {
   // where the result index is a multiple of `group`
   int32_t group;
   int32_t galign;
+  // ---- written by the host planner: block search (bls_blocks.hip): bins per
+  // block, blocks, least and largest offset of a block pair that holds a box
+  // of the width range, ceil(2^20 / bsize)
+  int32_t bsize;
+  int32_t nblocks;
+  int32_t omin;
+  int32_t omax;
+  int32_t bmagic;
+  // ---- written by the prep kernel: smallest encoded weight of a kept point
+  int32_t qwmin;
 };
 
 struct PrepArgs {
@@ -118,9 +128,38 @@ struct SearchArgs {
   // (workgroups are dispatched to the XCDs round-robin, so a partition's
   // curves stay in one XCD's L2); counter[x] counts its items taken.
   int32_t nparts;
+  // block search: the waves' scratch in dynamic LDS, scr_bytes each from
+  // scr_offset on (0 bytes: the launch runs search_kernel)
+  int32_t scr_bytes;
+  int32_t scr_offset;
   int32_t pad_parts;
   int64_t part_begin[kMaxParts + 1];
 };
+
+// Block search: geometry of a curve's blocks of consecutive prefix sums.
+constexpr int kBlockQueue = 128;    // queued block pairs per wave
+constexpr int kBlockCand = 128;     // candidate boxes kept per wave
+constexpr int kMaxBlocks = 256;     // blocks per period (queue entries hold 8 bits)
+struct BlockGeom {
+  int bsize, nblocks, omin, omax, magic;
+};
+bool block_geometry(int nbins, int kmin, int kmax, BlockGeom *g);
+// LDS words (64-bit) of a period's plane: the prefixes up to nbins + kmax
+// and a block more (read past a lane's last box), and zeros up to the last
+// block's end.
+inline int block_plane_words(int nbins, int kmax, const BlockGeom &g) {
+  const int a = nbins + kmax + 1 + g.bsize, b = g.nblocks * g.bsize + 1;
+  return a > b ? a : b;
+}
+// Scratch of one wave: the blocks' table with its wrapped copy, the blocks'
+// counts, the candidates, the pair queue, one mark per start bin.
+inline int block_scratch_bytes(int nbins, const BlockGeom &g) {
+  const int n = 16 * (g.nblocks + g.omax + 3) + 8 * g.nblocks + 4 * kBlockCand + 2 * kBlockQueue +
+                4 * ((nbins + 31) / 32);
+  return (n + 15) & ~15;
+}
+// The block kernel for a launch (bls_blocks.hip).
+const void *block_search_fn(bool weighted, bool dip);
 
 // One partition over all items (callers without an XCD split).
 inline void single_partition(SearchArgs &a) {
@@ -242,8 +281,8 @@ int launch_best_index(unsigned long long *keys, int32_t n, void *stream);
 // Phase bin of every prepared point at one period (diagnostic).
 int launch_bins(const double *dt, int64_t n, const double *period, int32_t nbins, int32_t *bins,
                 void *stream);
-// Workgroups of the search kernel one CU holds at this LDS size.
-int search_blocks_per_cu(bool weighted, bool dip_only, int hist_bytes,
-                         int *blocks);
+// Workgroups of the search kernel (block: of the block search kernel) one CU
+// holds at this LDS size.
+int search_blocks_per_cu(bool weighted, bool dip_only, bool block, int hist_bytes, int *blocks);
 
 }  // namespace bls

@@ -31,6 +31,7 @@
 
 #include "bls_block.h"
 #include "bls_device.h"
+#include "bls_fold.h"
 #include "bls_items.h"
 #include "../../include/bls.h"
 
@@ -163,6 +164,7 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
 
   // Pass 3: encode; exact totals of the encoded weights and values.
   long long sqw = 0, sq = 0;
+  double qwmin = INFINITY, unused_max = 0.0;
   for (int64_t i = tid; i < n; i += kBlock) {
     const double wi = weighted ? a.w[off + i] : 1.0;
     if (wi == 0.0) {
@@ -181,9 +183,11 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
       const int qwi = __double2int_rn(ldexp(wi, ew));
       a.qw[off + i] = qwi;
       sqw += qwi;
+      qwmin = fmin(qwmin, (double)qwi);
     }
   }
   block_isum2(sqw, sq, ia, ib);
+  if (weighted) block_minmax(qwmin, unused_max, sa, sb);
 
   if (tid == 0) {
     cd->t0 = tmin;
@@ -197,191 +201,12 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
     cd->Wtot = weighted ? ldexp((double)sqw, -qbits) : (double)cnt;
     cd->Stot = ldexp((double)sq, -qbits);
     cd->n_eff = (int32_t)cnt;
+    cd->qwmin = weighted ? (int32_t)qwmin : 0;
     cd->status = kCurveOk;
   }
 }
 
 // ---------------------------------------------------------------- search
-// One bin word holds (count << shift) + sum of signed fixed-point values.
-// |sum| < 2^46 < 2^(shift - 1), so the sum is the sign-extended low field
-// and the count is what remains above it.
-struct BinWord {
-  long long sum;
-  unsigned count;
-};
-
-__device__ inline BinWord decode_word(unsigned long long u, int shift) {
-  BinWord w;
-  const int hi = 64 - shift;
-  w.sum = ((long long)(u << hi)) >> hi;
-  // a negative sum borrowed one from the count field
-  w.count = (unsigned)(u >> shift) - (unsigned)(w.sum >> 63);
-  return w;
-}
-
-// Correctly rounded float of an integer with |v| < 2^47: both halves convert
-// exactly and the fused multiply-add rounds once.
-__device__ inline float int47_to_float(long long v) {
-  const int hi = (int)(v >> 24);
-  const unsigned lo = (unsigned)v & 0xFFFFFFu;
-  return fmaf((float)hi, 16777216.0f, (float)lo);
-}
-
-// trunc(frac(d f) nbins) with the FP64 operation order of the definition.
-// For finite c >= 0, c - floor(c) is exact and below 1, so v_fract_f64
-// returns exactly that value.  The result lies in [0, nbins]; nbins itself
-// (phase so close to 1 that the product rounds up) is the clamp case of the
-// definition.
-__device__ inline int raw_bin(double d, double f, double nbd) {
-  const double c = d * f;
-  const double ph = __builtin_amdgcn_fract(c);
-  return (int)(ph * nbd);
-}
-
-__device__ inline int phase_bin(double d, double f, double nbd, unsigned nbm1) {
-  return (int)min((unsigned)raw_bin(d, f, nbd), nbm1);
-}
-
-// A 64-bit value every lane holds alike, moved to scalar registers.
-__device__ inline int64_t uniform_i64(int64_t v) {
-  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((uint64_t)v & 0xFFFFFFFFu));
-  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((uint64_t)v >> 32));
-  return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// Lane spacing of the fold for one work item, in units of kPPT points:
-// 1, 2 or 4 (a chunk is kBlock / 64 = 4 waves of 64 lanes).  On a dense
-// cadence, points close in time fall into one bin at long periods, and
-// lanes of one LDS atomic on the same word are serialised.  The gap is
-// the smallest that puts adjacent lanes half a bin apart in phase at the
-// tile's longest period (fmin = its smallest frequency); cadence is the
-// curve's median time step.  Where lanes are that far apart already, the
-// contiguous layout (gap 1) is the faster one.
-static_assert(kBlock == 256 && kPPT == 4, "the fold's lane layout assumes 4 waves of 4 points");
-
-__device__ inline int fold_lane_gap(double fmin, int nbins, float cadence) {
-  // x = (lane step in time) / (bin width in time at the longest period)
-  const double x = fmin * (double)nbins * (double)kPPT * (double)cadence;
-  return !(x < 0.5) || !(x > 0.0) ? 1 : x >= 0.25 ? 2 : 4;
-}
-
-// Whether a tile's fold merges a thread's consecutive same-bin points: when
-// one cadence step advances the phase by less than 0.3 bins at the tile's
-// longest period (frequency fmin), so that runs of about three points or
-// more share a bin, unless the launch fixes the choice (policy 1: always,
-// 2: never).  The merge costs VALU operations on every point and saves one
-// LDS atomic per point it joins; shorter runs do not repay it.  A weighted
-// point saves two atomics, and there the merge pays from one bin per step.
-// Any answer is correct; this one only picks the faster fold.
-__device__ inline bool fold_merges(double fmin, int nbins, float cadence, int policy,
-                                   bool weighted) {
-  if (policy != 0) return policy == 1;
-  const double x = fmin * (double)nbins * (double)cadence;
-  return !(x >= (weighted ? 1.0 : 0.3));
-}
-
-// Fold and bin one chunk of kBlock * kPPT points into the tile's histograms.
-// Each thread takes kPPT consecutive points, so the 64 lanes of one atomic
-// instruction hold points kPPT apart in time: their phases (hence bins and
-// LDS banks) are far less correlated than those of 64 consecutive points of
-// a sorted light curve, which cuts same-bin and same-bank collisions.
-// Each period's histogram plane starts HS words after the previous one: nb
-// bins, the word after them (it catches the clamp case and is added to bin
-// nb - 1 when the histogram is decoded, later the start of the wrap-around
-// copy), and padding that keeps the scan's reads free of bank conflicts.
-// Weighted curves use two such planes per period, A (count, weight) then B
-// (weighted signal), each contiguous so that the lanes of one atomic spread
-// over all LDS banks.
-// MERGE: consecutive points of a thread that share a bin are summed first;
-// without it every point is one atomic (tiles whose periods are short
-// against the cadence, where neighbours almost never share a bin).
-template <bool WEIGHTED, bool FULL, bool MERGE>
-__device__ inline void fold_chunk(const SearchArgs &a, const CurveDesc &cd, int64_t base,
-                                  int np, const double *s_f, unsigned long long *s_hist,
-                                  int HS, int gap) {
-  const int tid = threadIdx.x;
-  // The chunk's first point and the points left from there, kept in scalar
-  // registers.
-  const int64_t off = uniform_i64(cd.n_off + base);
-  const int64_t left = uniform_i64(cd.n - base);
-  // Each thread takes kPPT consecutive points; the lanes of a wave are
-  // kPPT gap points apart and the waves interleave (gap 1, 2 or 4).  The
-  // gap passes through an opaque copy so that the compiler recomputes this
-  // per chunk instead of holding it in VGPRs through the item.
-  asm volatile("" : "+s"(gap));
-  const int w = tid >> 6, l = tid & 63;
-  const int k0 = kPPT * (l * gap + (w & (gap - 1))) + 64 * kPPT * gap * (w >> (gap >> 1));
-  const double *dt = a.dt + off;
-  const int32_t *q = a.q + off;
-  const int32_t *qw = WEIGHTED ? a.qw + off : nullptr;
-  const double nbd = (double)cd.nbins;
-  const unsigned long long one = 1ull << cd.shift;
-  double d[kPPT];
-  unsigned long long va[kPPT];
-  unsigned long long vb[kPPT];
-  bool ok[kPPT];
-#pragma unroll
-  for (int r = 0; r < kPPT; ++r) {
-    const int k = k0 + r;
-    ok[r] = FULL || (int64_t)k < left;
-    d[r] = 0.0;
-    va[r] = 0;
-    vb[r] = 0;
-    if (ok[r]) {
-      d[r] = dt[k];
-      const long long qi = q[k];
-      if (WEIGHTED) {
-        const int qwi = qw[k];
-        va[r] = qwi >= 0 ? one + (unsigned long long)(long long)qwi : 0ull;
-        vb[r] = (unsigned long long)qi;
-      } else {
-        va[r] = one + (unsigned long long)qi;
-      }
-    }
-  }
-  constexpr int wpb = WEIGHTED ? 2 : 1;
-  for (int t = 0; t < np; ++t) {
-    const double f = s_f[t];
-    unsigned long long *h = s_hist + (size_t)t * HS * wpb;
-    // A thread's consecutive points that share a bin (common at long
-    // periods) are summed in registers and sent as one atomic.
-    int bin[kPPT];
-#pragma unroll
-    for (int r = 0; r < kPPT; ++r) bin[r] = raw_bin(d[r], f, nbd);
-    if (!MERGE) {
-#pragma unroll
-      for (int r = 0; r < kPPT; ++r) {
-        if (FULL || ok[r]) {
-          __hip_atomic_fetch_add(h + bin[r], va[r], __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (WEIGHTED)
-            __hip_atomic_fetch_add(h + HS + bin[r], vb[r], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-      }
-      continue;
-    }
-    unsigned long long accA = 0, accB = 0;
-#pragma unroll
-    for (int r = 0; r < kPPT; ++r) {
-      if (FULL || ok[r]) {
-        accA += va[r];
-        if (WEIGHTED) accB += vb[r];
-        const int rn = r + 1 < kPPT ? r + 1 : r;
-        const bool run_ends = r == kPPT - 1 || !(FULL || ok[rn]) || bin[rn] != bin[r];
-        if (run_ends) {
-          __hip_atomic_fetch_add(h + bin[r], accA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (WEIGHTED)
-            __hip_atomic_fetch_add(h + HS + bin[r], accB, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-          accA = 0;
-          accB = 0;
-        }
-      }
-    }
-  }
-}
-
 // Exact test of one box against a lane's best (bn, bd): divide-free
 // comparison v > v_best, validity on exact counts, dip-only sign.
 template <bool WEIGHTED, bool DIP, bool MIP1>
@@ -1056,7 +881,8 @@ int launch_prep(const PrepArgs &a, void *stream) {
 
 int launch_search(const SearchArgs &a, bool weighted, bool dip_only, int grid, void *stream) {
   if (a.nitems <= 0) return 0;
-  const void *fn = pick(weighted, dip_only, a.hist_bytes);
+  const void *fn = a.scr_bytes > 0 ? block_search_fn(weighted, dip_only)
+                                   : pick(weighted, dip_only, a.hist_bytes);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, a.hist_bytes);
   if (e != hipSuccess) return (int)e;
   void *args[] = {const_cast<SearchArgs *>(&a)};
@@ -1081,8 +907,9 @@ int launch_best_index(unsigned long long *keys, int32_t n, void *stream) {
   return (int)hipGetLastError();
 }
 
-int search_blocks_per_cu(bool weighted, bool dip_only, int hist_bytes, int *blocks) {
-  const void *fn = pick(weighted, dip_only, hist_bytes);
+int search_blocks_per_cu(bool weighted, bool dip_only, bool block, int hist_bytes, int *blocks) {
+  const void *fn =
+      block ? block_search_fn(weighted, dip_only) : pick(weighted, dip_only, hist_bytes);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, hist_bytes);
   if (e != hipSuccess) return (int)e;
   return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, kBlock, (size_t)hist_bytes);

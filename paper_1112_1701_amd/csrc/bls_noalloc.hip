@@ -151,7 +151,6 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   if (st != BLS_OK) return set_error_noplan(st, err);
   const int nc = b->ncurves;
   const bool weighted = b->weights != nullptr;
-  const int wpb = weighted ? 2 : 1;
 
   // Built-in tile table; tiles cut so that the call has work items for two
   // workgroups per CU (as for untuned small plan calls).
@@ -161,26 +160,33 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   const int64_t cap = periods / (2 * (int64_t)(ds.num_cus > 0 ? ds.num_cus : 1));
   tc.tile_cap = (int)(cap < 1 ? 1 : cap < tc.tile_cap ? cap : tc.tile_cap);
 
-  // the LDS budget follows the widest curve
+  // LDS budgets follow the widest curve.
   int widest = 0;
   for (int c = 1; c < nc; ++c)
     if (shapes[c].nbins > shapes[widest].nbins) widest = c;
-  tc.lds_budget = untuned_lds_budget(shapes[widest], periods, weighted, ds.num_cus);
+  const bool block = block_batch(shapes, nc, weighted, ds.max_lds);
+  if (block) {
+    tc.tile_cap = tc.tile_cap < 4 ? tc.tile_cap : 4;
+    tc.lds_budget = block_lds_budget(shapes[widest], weighted, ds.max_lds);
+  } else {
+    tc.lds_budget = untuned_lds_budget(shapes[widest], periods, weighted, ds.num_cus);
+  }
 
   CurveDesc desc[kNaCurves];
   double cost[kNaCurves];
   int64_t items_of[kNaCurves];
-  int hist_bytes = 0;
+  LdsLayout lds;
   for (int c = 0; c < nc; ++c) {
     const CurveShape &s = shapes[c];
-    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, false, desc[c]);
+    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, false, block,
+                    desc[c]);
     const int T = desc[c].tile;
-    const int hb = T * desc[c].hstride * 8 * wpb;
-    if (hb > hist_bytes) hist_bytes = hb;
+    lds.add(desc[c], block);
     const double nw = (double)(s.kmax - s.kmin + 1);
     cost[c] = (double)T * ((double)s.n + 1.6 * (double)s.nbins * nw);
     items_of[c] = (s.nperiods + T - 1) / T;
   }
+  const int hist_bytes = lds.total();
   if (hist_bytes > ds.max_lds - 1024)
     return set_error_noplan(BLS_ERR_CAPACITY,
                             "one period's histogram needs more LDS than a workgroup has");
@@ -204,7 +210,7 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
 
   int per_cu = 0;
   hipError_t e = (hipError_t)search_blocks_per_cu(weighted, (flags & BLS_DIP_ONLY) != 0,
-                                                  hist_bytes, &per_cu);
+                                                  block, hist_bytes, &per_cu);
   if (e != hipSuccess) return set_error_noplan(BLS_ERR_DEVICE, "occupancy query failed");
   if (per_cu < 1) return set_error_noplan(BLS_ERR_CAPACITY, "search kernel does not fit a CU");
   int64_t grid = (int64_t)ds.num_cus * per_cu;
@@ -283,6 +289,8 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   sa.kwidth = o->kwidth;
   sa.best_key = keys;
   sa.hist_bytes = hist_bytes;
+  sa.scr_bytes = lds.scratch;
+  sa.scr_offset = lds.planes;
   sa.ucap = 0;
   single_partition(sa);
   if ((e = (hipError_t)launch_search(sa, weighted, (flags & BLS_DIP_ONLY) != 0, (int)grid,

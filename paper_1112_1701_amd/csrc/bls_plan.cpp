@@ -193,8 +193,137 @@ struct ErrBuf {
 };
 }  // namespace
 
+// Block size: odd (the lanes' strides then spread over the LDS banks), so
+// that r = 1 .. 4 waves-full of blocks cover the bins, r by the estimated
+// cost: r rounds of pair tests per offset, and the boxes of the pairs that
+// pass (about 25 and one per 22 bins of them on noise), a lane per start.
+bool block_geometry(int nbins, int kmin, int kmax, BlockGeom *out) {
+  if (2 * kmax > nbins || kmin > kmax) return false;
+  double best = 0.0;
+  for (int r = 1; r <= kMaxBlocks / 64; ++r) {
+    BlockGeom g;
+    g.bsize = (nbins + 64 * r - 1) / (64 * r) | 1;
+    g.nblocks = (nbins + g.bsize - 1) / g.bsize;
+    const int pad = g.nblocks * g.bsize - nbins;
+    g.omin = kmin >= g.bsize ? kmin / g.bsize : 0;  // least o with o s + s - 1 >= kmin
+    if (g.omin * g.bsize + g.bsize - 1 < kmin) ++g.omin;
+    g.omax = (kmax + g.bsize - 1 + pad) / g.bsize;
+    g.magic = ((1 << 20) + g.bsize - 1) / g.bsize;
+    if (g.omax + 1 >= g.nblocks || g.omax > 255 || g.bsize > 64) continue;
+    const int rounds = (g.nblocks + 63) / 64;
+    const double pairs = 25.0 + nbins / 22.0;
+    const double cost = rounds * (g.omax + 1) * 35.0 +
+                        ceil(pairs * g.bsize / 64.0) * (20.0 + 13.0 * g.bsize) +
+                        rounds * g.bsize * 25.0;
+    if (best == 0.0 || cost < best) {
+      best = cost;
+      *out = g;
+    }
+  }
+  return best > 0.0;
+}
+
+// Periods per work item of the block search and the workgroups that share a
+// CU: as many periods in hand per CU as its LDS allows (a wave works on one),
+// and of equal choices the largest tile with at least four workgroups per CU
+// (they load the points for more periods at once), else the smallest tile.
+// One-period-per-wave tiles also beat larger ones (uniform batch, 300 bins:
+// tiles of 1, 2, 3, 4, 8 took 14.2, 8.6, 7.0, 6.1, 6.4 ms; 1000 bins, 600
+// points: 8.3, 5.6, 5.0, 4.9 ms for 1 to 4; 2000 bins: 3.4, 3.8, 4.0, 6.1).
+int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom &g, int *groups) {
+  const int cap = weighted ? 5 : 6;  // workgroups per CU that the registers allow
+  int best = 0, best_periods = 0, best_groups = 0;
+  for (int T = 1; T <= 4; ++T) {
+    const int bytes = block_tile_bytes(T, nbins, kmax, weighted, g) + kBlockStaticLds;
+    const int w = std::min(cap, max_lds / bytes);
+    if (w < 1) break;
+    const int periods = T * w;
+    if (periods > best_periods || (periods == best_periods && w >= 4)) {
+      best = T;
+      best_periods = periods;
+      best_groups = w;
+    }
+  }
+  if (groups) *groups = best_groups;
+  return best;
+}
+
+// Whether the block search is the faster kernel for a batch, from the clocks
+// per period and CU that both took (after the fold, which they share) at 200
+// to 2000 bins, 220 to 20000 points and duty-cycle ranges of 0.01-0.03 to
+// 0.02-0.2, search_kernel with its tuned tile.  Scoring every box: 0.72 of
+// its instructions (weighted 1.3: half the waves).  The block search: 1 (1.4)
+// of its own where a CU holds 20 periods, more where its LDS holds fewer, and
+// a little more on sparse curves, whose boxes tie more often.  Measured new
+// over old: 300 bins (0.01-0.1) 1.06 unit and 0.94 weighted; 400 bins 0.95,
+// 0.86; 600 bins 0.68, 0.78; 1000 bins (0.005-0.05) 0.93, 1.19; (0.01-0.1)
+// 0.57, 0.78; 200 bins 1.08, 0.95.
+namespace {
+double every_box_cost(const CurveShape &s, bool weighted) {
+  return (weighted ? 1.3 : 0.72) * s.nbins / 64.0 *
+         (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
+}
+double block_cost(const CurveShape &s, bool weighted, const BlockGeom &g, int periods_per_cu) {
+  const int rounds = (g.nblocks + 63) / 64, per = 64 / g.bsize;
+  const double batches = ceil((20.0 + s.nbins / 25.0) / per);
+  const double instr = 330.0 + rounds * (60.0 + 24.0 * g.bsize + 27.0 * (g.omax - g.omin + 1)) +
+                       batches * (32.0 + 13.5 * g.bsize);
+  return instr * (weighted ? 1.4 : 1.0) * std::max(1.0, pow(20.0 / periods_per_cu, 0.8)) *
+         (s.n < s.nbins ? 1.15 : 1.0);
+}
+}  // namespace
+
+bool block_batch(const CurveShape *shapes, int n, bool weighted, int max_lds) {
+  const char *e = getenv("BLS_BLOCK_SEARCH");  // 0: never, 1: wherever it can run
+  if (e && atoi(e) == 0) return false;
+  double every = 0.0, block = 0.0;
+  for (int c = 0; c < n; ++c) {
+    const CurveShape &s = shapes[c];
+    BlockGeom g;
+    if (!block_geometry(s.nbins, s.kmin, s.kmax, &g)) return false;
+    int groups = 0;
+    const int T = block_tile(s.nbins, s.kmax, weighted, max_lds, g, &groups);
+    if (T < 1) return false;
+    every += (double)s.nperiods * every_box_cost(s, weighted);
+    block += (double)s.nperiods * block_cost(s, weighted, g, T * groups);
+  }
+  return e != nullptr || block < every;
+}
+
+// LDS budget of the block search for a batch whose typical curve is `rep`:
+// its best tile's share of a CU, so that larger curves take smaller tiles
+// and the launch keeps that tile's workgroups.
+int block_lds_budget(const CurveShape &rep, bool weighted, int max_lds) {
+  BlockGeom g;
+  int groups = 1;
+  if (!block_geometry(rep.nbins, rep.kmin, rep.kmax, &g) ||
+      block_tile(rep.nbins, rep.kmax, weighted, max_lds, g, &groups) < 1)
+    return max_lds - kBlockStaticLds;
+  return max_lds / groups - kBlockStaticLds;
+}
+
+void fit_block_tile(int nbins, int kmin, int kmax, int64_t nperiods, int lds_budget, int tile_cap,
+                    bool weighted, int *tile, int *stride, BlockGeom *g) {
+  block_geometry(nbins, kmin, kmax, g);
+  // at most one period per wave (block_tile)
+  int T = (int)std::min<int64_t>(std::min(tile_cap, 4), std::max<int64_t>(nperiods, 1));
+  while (T > 1 && block_tile_bytes(T, nbins, kmax, weighted, *g) > lds_budget) --T;
+  *tile = std::max(T, 1);
+  *stride = block_plane_words(nbins, kmax, *g);
+}
+
+void LdsLayout::add(const CurveDesc &d, bool block) {
+  planes = std::max(planes, d.tile * d.hstride * 8 * (d.weighted ? 2 : 1));
+  if (block) {
+    const BlockGeom g{d.bsize, d.nblocks, d.omin, d.omax, d.bmagic};
+    planes = (planes + 15) & ~15;
+    waves = std::max(waves, std::min(d.tile, 4));
+    scratch = std::max(scratch, block_scratch_bytes(d.nbins, g));
+  }
+}
+
 void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
-                     bool check_periods, bool memo, CurveDesc &d) {
+                     bool check_periods, bool memo, bool block, CurveDesc &d) {
   memset(&d, 0, sizeof d);
   d.n_off = s.n_off;
   d.n = s.n;
@@ -212,7 +341,18 @@ void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
   // bins, then the clamp word / wrap-around copy, per period and plane,
   // padded against LDS bank conflicts, as the kernel lays them out
   int T = 1, hs = 0;
-  fit_tile(s.nbins, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T, &hs, memo);
+  if (block) {
+    BlockGeom g;
+    fit_block_tile(s.nbins, s.kmin, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T,
+                   &hs, &g);
+    d.bsize = g.bsize;
+    d.nblocks = g.nblocks;
+    d.omin = g.omin;
+    d.omax = g.omax;
+    d.bmagic = g.magic;
+  } else {
+    fit_tile(s.nbins, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T, &hs, memo);
+  }
   d.tile = T;
   d.hstride = hs;
 }
@@ -441,7 +581,6 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
   // queued copies (or graph replays) may still read the pinned descriptors
   const int ws = desc_wait(p);
   if (ws != BLS_OK) return ws;
-  const int wpb = weighted ? 2 : 1;
   out = PlannedBatch{};
   out.ncurves = nc;
   out.weighted = weighted;
@@ -451,19 +590,20 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
   // them for several items per resident workgroup; one tile each otherwise.
   const int G = item_group(p, shapes);
   // Per-curve tile: as many periods as fit the LDS budget, at least one.
-  int hist_bytes = 0;
+  const bool block = tc.block;
+  LdsLayout lds;
   std::vector<double> item_cost(nc);
   for (int c = 0; c < nc; ++c) {
     const CurveShape &s = shapes[c];
     CurveDesc &d = p->h_curves[c];
     // each distinct period range is checked once (a shared grid by curve 0)
-    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, true, d);
+    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, true, block, d);
     const int T = d.tile;
     if (G > 0) {
       d.group = G;
       d.galign = (int32_t)(s.r_off % G);
     }
-    hist_bytes = std::max(hist_bytes, T * d.hstride * 8 * wpb);
+    lds.add(d, block);
     const double nw = (double)(s.kmax - s.kmin + 1);
     item_cost[c] = (double)(G > 0 ? G : T) * ((double)s.n + 1.6 * (double)s.nbins * nw);
     out.total_points += s.n;
@@ -471,6 +611,7 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
     out.trial_points += (double)s.n * (double)s.nperiods;
     out.box_evals += (double)s.nbins * nw * (double)s.nperiods;
   }
+  const int hist_bytes = lds.total();
   if (hist_bytes > p->max_lds - 1024) {
     return set_error(p, BLS_ERR_CAPACITY,
                      "one period's histogram needs " + std::to_string(hist_bytes) +
@@ -488,9 +629,11 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
   layout_partitions(p, item_cost, items_of, out);
   const int64_t items = out.nitems;
   out.hist_bytes = hist_bytes;
+  out.scr_bytes = lds.scratch;
+  out.scr_offset = lds.planes;
 
   int per_cu = 0;
-  hipError_t e = (hipError_t)search_blocks_per_cu(weighted, (p->cfg.flags & BLS_DIP_ONLY) != 0,
+  hipError_t e = (hipError_t)search_blocks_per_cu(weighted, (p->cfg.flags & BLS_DIP_ONLY) != 0, block,
                                                   hist_bytes, &per_cu);
   if (e != hipSuccess) return hip_error(p, e, "occupancy query");
   if (per_cu < 1) return set_error(p, BLS_ERR_CAPACITY, "search kernel does not fit a CU");
@@ -587,6 +730,8 @@ int enqueue_kernel(bls_plan *p, const PlannedBatch &pb, const double *periods, f
   sa.kwidth = ks;
   sa.best_key = reinterpret_cast<unsigned long long *>(best);
   sa.hist_bytes = pb.hist_bytes;
+  sa.scr_bytes = pb.scr_bytes;
+  sa.scr_offset = pb.scr_offset;
   sa.ucap = pb.ucap;
   sa.uws = pb.uws;
   sa.uws_stride = pb.uws_stride;

@@ -18,6 +18,7 @@ struct TileChoice {
   int lds_budget = 32768;   // dynamic LDS bytes per workgroup to aim for
   int tile_cap = kTileMax;  // upper bound on periods per work item
   int occupancy = 0;        // workgroups per CU to launch (0 = max resident)
+  bool block = false;       // the block search (every curve qualifies)
 };
 
 // A fully planned call: descriptors in pinned host memory, ready to upload.
@@ -28,7 +29,9 @@ struct PlannedBatch {
   int64_t total_results = 0;
   int64_t nitems = 0;
   int32_t nseg = 0;
-  int32_t hist_bytes = 0;
+  int32_t hist_bytes = 0;  // dynamic LDS of a workgroup
+  int32_t scr_bytes = 0;   // block search: scratch per wave (0: search_kernel)
+  int32_t scr_offset = 0;
   int32_t grid = 0;
   double trial_points = 0.0;
   double box_evals = 0.0;
@@ -158,8 +161,34 @@ int validate_batch_into(const bls_plan_config &cfg, const bls_batch &b, bool che
 // layout, and the period tile and plane stride that fit tc's LDS budget.
 // memo: keep the bank-conflict costs of plane strides in the process-wide
 // cache (false: compute them afresh, with no heap use).
+// block: the layout of the block search (see block_curve).
 void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
-                     bool check_periods, bool memo, CurveDesc &d);
+                     bool check_periods, bool memo, bool block, CurveDesc &d);
+
+// Whether the block search can run every curve of a launch (boxes of at most
+// half the bins) and is the faster kernel for it.
+bool block_batch(const CurveShape *shapes, int n, bool weighted, int max_lds);
+// LDS budget per workgroup of the block search (`rep`: the batch's typical
+// curve).
+int block_lds_budget(const CurveShape &rep, bool weighted, int max_lds);
+constexpr int kBlockStaticLds = 1536;  // static LDS of block_search_kernel, rounded up
+// Periods per work item of the block search within an LDS budget (at least
+// one), its plane stride and geometry.
+void fit_block_tile(int nbins, int kmin, int kmax, int64_t nperiods, int lds_budget, int tile_cap,
+                    bool weighted, int *tile, int *stride, BlockGeom *g);
+// LDS layout of a launch, extended by one curve at a time: dynamic LDS bytes
+// and, for the block search, the waves' scratch behind the planes.
+struct LdsLayout {
+  int planes = 0, scratch = 0, waves = 0;
+  void add(const CurveDesc &d, bool block);
+  int total() const { return planes + waves * scratch; }
+};
+// LDS of a block-search tile of T periods: its planes, and scratch for the
+// waves that have a period.
+inline int block_tile_bytes(int T, int nbins, int kmax, bool weighted, const BlockGeom &g) {
+  return T * block_plane_words(nbins, kmax, g) * 8 * (weighted ? 2 : 1) +
+         (T < 4 ? T : 4) * block_scratch_bytes(nbins, g);
+}
 
 // Segments grouped into work partitions (one per XCD), curves assigned
 // round-robin in descending cost; items_of[c] = work items of curve c.

@@ -50,18 +50,22 @@ struct Req {
   int64_t best = -1;
   int slot = -1;
   size_t pt_off = 0, pr_off = 0;
+  bool block = false;  // runs the block search
+  BlockGeom geom{};
   int32_t tile = 1, hstride = 0, ntiles = 0, issued = 0, done_tiles = 0;
   double item_cost = 0;
   uint64_t order = 0;
   double pp = 0, evals = 0;
 };
 
-// One tick: period tiles of every kind of admitted request, unit-weight
-// segments first (nu of them), then weighted ones; each kind is its own
-// persistent launch of the tick, back to back on the server's stream.
+// One tick: period tiles of every kind of admitted request, kind by kind (n of
+// each); a kind is its own persistent launch of the tick (a kernel), the
+// launches back to back on the server's stream.
+constexpr int kKinds = 4;  // block search or not, weighted or not
+inline int kind_of(const Req *r) { return (r->weighted ? 2 : 0) + (r->block ? 1 : 0); }
 struct Tick {
   int buf = 0;
-  int nu = 0;
+  int n[kKinds] = {};
   std::vector<TickSegment> segs;
 };
 
@@ -202,6 +206,11 @@ hipError_t start_request(bls_server *s, Req *r) {
   d.kmax = r->kmax;
   d.tile = r->tile;
   d.hstride = r->hstride;
+  d.bsize = r->geom.bsize;
+  d.nblocks = r->geom.nblocks;
+  d.omin = r->geom.omin;
+  d.omax = r->geom.omax;
+  d.bmagic = r->geom.magic;
   const int cb = cbits_of(r->n);
   d.shift = 64 - cb;
   d.qbits = std::min(kQBitsMax, 63 - 2 * cb);
@@ -242,8 +251,9 @@ hipError_t start_request(bls_server *s, Req *r) {
 
 // One persistent launch over segments [s0, s0 + n) of the tick's arrays;
 // seg_start holds n + 1 entries from sbase.
-hipError_t launch_kind(bls_server *s, int b, bool weighted, int s0, int sbase, int n,
-                       int64_t items, int hist_bytes, unsigned long long *counter) {
+hipError_t launch_kind(bls_server *s, int b, int kind, int s0, int sbase, int n, int64_t items,
+                       const LdsLayout &lds, unsigned long long *counter) {
+  const bool weighted = kind >= 2, block = (kind & 1) != 0;
   if (n == 0 || items == 0) return hipSuccess;
   SearchArgs a;
   memset(&a, 0, sizeof a);
@@ -264,11 +274,13 @@ hipError_t launch_kind(bls_server *s, int b, bool weighted, int s0, int sbase, i
   a.jstart = s->d_js;
   a.kwidth = s->d_ks;
   a.best_key = s->d_keys;
-  a.hist_bytes = hist_bytes;
+  a.hist_bytes = lds.total();
+  a.scr_bytes = lds.scratch;
+  a.scr_offset = lds.planes;
   single_partition(a);
   const bool dip = (s->cfg.flags & BLS_DIP_ONLY) != 0;
   int per_cu = 1;
-  hipError_t e = (hipError_t)search_blocks_per_cu(weighted, dip, hist_bytes, &per_cu);
+  hipError_t e = (hipError_t)search_blocks_per_cu(weighted, dip, block, a.hist_bytes, &per_cu);
   if (e != hipSuccess) return e;
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(items, (int64_t)s->num_cus *
                                                                           std::max(per_cu, 1)));
@@ -278,42 +290,42 @@ hipError_t launch_kind(bls_server *s, int b, bool weighted, int s0, int sbase, i
 hipError_t launch_tick(bls_server *s, Tick &tk) {
   const int b = tk.buf;
   const int nseg = (int)tk.segs.size();
-  const int nu = tk.nu, nw = nseg - nu;
-  // seg_start: the unit-weight launch's nu + 1 entries, then the weighted
-  // launch's nw + 1; seg_curve and seg_tile0: nu, then nw entries.  Packed
-  // in that order: 8 (nseg + 2) + 4 nseg + 4 nseg bytes.
-  const size_t o_curve = 8 * (size_t)(nseg + 2), o_tile0 = o_curve + 4 * (size_t)nseg;
+  // seg_start: each kind's n + 1 entries in turn; seg_curve and seg_tile0:
+  // the segments in the same order.  Packed one after the other: 8 (nseg +
+  // kKinds) + 4 nseg + 4 nseg bytes.
+  const size_t o_curve = 8 * (size_t)(nseg + kKinds), o_tile0 = o_curve + 4 * (size_t)nseg;
   int64_t *h_start = reinterpret_cast<int64_t *>(s->h_seg[b]);
   int32_t *h_curve = reinterpret_cast<int32_t *>(s->h_seg[b] + o_curve);
   int32_t *h_tile0 = reinterpret_cast<int32_t *>(s->h_seg[b] + o_tile0);
   s->d_seg_start[b] = reinterpret_cast<int64_t *>(s->d_seg[b]);
   s->d_seg_curve[b] = reinterpret_cast<int32_t *>(s->d_seg[b] + o_curve);
   s->d_seg_tile0[b] = reinterpret_cast<int32_t *>(s->d_seg[b] + o_tile0);
-  int64_t items[2] = {0, 0};
-  int hist[2] = {0, 0};
-  for (int i = 0; i < nseg; ++i) {
-    const TickSegment &g = tk.segs[i];
-    const int kind = i < nu ? 0 : 1;
+  int64_t items[kKinds] = {};
+  LdsLayout lds[kKinds];
+  int i = 0;
+  for (int kind = 0; kind < kKinds; ++kind) {
+    for (int k = 0; k < tk.n[kind]; ++k, ++i) {
+      const TickSegment &g = tk.segs[i];
+      h_start[i + kind] = items[kind];
+      h_curve[i] = g.slot;
+      h_tile0[i] = g.tile0;
+      items[kind] += g.ntiles;
+      lds[kind].add(s->h_curves[g.slot], (kind & 1) != 0);
+    }
     h_start[i + kind] = items[kind];
-    h_curve[i] = g.slot;
-    h_tile0[i] = g.tile0;
-    items[kind] += g.ntiles;
-    const Req *r = s->slots[g.slot];
-    hist[kind] = std::max(hist[kind], r->tile * r->hstride * 8 * (kind ? 2 : 1));
   }
-  h_start[nu] = items[0];
-  h_start[nseg + 1] = items[1];
   hipStream_t st = s->stream;
   hipError_t e;
   if ((e = hipMemcpyAsync(s->d_seg[b], s->h_seg[b], o_tile0 + 4 * (size_t)nseg,
                           hipMemcpyHostToDevice, st)))
     return e;
-  // eight counters: the unit-weight launch takes the first, the weighted the fifth
+  // eight counters, two apart for the kinds' launches
   if ((e = (hipError_t)launch_fill(s->d_counter[b], nullptr, 0, st))) return e;
   if ((e = hipEventRecord(s->ev_s[b], st))) return e;
-  if ((e = launch_kind(s, b, false, 0, 0, nu, items[0], hist[0], s->d_counter[b]))) return e;
-  if ((e = launch_kind(s, b, true, nu, nu + 1, nw, items[1], hist[1], s->d_counter[b] + 4)))
-    return e;
+  for (int kind = 0, s0 = 0; kind < kKinds; s0 += tk.n[kind], ++kind)
+    if ((e = launch_kind(s, b, kind, s0, s0 + kind, tk.n[kind], items[kind], lds[kind],
+                         s->d_counter[b] + 2 * kind)))
+      return e;
   return hipEventRecord(s->ev_e[b], st);
 }
 
@@ -537,12 +549,11 @@ void scheduler(bls_server *s) {
       if (!work.empty()) {
         tk.buf = next_buf;
         tk.segs = build_tick(work, s->tick_cost, 1);
-        // unit-weight segments first: each kind is one launch of the tick
-        std::stable_partition(tk.segs.begin(), tk.segs.end(), [&](const TickSegment &g) {
-          return !s->slots[g.slot]->weighted;
-        });
-        tk.nu = 0;
-        for (const TickSegment &g : tk.segs) tk.nu += s->slots[g.slot]->weighted ? 0 : 1;
+        std::stable_sort(tk.segs.begin(), tk.segs.end(),
+                         [&](const TickSegment &x, const TickSegment &y) {
+                           return kind_of(s->slots[x.slot]) < kind_of(s->slots[y.slot]);
+                         });
+        for (const TickSegment &g : tk.segs) ++tk.n[kind_of(s->slots[g.slot])];
         for (const SlotWork &wk : work) s->slots[wk.slot]->issued = wk.next_tile;
         have_tick = !tk.segs.empty();
       }
@@ -683,10 +694,10 @@ int bls_server_create(bls_server **out, const bls_server_config *cfg_in) {
   s->d_js = reinterpret_cast<int32_t *>(s->d_depth + Q);
   s->d_ks = s->d_js + Q;
   for (int b = 0; b < kTickBuffers; ++b) {
-    if ((e = device_alloc((void **)&s->d_seg[b], 16 * (M + 1))) ||
+    if ((e = device_alloc((void **)&s->d_seg[b], 16 * (M + 2))) ||
         (e = device_alloc((void **)&s->d_counter[b], 64)))
       return fail(srv_hip(s, e, "allocate tick buffers"));
-    if ((e = hipHostMalloc((void **)&s->h_seg[b], 16 * (M + 1), 0)))
+    if ((e = hipHostMalloc((void **)&s->h_seg[b], 16 * (M + 2), 0)))
       return fail(srv_hip(s, e, "allocate pinned tick buffers"));
     if ((e = hipEventCreate(&s->ev_s[b])) || (e = hipEventCreate(&s->ev_e[b])))
       return fail(srv_hip(s, e, "create events"));
@@ -807,7 +818,13 @@ int bls_server_submit(bls_server *s, const bls_request *q, uint64_t *ticket) {
   }
   const int wpb = r->weighted ? 2 : 1;
   int T = 1, hs = 0;
-  fit_tile(r->nbins, r->kmax, r->np, s->lds_budget, kTileMax, r->weighted, &T, &hs);
+  r->block = block_batch(shapes.data(), 1, r->weighted, s->max_lds);
+  if (r->block)
+    fit_block_tile(r->nbins, r->kmin, r->kmax, r->np,
+                   block_lds_budget(shapes[0], r->weighted, s->max_lds), 4, r->weighted, &T, &hs,
+                   &r->geom);
+  else
+    fit_tile(r->nbins, r->kmax, r->np, s->lds_budget, kTileMax, r->weighted, &T, &hs);
   const int per_period = hs * 8 * wpb;
   r->tile = T;
   r->hstride = hs;
