@@ -130,5 +130,36 @@ __device__ inline double wave_sum(double v) {
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
+// A DPP move whose lanes without a source get 0.
+template <int CTRL>
+__device__ __forceinline__ int dpp_zero(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
+}
+// Largest of the lanes' non-negative values (every lane's result): their bits
+// compare as the values do, and an integer maximum takes its DPP operand
+// directly.
+template <int CTRL>
+__device__ __forceinline__ unsigned max_step(unsigned v) {
+  const unsigned o = (unsigned)dpp_zero<CTRL>((int)v);
+  return v > o ? v : o;
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned max_rows(unsigned v) {
+  const unsigned o = (unsigned)dpp_i32<CTRL, ROWS>((int)v);
+  return v > o ? v : o;
+}
+__device__ __forceinline__ unsigned wave_umax(unsigned v) {
+  v = max_step<0xb1>(v);
+  v = max_step<0x4e>(v);
+  v = max_step<0x141>(v);
+  v = max_step<0x140>(v);
+  v = max_rows<0x142, 0xa>(v);
+  v = max_rows<0x143, 0xc>(v);
+  return (unsigned)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ float wave_fmax(float v) {
+  return __uint_as_float(wave_umax(__float_as_uint(v)));
+}
+
 }  // namespace
 }  // namespace bls

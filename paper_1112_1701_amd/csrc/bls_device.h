@@ -168,13 +168,24 @@ inline void single_partition(SearchArgs &a) {
   for (int x = 0; x <= kMaxParts; ++x) a.part_begin[x] = x == 0 ? 0 : a.nitems;
 }
 
-// Unbinned search: bytes of per-point arrays for curves of up to n points
-// (LDS, or a workspace slice per workgroup above kUnbinnedMaxPoints).
-int64_t unbinned_lds_bytes(int n, bool weighted);
-int launch_unbinned(const SearchArgs &a, bool weighted, bool dip_only, int grid, void *stream);
-int unbinned_blocks_per_cu(bool weighted, bool dip_only, bool glob, int lds_bytes, int *blocks);
+// Unbinned search, curves of up to n points: where the per-point arrays are,
+// their bytes, and the LDS of a workgroup.  Above kUnbinnedMaxPoints they are
+// in a workspace slice per workgroup; up to kUnbCellsMaxPoints the sort's cell
+// counts then have the LDS to themselves (with 8192 cells four workgroups
+// share a CU, a cell holds at most four points on average, and the table of
+// the large blocks fits where the counts were).
 constexpr int kUnbinnedMaxPoints = 4096;         // per-point arrays in LDS
 constexpr int kUnbinnedMaxPointsGlobal = 1 << 20;  // in a device workspace
+constexpr int kUnbMaxCells = 8192;
+constexpr int kUnbCellsMaxPoints = 32768;
+enum : int { kUnbLds = 0, kUnbCells = 1, kUnbGlobal = 2 };
+inline int unbinned_mode(int n) {
+  return n <= kUnbinnedMaxPoints ? kUnbLds : n <= kUnbCellsMaxPoints ? kUnbCells : kUnbGlobal;
+}
+int64_t unbinned_array_bytes(int n, bool weighted);
+int unbinned_lds_bytes(int n, bool weighted);
+int launch_unbinned(const SearchArgs &a, bool weighted, bool dip_only, int grid, void *stream);
+int unbinned_blocks_per_cu(bool weighted, bool dip_only, int ucap, int *blocks);
 
 struct DetectDesc {
   int64_t p_off;     // first trial period of the curve

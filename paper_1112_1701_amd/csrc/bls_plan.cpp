@@ -1448,16 +1448,14 @@ int bls_search_unbinned_device(bls_plan *p, const bls_batch *b, const bls_unbinn
   layout_partitions(p, cost, items_of, pb);
   const int64_t items = pb.nitems;
   pb.ucap = ucap;
-  // Curves up to kUnbinnedMaxPoints keep their per-point arrays in LDS;
-  // longer ones in a device workspace slice per workgroup.
-  const bool glob = ucap > kUnbinnedMaxPoints;
-  const int64_t arrays = unbinned_lds_bytes(ucap, weighted);
-  pb.hist_bytes = glob ? 0 : (int32_t)arrays;
+  const bool glob = unbinned_mode(ucap) != kUnbLds;
+  const int64_t arrays = unbinned_array_bytes(ucap, weighted);
+  pb.hist_bytes = unbinned_lds_bytes(ucap, weighted);
   if (pb.hist_bytes > p->max_lds - 2048)
     return set_error(p, BLS_ERR_CAPACITY, "curve too long for the unbinned search's LDS");
   int per_cu = 0;
-  if ((e = (hipError_t)unbinned_blocks_per_cu(weighted, (p->cfg.flags & BLS_DIP_ONLY) != 0, glob,
-                                              pb.hist_bytes, &per_cu)) != hipSuccess)
+  if ((e = (hipError_t)unbinned_blocks_per_cu(weighted, (p->cfg.flags & BLS_DIP_ONLY) != 0, ucap,
+                                              &per_cu)) != hipSuccess)
     return hip_error(p, e, "occupancy query");
   if (per_cu < 1) return set_error(p, BLS_ERR_CAPACITY, "unbinned kernel does not fit a CU");
   int64_t grid = std::min<int64_t>(items, (int64_t)p->num_cus * per_cu);
