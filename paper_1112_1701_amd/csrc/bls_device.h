@@ -232,6 +232,7 @@ struct WindowArgs {
   int32_t min_eclipses; // 1 or 2
   double duration;
   unsigned int *overflow;  // set when a cycle number exceeds kMaxCycle
+  bool per_wave;           // window_wave_kernel
 };
 constexpr int kMaxCycle = 1 << 29;
 
@@ -240,8 +241,12 @@ constexpr int kMaxCycle = 1 << 29;
 // entries past a period's wrapped copy without using them, s the entries
 // per lane (at most the value below, for windows of nphase bins).
 constexpr int window_pad(int nphase) { return ((2 * nphase - 1 + 63) >> 6) | 1; }
-constexpr int window_lds_bytes(int tile, int nphase) {
-  return (tile * nphase + window_pad(nphase)) * 8;
+// per_wave: every wave has the bins of its period (rows of window_stride
+// entries), otherwise the workgroup those of a tile.
+constexpr int window_stride(int nphase) { return (nphase + 1) & ~1; }
+constexpr int window_lds_bytes(int tile, int nphase, bool per_wave) {
+  return ((per_wave ? kBlock / 64 * window_stride(nphase) : tile * nphase) +
+          window_pad(nphase)) * 8;
 }
 // Static LDS of the window kernel (period frequencies and window lengths).
 constexpr int kWindowStaticLds = kTileMax * (8 + 4);
@@ -278,7 +283,7 @@ struct VarArgs {
 };
 
 int launch_variability(const VarArgs &a, void *stream);
-int window_blocks_per_cu(int lds_bytes, int *blocks);
+int window_blocks_per_cu(bool per_wave, int min_eclipses, int lds_bytes, int *blocks);
 
 // Launch wrappers (bls_kernels.hip).  All return hipError_t as int.
 int launch_detect(const DetectArgs &a, void *stream);

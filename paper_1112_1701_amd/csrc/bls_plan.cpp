@@ -1558,11 +1558,23 @@ int bls_eclipse_window_device(bls_plan *p, const bls_batch *b, int32_t nphase, d
       (!b->p_off && b->nperiods_shared < 1))
     return set_error(p, BLS_ERR_INVALID_ARG, "n_off[0] and p_off[0] must be 0, grid non-empty");
   const int nc = b->ncurves;
-  // up to 32 KB of LDS per workgroup (four periods at 1000 phase bins, one
-  // per wave in the window pass): five workgroups per CU
-  const int tile = std::max(
+  // up to 32 KB of LDS per workgroup: five workgroups per CU
+  int tile = std::max(
       1, std::min(kTileMax, ((32 << 10) - kWindowStaticLds - 8 * window_pad(nphase)) /
                                 (8 * nphase)));
+  // A wave per period where the LDS then holds two workgroups' bins and the
+  // call has periods for four rounds of them (call, the workgroup on a period
+  // / a wave each: 24 x 100000 periods, 200 bins 2.00 / 1.79 ms, 1000 bins 3.13
+  // / 2.64; 24 x 50000, 2000 bins 4.89 / 3.06; 12 x 50000, 3000 bins, one
+  // workgroup per CU, 3.27 / 3.82; 4 x 20000, 1000 bins 0.212 / 0.189, but 2 x
+  // 4500 0.097 / 0.100), up to eight periods per wave and item.
+  const double waves = std::max(p->num_cus, 1) * 4.0 * (kBlock / 64);
+  double periods = 0.0;  // (checked below)
+  for (int c = 0; c < nc; ++c)
+    periods += b->p_off ? (double)b->p_off[c + 1] - (double)b->p_off[c] : (double)b->nperiods_shared;
+  const bool per_wave =
+      2 * window_lds_bytes(tile, nphase, true) <= p->max_lds && periods >= 4 * waves;
+  if (per_wave) tile = (int)std::min(8.0, periods / waves) * (kBlock / 64);
   std::vector<WindowDesc> wd(nc);
   int64_t items = 0, results = 0;
   for (int c = 0; c < nc; ++c) {
@@ -1597,9 +1609,9 @@ int bls_eclipse_window_device(bls_plan *p, const bls_batch *b, int32_t nphase, d
       return hip_error(p, e, "allocate eclipse-window buffers");
     }
   }
-  const int lds = window_lds_bytes(tile, nphase);
+  const int lds = window_lds_bytes(tile, nphase, per_wave);
   int per_cu = 0;
-  if ((e = (hipError_t)window_blocks_per_cu(lds, &per_cu)) != hipSuccess)
+  if ((e = (hipError_t)window_blocks_per_cu(per_wave, min_eclipses, lds, &per_cu)) != hipSuccess)
     return hip_error(p, e, "window occupancy");
   const int64_t grid = std::min<int64_t>(items, (int64_t)std::max(per_cu, 1) * p->num_cus * 4);
   hipStream_t s = p->stream;
@@ -1621,6 +1633,7 @@ int bls_eclipse_window_device(bls_plan *p, const bls_batch *b, int32_t nphase, d
   a.min_eclipses = min_eclipses;
   a.duration = duration;
   a.overflow = p->d_window_flag;
+  a.per_wave = per_wave;
   if ((e = hipEventRecord(p->ev_search0, s)) != hipSuccess) return hip_error(p, e, "event");
   if ((e = (hipError_t)launch_window(a, (int)grid, s))) return hip_error(p, e, "launch window");
   if ((e = hipEventRecord(p->ev_search1, s)) != hipSuccess) return hip_error(p, e, "event");

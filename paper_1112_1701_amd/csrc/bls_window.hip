@@ -124,28 +124,41 @@ __device__ __forceinline__ int window_period(const int2 *row, int nb, int k) {
   // the unwrapped frame where the lane crosses.
   const int sl = nb / s, mc = nb - sl * s;
   const int wa = lane >= sl ? 1 : 0, wb = lane > sl ? 1 : 0;
-  // the next filled entry (none yet: a key no entry has makes the first
-  // one found take NB(q+1) = p_pos = kWinOut)
+  // Positions are offsets in the lane's entries until the walk is over (a
+  // scalar at each step).  The next filled entry (none yet: a key no entry
+  // has makes the first one found take NB(q+1) = p_pos = kWinOut):
   int p_pos = kWinOut, p_key = kWinNone, p_nb = kWinOut;
   int g = kWinInf;      // G of the next filled entry = D of the entries so far
   int last = -1;        // the lane's last filled entry
-  int olo = kWinInf;    // lowest entry whose D is NB past the lane
+  int nout = 0;         // entries whose D is NB past the lane: last and those before it
   int cnt = 0;
-  auto step = [&](int m, const int2 *r, int kk) {
-    const int x = base + m;
-    const int2 v = r[x];
-    const bool fl = v.x <= v.y;
-    const bool mx = GAP ? v.x < v.y : fl;
-    const int key = mx ? x + kWinMix : v.x;
-    const int nq = key != p_key ? p_pos : p_nb;
-    const int gq = mx ? x : nq;
-    p_pos = fl ? x : p_pos;
-    p_key = fl ? key : p_key;
-    p_nb = fl ? nq : p_nb;
-    g = fl ? gq : g;
-    last = max(last, fl ? x : -1);
-    olo = g == kWinOut ? x : olo;
-    cnt += g < x + kk ? 1 : 0;
+  // A filled entry's part runs under the execution mask: that takes fewer
+  // instructions than selecting each of its results (14 against 20 a step).
+  auto step = [&](int m, const int2 v) {
+    if (v.x <= v.y) {
+      asm volatile("");  // (a branch, not selects)
+      const bool mx = GAP ? v.x < v.y : true;
+      const int key = mx ? m + kWinMix : v.x;
+      p_nb = key != p_key ? p_pos : p_nb;
+      g = mx ? m : p_nb;
+      p_pos = m;
+      p_key = key;
+      last = max(last, m);
+    }
+    nout += g == kWinOut ? 1 : 0;
+    cnt += g < m + k ? 1 : 0;
+  };
+  // entries m1 - 1 down to m0, four loads at a time
+  auto walk = [&](int m1, int m0, const int2 *r) {
+    for (; m1 - 4 >= m0; m1 -= 4) {
+      const int2 *q = r + (m1 - 4);
+      const int2 a = q[3], b = q[2], c = q[1], d = q[0];
+      step(m1 - 1, a);
+      step(m1 - 2, b);
+      step(m1 - 3, c);
+      step(m1 - 4, d);
+    }
+    for (; m1 > m0; --m1) step(m1 - 1, r[m1 - 1]);
   };
   // wrapped entries x read bin x - nb; entries from L on decide nothing:
   // a lane holding only such entries reads the first s bins, the lane
@@ -153,61 +166,168 @@ __device__ __forceinline__ int window_period(const int2 *row, int nb, int k) {
   // copy (into the next period or the workspace's padding).  Only unwrapped
   // entries start windows.
   const bool idle = base >= L;
-  const int2 *ra = row - (idle ? base : wa * nb), *rb = row - (idle ? base : wb * nb);
-  const int ka = wa ? 0 : k, kb = wb ? 0 : k;
-  for (int m = s - 1; m >= mc; --m) step(m, ra, ka);
+  const int2 *ra = row + (idle ? 0 : base - wa * nb), *rb = row + (idle ? 0 : base - wb * nb);
+  walk(s, mc, ra);
   if (p_key < kWinMix) p_key -= wa - wb;
-  for (int m = mc - 1; m >= 0; --m) step(m, rb, kb);
+  if (wa) cnt = 0;
+  walk(mc, 0, rb);
   if (p_key < kWinMix) p_key -= wb;
-  // the lane's first filled entry is p (G(p) = g), its last one `last`
+  if (wb) cnt = 0;
+  // to positions among all entries
+  auto place = [&](int x) { return x < kWinOut ? x + base : x; };
   const bool any = last >= 0;
+  last = any ? last + base : -1;
+  p_pos = place(p_pos);
+  p_nb = place(p_nb);
+  g = place(g);
+  if (p_key >= kWinMix) p_key += base;
+  // the lane's first filled entry is p (G(p) = g), its last one `last`
   int l_key = kWinNone;
   if (any) {
     // (an entry from L on, read from any bin, decides nothing)
     const int wrap = last >= nb ? 1 : 0;
-    const int2 v = row[min(last - wrap * nb, nb - 1)];
-    l_key = (GAP ? v.x < v.y : true) ? last + kWinMix : v.x - wrap;
+    const int2 e = row[min(last - wrap * nb, nb - 1)];
+    l_key = (GAP ? e.x < e.y : true) ? last + kWinMix : e.x - wrap;
   }
+  // The lanes' parts are in the order of their entries, so the value a lane
+  // needs from the lanes before or after is that of the nearest one that has
+  // any: its number from a ballot, its value in one exchange.
+  const unsigned long long below = (1ull << lane) - 1ull, above = ~below << 1;
+  const unsigned long long filled = __builtin_amdgcn_ballot_w64(any);
+  auto from = [&](int v, int l) { return __builtin_amdgcn_ds_bpermute(l << 2, v); };
+  auto next_lane = [&](unsigned long long m) { return (int)__builtin_ctzll(m | (1ull << 63)); };
   // the key of the last filled entry of the lanes before
-  int xs = l_key;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(xs, d, 64);
-    if (lane >= d && xs == kWinNone) xs = y;
-  }
-  int carry = __shfl_up(xs, 1, 64);
-  if (lane == 0) carry = kWinNone;
-  const bool bf = any && (carry != kWinNone ? carry != p_key : p_key >= kWinMix);
+  const bool before = (filled & below) != 0ull;
+  const int carry = from(l_key, 63 - (int)__builtin_clzll((filled & below) | 1ull));
+  const bool bf = any && (before ? carry != p_key : p_key >= kWinMix);
   // the lane's first B: its first filled entry, or NB past it
-  int nbx = bf ? p_pos : (any && p_nb != kWinOut ? p_nb : kWinInf);
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_down(nbx, d, 64);
-    if (lane + d < 64) nbx = min(nbx, y);
-  }
-  int nb_out = __shfl_down(nbx, 1, 64);
-  if (lane == 63) nb_out = kWinInf;
-  // entries olo .. last have D = NB past the lane
-  if (any && olo <= last && nb_out < kWinInf)
-    cnt += max(0, min(last + 1, nb) - max(olo, nb_out - k + 1));
+  const int nbx = bf ? p_pos : (any && p_nb != kWinOut ? p_nb : kWinInf);
+  const unsigned long long nbm = __builtin_amdgcn_ballot_w64(nbx != kWinInf) & above;
+  const int nb_next = from(nbx, next_lane(nbm));
+  const int nb_out = nbm != 0ull ? nb_next : kWinInf;
+  // nout entries up to the last filled one have D = NB past the lane
+  if (nout > 0 && nb_out < kWinInf)
+    cnt += max(0, min(last + 1, nb) - max(last + 1 - nout, nb_out - k + 1));
   // the entries after the last filled one have D = G of the next filled
   // entry of the lanes after
-  int gx = any ? (g == kWinOut ? nb_out : g) : -1;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_down(gx, d, 64);
-    if (lane + d < 64 && gx < 0) gx = y;
-  }
-  int gc = __shfl_down(gx, 1, 64);
-  if (lane == 63) gc = -1;
-  if (gc >= 0 && gc < kWinInf)
+  const int gc = from(g == kWinOut ? nb_out : g, next_lane(filled & above));
+  if ((filled & above) != 0ull && gc < kWinInf)
     cnt += max(0, min(base + s, nb) - max(max(last + 1, base), gc - k + 1));
   return wave_isum(cnt);
 }
 
+// One kept time in its bin: the cycle numbers' extremes (clamped at kMaxCycle,
+// which the period's set-up has flagged: the largest d f of the cadence is its
+// last kept time's).
+__device__ __forceinline__ void fold_cycle(double d, double f, double nbd, unsigned nbm1,
+                                           int2 *row) {
+  const double cyc = d * f;  // not negative: the conversion is the floor
+  const int b = (int)min((unsigned)(int)(__builtin_amdgcn_fract(cyc) * nbd), nbm1);
+  const int e = min((int)cyc, kMaxCycle);
+  int *w2 = reinterpret_cast<int *>(row + b);
+  atomicMin(w2, e);
+  atomicMax(w2 + 1, e);
+}
+
+// Bins of a window at frequency f.
+__device__ __forceinline__ int window_bins(double duration, double f, int nb) {
+  const double kr = __builtin_round(duration * f * (double)nb);
+  return kr < 1.0 ? 1 : kr > (double)nb ? nb : (int)kr;
+}
+
+// A wave per period, from the clearing of its bins to its count: without
+// barriers, and no wave folds a remainder that the others wait for.  VALU-
+// bound, 540 instructions a period of 570 times and 1000 bins at 0.77 issued
+// per CU and clock: 24 cadences x 100000 periods 2.64 ms, 3.80 with both the
+// workgroup's waves on a period in the fold and a window pass of selects (740
+// instructions).
+template <int GAP>
+__global__ __launch_bounds__(kBlock) void window_wave_kernel(WindowArgs a) {
+  extern __shared__ __align__(16) int2 s_mm[];  // [wave][nphase] (min, max cycle), padding
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nb = a.nphase;
+  const double nbd = (double)nb;
+  const unsigned nbm1 = (unsigned)(nb - 1);
+  int2 *row = s_mm + wave * window_stride(nb);
+  const int share = a.tile / (kBlock / 64);
+  // (the cadence of the item, and its times, as in window_kernel)
+  int cur = 0;
+  int64_t next0 = a.ncurves > 1 ? a.desc[1].item0 : a.nitems;
+  WindowDesc wd = a.desc[0];
+  constexpr int kRegs = 16;
+  double d[kRegs];
+  int cached = -1;
+  for (int64_t item = blockIdx.x; item < a.nitems; item += gridDim.x) {
+    if (item >= next0) {
+      while (cur + 1 < a.ncurves && a.desc[cur + 1].item0 <= item) ++cur;
+      wd = a.desc[cur];
+      next0 = cur + 1 < a.ncurves ? a.desc[cur + 1].item0 : a.nitems;
+    }
+    const int p0 = (int)(item - wd.item0) * a.tile + wave * share;
+    const int np = min(share, wd.nperiods - p0);
+    if (np <= 0) continue;
+    int32_t *out = a.observed + wd.r_off + p0;
+    if (wd.status != kCurveOk) {
+      if (lane < np) out[lane] = -1;
+      continue;
+    }
+    // frequencies and windows of the share, a lane each
+    double fl = 0.0;
+    int kl = 1;
+    if (lane < np) {
+      fl = 1.0 / a.periods[wd.p_off + p0 + lane];
+      kl = window_bins(a.duration, fl, nb);
+      if (wd.dmax * fl >= (double)kMaxCycle) atomicOr(a.overflow, 1u);
+    }
+    const int n = __builtin_amdgcn_readfirstlane((int)min(wd.n, (int64_t)INT32_MAX));
+    const bool regs = n <= 64 * kRegs;
+    if (regs && cached != cur) {
+#pragma unroll
+      for (int r = 0; r < kRegs; ++r) {
+        const int i = lane + 64 * r;
+        const double w = i < n ? (a.w ? a.w[wd.n_off + i] : 1.0) : 0.0;
+        d[r] = w != 0.0 ? a.t[wd.n_off + i] - wd.t0 : -1.0;  // (-1: not kept)
+      }
+      cached = cur;
+    }
+    int res = 0;
+    for (int t = 0; t < np; ++t) {
+      const double f = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(fl), t),
+                                        __builtin_amdgcn_readlane(__double2loint(fl), t));
+      const int k = __builtin_amdgcn_readlane(kl, t);
+      for (int i = lane; i < (nb + 1) / 2; i += 64)
+        reinterpret_cast<int4 *>(row)[i] =
+            make_int4(kCycleEmptyLo, kCycleEmptyHi, kCycleEmptyLo, kCycleEmptyHi);
+      // (LDS operations of one wave complete in order)
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      if (regs) {
+#pragma unroll
+        for (int r = 0; r < kRegs; ++r)
+          if (64 * r < n && d[r] >= 0.0) fold_cycle(d[r], f, nbd, nbm1, row);
+      } else {
+#pragma unroll 4
+        for (int64_t i = lane; i < wd.n; i += 64) {
+          const double w = a.w ? a.w[wd.n_off + i] : 1.0;
+          const double ti = a.t[wd.n_off + i];
+          if (w != 0.0) fold_cycle(ti - wd.t0, f, nbd, nbm1, row);
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int c = window_period<GAP>(row, nb, k);
+      res = lane == t ? c : res;
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    if (lane < np) out[lane] = res;
+  }
+}
+
 template <int GAP>
 __global__ __launch_bounds__(kBlock) void window_kernel(WindowArgs a) {
-  extern __shared__ int2 s_mm[];            // [tile][nphase] (min, max cycle), padding
+  extern __shared__ __align__(16) int2 s_mm[];            // [tile][nphase] (min, max cycle), padding
   __shared__ double s_f[kTileMax];
   __shared__ int s_k[kTileMax];
   static_assert(sizeof(s_f) + sizeof(s_k) == kWindowStaticLds, "window kernel static LDS");
@@ -245,26 +365,16 @@ __global__ __launch_bounds__(kBlock) void window_kernel(WindowArgs a) {
     } else {
     if (tid < np) {
       const double f = 1.0 / a.periods[wd.p_off + p0 + tid];
-      const double kr = __builtin_round(a.duration * f * nbd);
       s_f[tid] = f;
-      s_k[tid] = kr < 1.0 ? 1 : kr > nbd ? nb : (int)kr;
+      s_k[tid] = window_bins(a.duration, f, nb);
       if (wd.dmax * f >= (double)kMaxCycle) atomicOr(a.overflow, 1u);
     }
-    for (int i = tid; i < np * nb; i += kBlock) s_mm[i] = make_int2(kCycleEmptyLo, kCycleEmptyHi);
+    for (int i = tid; i < (np * nb + 1) / 2; i += kBlock)  // (one entry more: the padding's)
+      reinterpret_cast<int4 *>(s_mm)[i] =
+          make_int4(kCycleEmptyLo, kCycleEmptyHi, kCycleEmptyLo, kCycleEmptyHi);
     __syncthreads();
 
-    // Fold: cycle numbers per bin (clamped at kMaxCycle, which the item's
-    // set-up has flagged: the largest d f of the cadence is its last kept
-    // time's).
-    auto fold_point = [&](double d, double f, int2 *row) {
-      const double cyc = d * f;
-      const double e = floor(cyc);
-      const int b = (int)min((unsigned)(int)(__builtin_amdgcn_fract(cyc) * nbd), nbm1);
-      const int ei = (int)fmin(e, (double)kMaxCycle);
-      int *w2 = reinterpret_cast<int *>(row + b);
-      atomicMin(w2, ei);
-      atomicMax(w2 + 1, ei);
-    };
+    // Fold: cycle numbers per bin.
     if (wd.n <= (int64_t)kBlock * kWinRegs) {
       if (cached != cur) {
 #pragma unroll
@@ -281,7 +391,7 @@ __global__ __launch_bounds__(kBlock) void window_kernel(WindowArgs a) {
         const double f = s_f[t];
 #pragma unroll
         for (int r = 0; r < kWinRegs; ++r)
-          if (kreg[r]) fold_point(dreg[r], f, s_mm + t * nb);
+          if (kreg[r]) fold_cycle(dreg[r], f, nbd, nbm1, s_mm + t * nb);
       }
     } else {
       for (int t = 0; t < np; ++t) {
@@ -289,7 +399,7 @@ __global__ __launch_bounds__(kBlock) void window_kernel(WindowArgs a) {
         for (int64_t i = tid; i < wd.n; i += kBlock) {
           const double wi = a.w ? a.w[wd.n_off + i] : 1.0;
           if (wi == 0.0) continue;
-          fold_point(a.t[wd.n_off + i] - wd.t0, f, s_mm + t * nb);
+          fold_cycle(a.t[wd.n_off + i] - wd.t0, f, nbd, nbm1, s_mm + t * nb);
         }
       }
     }
@@ -308,15 +418,22 @@ __global__ __launch_bounds__(kBlock) void window_kernel(WindowArgs a) {
 
 }  // namespace
 
+const void *window_fn(bool per_wave, int min_eclipses) {
+  if (per_wave)
+    return min_eclipses >= 2 ? reinterpret_cast<const void *>(&window_wave_kernel<1>)
+                             : reinterpret_cast<const void *>(&window_wave_kernel<0>);
+  return min_eclipses >= 2 ? reinterpret_cast<const void *>(&window_kernel<1>)
+                           : reinterpret_cast<const void *>(&window_kernel<0>);
+}
+
 int launch_window(const WindowArgs &a, int grid, void *stream) {
   if (a.ncurves <= 0) return 0;
   hipLaunchKernelGGL(window_prep_kernel, dim3(a.ncurves), dim3(kBlock), 0, (hipStream_t)stream,
                      a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.nitems <= 0) return (int)e;
-  const int lds = window_lds_bytes(a.tile, a.nphase);
-  const void *fn = a.min_eclipses >= 2 ? reinterpret_cast<const void *>(&window_kernel<1>)
-                                       : reinterpret_cast<const void *>(&window_kernel<0>);
+  const int lds = window_lds_bytes(a.tile, a.nphase, a.per_wave);
+  const void *fn = window_fn(a.per_wave, a.min_eclipses);
   e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return (int)e;
   void *args[] = {const_cast<WindowArgs *>(&a)};
@@ -325,9 +442,8 @@ int launch_window(const WindowArgs &a, int grid, void *stream) {
   return (int)hipGetLastError();
 }
 
-
-int window_blocks_per_cu(int lds_bytes, int *blocks) {
-  const void *fn = reinterpret_cast<const void *>(&window_kernel<1>);
+int window_blocks_per_cu(bool per_wave, int min_eclipses, int lds_bytes, int *blocks) {
+  const void *fn = window_fn(per_wave, min_eclipses);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes);
   if (e != hipSuccess) return (int)e;
   return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, kBlock, (size_t)lds_bytes);
