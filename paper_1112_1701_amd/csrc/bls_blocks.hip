@@ -760,6 +760,7 @@ __attribute__((amdgpu_waves_per_eu(WEIGHTED ? 5 : 6))) void block_search_kernel(
   __shared__ double s_S[kGroupMax];
   __shared__ double s_R[kGroupMax];
   __shared__ int s_jk[kGroupMax];
+  __shared__ Claims s_claims;
   __shared__ long long s_item;
   __shared__ int s_curve;
   __shared__ int s_p0, s_gp0, s_gp1, s_t, s_edge;
@@ -771,11 +772,10 @@ __attribute__((amdgpu_waves_per_eu(WEIGHTED ? 5 : 6))) void block_search_kernel(
       reinterpret_cast<unsigned char *>(s_hist) + a.scr_offset + wave * a.scr_bytes;
   // Items and groups as in search_kernel: thread 0 claims one group ahead and
   // steps through the group's tiles.
-  unsigned done_mask = 0u;
-  SegCache sc = {0, 0, 0, 0};
   ItemRef nx = {-1, 0, 0};
   if (tid == 0) {
-    nx = claim_item(a, done_mask, sc);
+    claims_start(s_claims);
+    nx = claim_item(a, s_claims);
     s_p0 = 0;
     s_t = 0;
     s_gp1 = 0;
@@ -810,7 +810,7 @@ __attribute__((amdgpu_waves_per_eu(WEIGHTED ? 5 : 6))) void block_search_kernel(
     const int edge = __builtin_amdgcn_readfirstlane(s_edge);
     const int gp0 = __builtin_amdgcn_readfirstlane(s_gp0);
     const int gp1 = __builtin_amdgcn_readfirstlane(s_gp1);
-    if (tid == 0 && (edge & 1)) nx = claim_item(a, done_mask, sc);
+    if (tid == 0 && (edge & 1)) nx = claim_item(a, s_claims);
     // The curve's record, in LDS for the group: read where it is needed, its
     // fields do not occupy registers through the tile.
     if (edge & 1) {

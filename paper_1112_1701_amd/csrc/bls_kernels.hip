@@ -498,6 +498,7 @@ void search_kernel(SearchArgs a) {
   __shared__ float s_rdp[kGroupMax];
   __shared__ int s_rjk[kGroupMax];      // j & 0xFFFF | k << 16
   __shared__ unsigned long long s_gkey;  // the item's largest (SR, ~period)
+  __shared__ Claims s_claims;
   __shared__ long long s_item;
   __shared__ int s_curve;
   __shared__ int s_p0, s_gp0, s_gp1, s_t, s_edge;
@@ -512,11 +513,10 @@ void search_kernel(SearchArgs a) {
   // being searched (its item, curve, periods [gp0, gp1), tile t and the
   // current tile's start p0) lives in LDS, written and read by thread 0, so
   // the tile body keeps the register footprint of one tile.
-  unsigned done_mask = 0u;
-  SegCache sc = {0, 0, 0, 0};
   ItemRef nx = {-1, 0, 0};
   if (tid == 0) {
-    nx = claim_item(a, done_mask, sc);
+    claims_start(s_claims);
+    nx = claim_item(a, s_claims);
     s_p0 = 0;
     s_t = 0;
     s_gp1 = 0;
@@ -551,7 +551,7 @@ void search_kernel(SearchArgs a) {
     const int p0 = __builtin_amdgcn_readfirstlane(s_p0);
     const int edge = __builtin_amdgcn_readfirstlane(s_edge);
     __syncthreads();  // everyone has read the item before thread 0 takes the next
-    if (tid == 0 && (edge & 1)) nx = claim_item(a, done_mask, sc);
+    if (tid == 0 && (edge & 1)) nx = claim_item(a, s_claims);
 
     const CurveDesc cd = a.curves[c];
     const int np = min(cd.tile, __builtin_amdgcn_readfirstlane(s_gp1) - p0);

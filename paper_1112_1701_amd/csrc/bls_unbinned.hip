@@ -87,6 +87,7 @@ template <bool WEIGHTED, bool DIP, int MODE>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(4))) void unbinned_kernel(SearchArgs a) {
   extern __shared__ __align__(16) unsigned char s_lds[];
+  __shared__ Claims s_claims;
   __shared__ long long s_item;
   __shared__ int s_curve;
   __shared__ int s_per;
@@ -128,10 +129,11 @@ __attribute__((amdgpu_waves_per_eu(4))) void unbinned_kernel(SearchArgs a) {
   double *Pw = reinterpret_cast<double *>(grp);
   float2 *tab = reinterpret_cast<float2 *>(sq);
 
-  unsigned done_mask = 0u;
-  SegCache sc = {0, 0, 0, 0};
   ItemRef nx = {-1, 0, 0};
-  if (tid == 0) nx = claim_item(a, done_mask, sc);  // one item ahead
+  if (tid == 0) {
+    claims_start(s_claims);
+    nx = claim_item(a, s_claims);  // one item ahead
+  }
   for (;;) {
     if (tid == 0) {
       s_item = nx.item;
@@ -143,7 +145,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void unbinned_kernel(SearchArgs a) {
     const int c = __builtin_amdgcn_readfirstlane(s_curve);
     const int p = __builtin_amdgcn_readfirstlane(s_per);
     __syncthreads();
-    if (tid == 0) nx = claim_item(a, done_mask, sc);
+    if (tid == 0) nx = claim_item(a, s_claims);
 
     const CurveDesc cd = a.curves[c];
     const int64_t r_out = cd.r_off + p;
