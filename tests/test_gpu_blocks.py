@@ -63,7 +63,8 @@ def test_blocks_equal_every_box(bls, monkeypatch, nbins, qmin, qmax, n, weighted
 @pytest.mark.parametrize("kind", ["binary", "constant", "rounded", "outlier", "alternating"])
 @pytest.mark.parametrize("n,nbins,weights", [(2, 10, None), (8, 50, "spread"),
                                              (60, 400, None), (300, 150, "few"),
-                                             (3000, 64, None)])
+                                             (3000, 64, None), (40, 63, "few"),
+                                             (40, 64, "few"), (90, 100, "spread")])
 def test_blocks_ties(bls, monkeypatch, kind, n, nbins, weights):
     rng = np.random.default_rng(n + nbins)
     t = np.sort(rng.uniform(0.0, 30.0, n))
