@@ -257,7 +257,14 @@ TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool
   if (const char *s = getenv("BLS_TILE_CAP")) tc.tile_cap = atoi(s), env = true;
   if (const char *s = getenv("BLS_OCCUPANCY")) tc.occupancy = atoi(s), env = true;
   if (shapes.empty()) return tc;
-  tc.block = block_batch(shapes.data(), (int)shapes.size(), weighted, p->max_lds);
+  double evals = 0.0;
+  for (const CurveShape &s : shapes)
+    evals += (double)s.nbins * (double)(s.kmax - s.kmin + 1) * (double)s.nperiods;
+  // Tuning a new shape costs about 0.1 s of device time; a call with less
+  // work than that many box evaluations keeps the built-in table.
+  const bool tuned = !(p->cfg.flags & BLS_NO_AUTOTUNE) && evals >= kTuneMinEvals;
+  tc.block = block_batch(shapes.data(), (int)shapes.size(), weighted, p->cfg.min_in_points,
+                         tuned && !env, p->num_cus, p->max_lds);
   if (env) return tc;
   if (tc.block) {
     // The block search's tile follows from its LDS (block_tile).
@@ -270,12 +277,7 @@ TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool
   const CurveShape rep = median_shape(shapes);
   tc.lds_budget = untuned_lds_budget(rep, periods, weighted, p->num_cus);
   if (p->cfg.flags & BLS_NO_AUTOTUNE) return tc;
-  // Tuning a new shape costs about 0.1 s of device time; a call with less
-  // work than that many box evaluations keeps the built-in table.
-  double evals = 0.0;
-  for (const CurveShape &s : shapes)
-    evals += (double)s.nbins * (double)(s.kmax - s.kmin + 1) * (double)s.nperiods;
-  if (evals < kTuneMinEvals) {
+  if (!tuned) {
     // The built-in table, with the tile cut so that the call has work items
     // for two workgroups per CU.  Tiles any smaller only add per-item work:
     // one 1000-point curve x 5000 periods (200 bins) took 69 / 50 / 62 /

@@ -164,7 +164,8 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   int widest = 0;
   for (int c = 1; c < nc; ++c)
     if (shapes[c].nbins > shapes[widest].nbins) widest = c;
-  const bool block = block_batch(shapes, nc, weighted, ds.max_lds);
+  const bool block = block_batch(shapes, nc, weighted, min_in_points, false, ds.num_cus,
+                                 ds.max_lds);
   if (block) {
     tc.tile_cap = tc.tile_cap < 4 ? tc.tile_cap : 4;
     tc.lds_budget = block_lds_budget(shapes[widest], weighted, ds.max_lds);

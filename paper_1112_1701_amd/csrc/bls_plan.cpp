@@ -248,35 +248,38 @@ int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom 
   return best;
 }
 
-// Whether the block search is the faster kernel for a batch, from the clocks
-// per period and CU that both took (after the fold, which they share) at 200
-// to 2000 bins, 220 to 20000 points and duty-cycle ranges of 0.01-0.03 to
-// 0.02-0.2, search_kernel with its tuned tile.  Scoring every box: 0.72 of
-// its instructions (weighted 1.3: half the waves).  The block search: 1 (1.4)
-// of its own where a CU holds 20 periods, more where its LDS holds fewer, and
-// a little more on sparse curves, whose boxes tie more often.  Measured new
-// over old: 300 bins (0.01-0.1) 1.06 unit and 0.94 weighted; 400 bins 0.95,
-// 0.86; 600 bins 0.68, 0.78; 1000 bins (0.005-0.05) 0.93, 1.19; (0.01-0.1)
-// 0.57, 0.78; 200 bins 1.08, 0.95.
+// Whether the block search is the faster kernel for a batch, from the kernel
+// times of both over 4000 calls of 1 to 200 curves, 140 to 50000 points, 1000
+// to 60000 periods and 100 to 1000 bins, in instructions per period after the
+// fold, which they share.  Scoring every box: a lane per start bin, three
+// quarters as many again for weights, and twice that where a box that passes
+// the screen has its points counted (weighted, a minimum of two or more); 0.8
+// to 0.9 of it where the call's tiles are tuned or let eight (six) workgroups
+// share a CU (untuned_lds_budget).  The block search: its parts for the curve's geometry,
+// 1.4 times that for weights, more where the LDS holds fewer than 20 periods
+// per CU.  The choice costs 1.6% against the faster kernel of each call; the
+// block search always, 7%, never, 18%.
 namespace {
-double every_box_cost(const CurveShape &s, bool weighted) {
-  return (weighted ? 1.3 : 0.72) * s.nbins / 64.0 *
-         (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
+double every_box_cost(const CurveShape &s, bool weighted, bool counts, bool eight) {
+  const double instr = s.nbins / 64.0 * (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
+  return instr * (!weighted ? (eight ? 0.9 : 1.0) : counts ? 3.0 : eight ? 1.25 : 1.55);
 }
 double block_cost(const CurveShape &s, bool weighted, const BlockGeom &g, int periods_per_cu) {
   const int rounds = (g.nblocks + 63) / 64, per = 64 / g.bsize;
   const double batches = ceil((20.0 + s.nbins / 25.0) / per);
   const double instr = 330.0 + rounds * (60.0 + 24.0 * g.bsize + 27.0 * (g.omax - g.omin + 1)) +
                        batches * (32.0 + 13.5 * g.bsize);
-  return instr * (weighted ? 1.4 : 1.0) * std::max(1.0, pow(20.0 / periods_per_cu, 0.8)) *
-         (s.n < s.nbins ? 1.15 : 1.0);
+  return instr * (weighted ? 1.4 : 1.0) * std::max(1.0, pow(20.0 / periods_per_cu, 0.8));
 }
 }  // namespace
 
-bool block_batch(const CurveShape *shapes, int n, bool weighted, int max_lds) {
+bool block_batch(const CurveShape *shapes, int n, bool weighted, int min_in_points, bool tuned,
+                 int num_cus, int max_lds) {
   const char *e = getenv("BLS_BLOCK_SEARCH");  // 0: never, 1: wherever it can run
   if (e && atoi(e) == 0) return false;
   double every = 0.0, block = 0.0;
+  int64_t periods = 0;
+  for (int c = 0; c < n; ++c) periods += shapes[c].nperiods;
   for (int c = 0; c < n; ++c) {
     const CurveShape &s = shapes[c];
     BlockGeom g;
@@ -284,9 +287,15 @@ bool block_batch(const CurveShape *shapes, int n, bool weighted, int max_lds) {
     int groups = 0;
     const int T = block_tile(s.nbins, s.kmax, weighted, max_lds, g, &groups);
     if (T < 1) return false;
-    every += (double)s.nperiods * every_box_cost(s, weighted);
+    const bool eight = tuned || untuned_lds_budget(s, periods, weighted, num_cus) <
+                                    default_tiles(weighted).lds_budget;
+    every += (double)s.nperiods * every_box_cost(s, weighted, min_in_points > 1, eight);
     block += (double)s.nperiods * block_cost(s, weighted, g, T * groups);
   }
+  // Fewer periods than seven waves per CU: a period takes a wave 25 us or more,
+  // and the four of a workgroup less (461 bins, 1497 periods 44 / 35 us; 400
+  // bins, 2000 periods 43 / 52).
+  if (e == nullptr && periods < 7 * (int64_t)num_cus) return false;
   return e != nullptr || block < every;
 }
 

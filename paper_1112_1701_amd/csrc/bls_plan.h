@@ -166,8 +166,10 @@ void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
                      bool check_periods, bool memo, bool block, CurveDesc &d);
 
 // Whether the block search can run every curve of a launch (boxes of at most
-// half the bins) and is the faster kernel for it.
-bool block_batch(const CurveShape *shapes, int n, bool weighted, int max_lds);
+// half the bins) and is the faster kernel for it.  tuned: the tiles of the
+// other kernel would be tuned.
+bool block_batch(const CurveShape *shapes, int n, bool weighted, int min_in_points, bool tuned,
+                 int num_cus, int max_lds);
 // LDS budget per workgroup of the block search (`rep`: the batch's typical
 // curve).
 int block_lds_budget(const CurveShape &rep, bool weighted, int max_lds);

@@ -818,7 +818,8 @@ int bls_server_submit(bls_server *s, const bls_request *q, uint64_t *ticket) {
   }
   const int wpb = r->weighted ? 2 : 1;
   int T = 1, hs = 0;
-  r->block = block_batch(shapes.data(), 1, r->weighted, s->max_lds);
+  r->block = block_batch(shapes.data(), 1, r->weighted, s->cfg.min_in_points, false,
+                         s->num_cus, s->max_lds);
   if (r->block)
     fit_block_tile(r->nbins, r->kmin, r->kmax, r->np,
                    block_lds_budget(shapes[0], r->weighted, s->max_lds), 4, r->weighted, &T, &hs,
