@@ -150,6 +150,58 @@ __device__ inline double block_sum_fixed(double v, double *s_red) {
   return t;
 }
 
+// The clipped statistics of a bin of up to 64 members in each region, by one
+// wave.
+__device__ inline void clip_members(const VarArgs &a, int64_t task, int cnt,
+                                    const int (*list)[kVarRegionCap], const int *count, int lane) {
+  constexpr int kRegions = kBlock / 64;
+  int star[kRegions];
+  double v[kRegions];
+  bool alive[kRegions];
+#pragma unroll
+  for (int w = 0; w < kRegions; ++w) {
+    alive[w] = lane < count[w];
+    star[w] = alive[w] ? list[w][lane] : -1;
+    v[w] = alive[w] ? a.rms[star[w]] : 0.0;
+  }
+  double mu = 0.0, sd = 0.0;
+  for (int it = 0;; ++it) {
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < kRegions; ++w)
+      if (alive[w]) sum = sum + v[w];
+    mu = (0.0 + wave_sum(sum)) / (double)cnt;
+    double ss = 0.0;
+#pragma unroll
+    for (int w = 0; w < kRegions; ++w) {
+      const double dv = v[w] - mu;
+      if (alive[w]) ss = ss + dv * dv;
+    }
+    sd = sqrt((0.0 + wave_sum(ss)) / (double)cnt);
+    if (it >= a.max_iter) break;
+    const double lo = mu - a.clip_sigma * sd, hi = mu + a.clip_sigma * sd;
+    int dropped = 0;
+#pragma unroll
+    for (int w = 0; w < kRegions; ++w) {
+      const bool drop = alive[w] && !(v[w] >= lo && v[w] <= hi);
+      alive[w] = alive[w] && !drop;
+      dropped += (int)__popcll(__ballot(drop));
+    }
+    if (dropped == 0) break;
+    cnt -= dropped;
+  }
+  if (lane == 0) {
+    a.bin_mean[task] = mu;
+    a.bin_std[task] = sd;
+    a.bin_count[task] = cnt;
+  }
+  if (cnt < a.min_stars) return;
+  const double thr = mu + a.flag_sigma * sd;
+#pragma unroll
+  for (int w = 0; w < kRegions; ++w)
+    if (star[w] >= 0 && v[w] > thr) a.flag[star[w]] = 1;
+}
+
 // One workgroup per (chip, bin).  Each wave scans a quarter of the chip's
 // stars and keeps its members in its own LDS region, so the regions in wave
 // order list the members in star order; a wave with more members than its
@@ -171,26 +223,26 @@ __global__ __launch_bounds__(kBlock) void var_clip_kernel(VarArgs a) {
   const int quarter = (c1 - c0 + 3) / 4;
   const int w0 = min(c1, c0 + wv * quarter), w1 = min(c1, w0 + quarter);
 
-  // Members of this wave's quarter, in star order, all alive; eight chunks
-  // of bin numbers are loaded together per round.
+  // Members of this wave's quarter, in star order; sixteen chunks of bin
+  // numbers are loaded together per round.
   int cnt_w = 0;
   const unsigned long long below = (1ull << lane) - 1ull;
-  for (int base = w0; base < w1; base += 64 * 8) {
-    int bv[8];
+  constexpr int kChunks = 16;
+  for (int base = w0; base < w1; base += 64 * kChunks) {
+    int bv[kChunks];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kChunks; ++u) {
       const int st = base + 64 * u + lane;
       bv[u] = st < w1 ? a.bin[st] : -1;
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kChunks; ++u) {
       const int st = base + 64 * u + lane;
       const bool mem = bv[u] == b;
       const unsigned long long mask = __ballot(mem);
       if (mem) {
         const int pos = cnt_w + __popcll(mask & below);
         if (pos < kVarRegionCap) s_list[wv][pos] = st;
-        a.alive[st] = 1;
       }
       cnt_w += __popcll(mask);
     }
@@ -198,10 +250,11 @@ __global__ __launch_bounds__(kBlock) void var_clip_kernel(VarArgs a) {
   if (lane == 0) s_wcnt[wv] = cnt_w;
   __syncthreads();
   int cnt0 = 0;
-  bool fits = true;
+  bool fits = true, small = true;
   for (int w = 0; w < kBlock / 64; ++w) {
     cnt0 += s_wcnt[w];
     fits = fits && s_wcnt[w] <= kVarRegionCap;
+    small = small && s_wcnt[w] <= 64;
   }
   const double qnan = __longlong_as_double(0x7ff8000000000000ll);
   if (cnt0 == 0) {
@@ -212,6 +265,15 @@ __global__ __launch_bounds__(kBlock) void var_clip_kernel(VarArgs a) {
     }
     return;  // uniform: every thread saw cnt0 == 0
   }
+  // A bin of few members (up to 64 in each region) is one wave's work, a
+  // member of each region to a lane, without barriers: the sums below would
+  // add the other waves' zeros to the same values in the same order.  (11
+  // chips x 60 bins of 150 stars: 25 us the other way, latency of its 30
+  // barriers; 13 us so, half of it the scan of the chip's bin numbers.)
+  if (small) {
+    if (wv == 0) clip_members(a, task, cnt0, s_list, s_wcnt, lane);
+    return;
+  }
   // Visit the members in star order: the regions in wave order (value and
   // alive flag in LDS, gathered once), or a rescan of the chip when a region
   // overflowed.  f(value, alive flag, star).
@@ -221,8 +283,11 @@ __global__ __launch_bounds__(kBlock) void var_clip_kernel(VarArgs a) {
         s_val[w][i] = a.rms[s_list[w][i]];
         s_alive[w][i] = 1;
       }
-    __syncthreads();
+  } else {
+    for (int st = c0 + tid; st < c1; st += kBlock)
+      if (a.bin[st] == b) a.alive[st] = 1;
   }
+  __syncthreads();
   auto for_members = [&](auto f) {
     if (fits) {
       for (int w = 0; w < kBlock / 64; ++w)
