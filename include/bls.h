@@ -64,7 +64,7 @@ typedef enum {
 /* Plan flags. */
 enum {
     BLS_DIP_ONLY = 1u << 0,     /* only boxes below the mean (S < 0) count  */
-    BLS_NO_GRAPH = 1u << 1,     /* never capture/replay HIP graphs          */
+    BLS_NO_GRAPH = 1u << 1,     /* plan every bls_search_device call afresh */
     BLS_NO_AUTOTUNE = 1u << 2   /* use the built-in tile table              */
 };
 
@@ -182,7 +182,7 @@ typedef struct {
  * on the device.  Asynchronous on the plan's stream: the device arrays are
  * borrowed until bls_synchronize returns.  Curves whose data is invalid get
  * SR = NaN and are reported by bls_synchronize.  Repeated calls with the
- * same batch description replay captured HIP graphs.  Several calls may be
+ * same batch description reuse the plan of the last.  Several calls may be
  * queued on one plan without synchronizing in between, with the same or
  * different batches: a call that must rewrite the plan's staged batch
  * description first waits (on the host) until the copies of the queued
@@ -478,7 +478,7 @@ typedef struct {
     int32_t grid;           /* workgroups of the persistent launch          */
     int32_t block;          /* threads per workgroup                        */
     int32_t lds_bytes;      /* dynamic LDS per workgroup                    */
-    int32_t graph_replayed; /* 1 if the call replayed a captured graph      */
+    int32_t graph_replayed; /* 1 if the call reused the last call's plan    */
 } bls_call_stats;
 
 int bls_last_stats(const bls_plan *plan, bls_call_stats *out);
@@ -486,8 +486,7 @@ int bls_last_stats(const bls_plan *plan, bls_call_stats *out);
 /* Device durations of the search kernel (or unbinned kernel) launches of
  * the plan's search calls since the last bls_kernel_times_reset, measured by
  * HIP events recorded on the plan's stream right before and after each
- * launch (graph replays included: the kernel is its own graph).  Waits for
- * the plan's stream, then writes the most recent min(max, available)
+ * launch.  Waits for the plan's stream, then writes the most recent min(max, available)
  * durations in ms, oldest first, to ms[] and their number to *count; the
  * plan keeps the last 64.  Errors: INVALID_ARG, DEVICE. */
 int bls_kernel_times(bls_plan *plan, float *ms, int32_t max, int32_t *count);

@@ -106,14 +106,8 @@ double time_candidate(bls_plan *p, std::vector<CurveShape> &shapes, bool weighte
     d.out_scale = 1.0;
   }
   hipStream_t st = p->stream;
-  if (hipMemcpyAsync(p->d_curves, p->h_curves, sizeof(CurveDesc) * pb.ncurves,
-                     hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(p->d_seg_start, p->h_seg_start, sizeof(int64_t) * (pb.nseg + 1),
-                     hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(p->d_seg_curve, p->h_seg_curve, sizeof(int32_t) * pb.nseg,
-                     hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(p->d_seg_tile0, p->h_seg_tile0, sizeof(int32_t) * pb.nseg,
-                     hipMemcpyHostToDevice, st) != hipSuccess ||
+  if (hipMemcpyAsync(p->d_curves, p->h_curves, desc_bytes(pb.ncurves), hipMemcpyHostToDevice,
+                     st) != hipSuccess ||
       desc_mark(p) != BLS_OK)
     return -1.0;
   SearchArgs a;

@@ -90,6 +90,9 @@ struct PrepArgs {
   double *dt;
   int32_t *q;
   int32_t *qw;
+  // cleared if given: the call's partition counters, the curves' best keys
+  unsigned long long *counter = nullptr;
+  unsigned long long *keys = nullptr;
 };
 
 struct SearchArgs {

@@ -11,9 +11,10 @@
 //                   bins, scans every start bin x width with running window
 //                   sums, and keeps the best box per period with a 64-bit
 //                   LDS atomic max on (value, -index)
-//   fill_kernel / best_index_kernel  counter and per-curve key set-up and
-//                   read-out (plain kernels so that the sequence can be
-//                   captured in a HIP graph)
+//   fill_kernel / best_index_kernel  counter set-up (calls without a prep
+//                   kernel, which does it itself) and per-curve key read-out
+//                   (plain kernels so that the sequence can be captured in a
+//                   HIP graph)
 //
 // The unbinned search (bls_unbinned.hip), the detection statistics
 // (bls_detect.hip), the eclipse detection efficiency (bls_window.hip) and
@@ -39,21 +40,22 @@ namespace bls {
 namespace {
 
 // ------------------------------------------------------------------ prep
-__device__ inline void block_isum2(long long &a, long long &b, long long *sa, long long *sb) {
-  const int tid = threadIdx.x;
-  sa[tid] = a;
-  sb[tid] = b;
-  __syncthreads();
-  for (int s = kBlock / 2; s > 0; s >>= 1) {
-    if (tid < s) {
-      sa[tid] += sa[tid + s];
-      sb[tid] += sb[tid + s];
-    }
-    __syncthreads();
-  }
-  a = sa[0];
-  b = sb[0];
-  __syncthreads();
+// One value per thread (v: all of them, in LDS) reduced by one wave: a tree
+// of halves, in the same order as with a barrier for each of its steps.
+template <class F>
+__device__ inline double tree_of(const double *v, F f) {
+  const int lane = threadIdx.x & 63;
+  double r = f(f(v[lane], v[lane + 128]), f(v[lane + 64], v[lane + 192]));
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) r = f(r, __shfl_down(r, s, 64));
+  return r;  // lane 0's
+}
+
+// Sum over the wave (exact), and over the waves' sums (w).
+__device__ inline long long wave_sum_i64(long long v) {
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s, 64);
+  return v;
 }
 
 // Exponent e with |v| 2^e < 2^bits for every |v| <= m (0 if m == 0).
@@ -64,11 +66,15 @@ __device__ inline int scale_exponent(double m, int bits) {
   return bits - ex;
 }
 
+// What bounds it: the latency of one workgroup's loads, so four points (eight
+// periods) of a thread are loaded at a time and the reductions of a pass share
+// two barriers.  1000 points, 5000 periods: 14.5 us with a load and a barrier
+// per step, 8.7 so; a grid of 20000 periods 30 us, 12.6 so.
 __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
-  __shared__ double sa[kBlock];
-  __shared__ double sb[kBlock];
-  __shared__ long long ia[kBlock];
-  __shared__ long long ib[kBlock];
+  __shared__ double s_a[kBlock], s_b[kBlock], s_c[kBlock];
+  __shared__ double s_r[3];
+  __shared__ long long s_w[3][kBlock / 64];
+  __shared__ double s_m[2][kBlock / 64];
 
   const int c = blockIdx.x;
   if (c >= a.ncurves) return;
@@ -78,46 +84,96 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
   const int qbits = cd->qbits;
   const bool weighted = a.w != nullptr;
   const int tid = threadIdx.x;
+  const int wave = tid >> 6, lane = tid & 63;
+  constexpr int kU = 4;
+  // the call's counters and the curve's best key
+  if (a.keys && tid == 0) a.keys[c] = 0ull;
+  if (a.counter && c == 0 && tid < kMaxParts) a.counter[tid] = 0ull;
 
   // Pass 1: validity, kept count, t0, sum w, sum w x.
-  long long cnt = 0, bad = 0;
+  int cnt = 0, bad = 0;
   double tmin = INFINITY, sw = 0.0, swx = 0.0;
-  for (int64_t i = tid; i < n; i += kBlock) {
-    const double wi = weighted ? a.w[off + i] : 1.0;
-    if (!(wi >= 0.0) || isinf(wi)) {
-      bad = 1;
-      continue;
+  for (int64_t i0 = tid; i0 < n; i0 += kU * kBlock) {
+    double wv[kU], tv[kU], xv[kU];
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {
+      const int64_t i = min(i0 + k * kBlock, n - 1);
+      wv[k] = weighted ? a.w[off + i] : 1.0;
+      tv[k] = a.t[off + i];
+      xv[k] = a.x[off + i];
     }
-    if (wi == 0.0) continue;
-    const double ti = a.t[off + i];
-    const double xi = a.x[off + i];
-    if (!isfinite(ti) || !isfinite(xi)) {
-      bad = 1;
-      continue;
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {
+      if (i0 + k * kBlock >= n) break;
+      const double wi = wv[k], ti = tv[k], xi = xv[k];
+      if (!(wi >= 0.0) || isinf(wi)) {
+        bad = 1;
+        continue;
+      }
+      if (wi == 0.0) continue;
+      if (!isfinite(ti) || !isfinite(xi)) {
+        bad = 1;
+        continue;
+      }
+      ++cnt;
+      tmin = fmin(tmin, ti);
+      sw = sw + wi;
+      swx = swx + wi * xi;
     }
-    ++cnt;
-    tmin = fmin(tmin, ti);
-    sw = sw + wi;
-    swx = swx + wi * xi;
   }
   // Trial periods of this curve (device-side inputs are checked here).
-  long long badp = 0, unused0 = 0;
+  int badp = 0;
   if (cd->check_periods) {
+#pragma unroll 8
     for (int64_t i = tid; i < cd->nperiods; i += kBlock) {
       const double P = a.periods[cd->p_off + i];
       if (!isfinite(P) || !(P > 0.0)) badp = 1;
     }
   }
-  block_isum2(badp, unused0, ia, ib);
-  block_isum2(cnt, bad, ia, ib);
-  block_sum2(sw, swx, sa, sb);
-  double tmax_unused = -INFINITY;
-  block_minmax(tmin, tmax_unused, sa, sb);
+  // Cadence: the lower median of 64 gaps between consecutive input times,
+  // sampled evenly along the curve (the fold spaces its lanes by it; any
+  // value is correct, a good one only makes the fold faster).
+  float gap = 0.0f;
+  if (wave == 3 && n >= 2) {
+    const int64_t i = (int64_t)lane * (n - 1) / 64;
+    gap = fabsf((float)(a.t[off + i + 1] - a.t[off + i]));
+    if (!isfinite(gap)) gap = INFINITY;
+  }
+  s_a[tid] = sw;
+  s_b[tid] = swx;
+  s_c[tid] = tmin;
+  {
+    const long long f = wave_sum_i64((long long)cnt | ((long long)bad << 32));
+    const long long g = wave_sum_i64(badp);
+    if (lane == 0) {
+      s_w[0][wave] = f;
+      s_w[1][wave] = g;
+    }
+  }
+  __syncthreads();
+  if (wave < 3) {
+    const double r = wave == 0   ? tree_of(s_a, [](double p, double q) { return p + q; })
+                     : wave == 1 ? tree_of(s_b, [](double p, double q) { return p + q; })
+                                 : tree_of(s_c, [](double p, double q) { return fmin(p, q); });
+    if (lane == 0) s_r[wave] = r;
+  }
+  __syncthreads();
+  sw = s_r[0];
+  swx = s_r[1];
+  tmin = s_r[2];
+  long long kept = 0, any = 0;
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) {
+    kept += s_w[0][w];
+    any += s_w[1][w];
+  }
+  const bool bad_period = any != 0, bad_data = (kept >> 32) != 0;
+  kept &= 0xFFFFFFFFll;
 
-  if (badp != 0 || bad != 0 || cnt < 2 || !(sw > 0.0) || !isfinite(sw)) {
+  if (bad_period || bad_data || kept < 2 || !(sw > 0.0) || !isfinite(sw)) {
     if (tid == 0) {
-      cd->status = badp ? kCurveBadPeriod : bad ? kCurveBadData : kCurveTooFew;
-      cd->n_eff = (int32_t)cnt;
+      cd->status = bad_period ? kCurveBadPeriod : bad_data ? kCurveBadData : kCurveTooFew;
+      cd->n_eff = (int32_t)kept;
     }
     // zero the encoded points so that no kernel reads garbage
     for (int64_t i = tid; i < n; i += kBlock) {
@@ -127,81 +183,126 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
     }
     return;
   }
-  const double W = weighted ? sw : (double)cnt;
+  const double W = weighted ? sw : (double)kept;
   const double xbar = swx / sw;
 
-  // Cadence: the lower median of 64 gaps between consecutive input times,
-  // sampled evenly along the curve (the fold spaces its lanes by it; any
-  // value is correct, a good one only makes the fold faster).
-  if (tid < 64) {
-    const int64_t i = (int64_t)tid * (n - 1) / 64;
-    float g = fabsf((float)(a.t[off + i + 1] - a.t[off + i]));
-    if (!isfinite(g)) g = INFINITY;
+  if (wave == 3) {
     int rank = 0;
+#pragma unroll
     for (int k = 0; k < 64; ++k) {
-      const float o = __shfl(g, k, 64);
-      rank += (o < g) || (o == g && k < tid);
+      const float o = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(gap), k));
+      rank += (o < gap) || (o == gap && k < lane);
     }
-    if (rank == 31) cd->cadence = g;
+    if (rank == 31) cd->cadence = gap;
   }
 
   // Pass 2: largest |w (x - xbar)| and largest w, for the fixed-point scales.
   double my = 0.0, mw = 0.0;
-  for (int64_t i = tid; i < n; i += kBlock) {
-    const double wi = weighted ? a.w[off + i] : 1.0;
-    if (wi == 0.0) continue;
-    const double yi = a.x[off + i] - xbar;
-    const double v = weighted ? wi * yi : yi;
-    my = fmax(my, fabs(v));
-    mw = fmax(mw, wi);
+  for (int64_t i0 = tid; i0 < n; i0 += kU * kBlock) {
+    double wv[kU], xv[kU];
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {
+      const int64_t i = min(i0 + k * kBlock, n - 1);
+      wv[k] = weighted ? a.w[off + i] : 1.0;
+      xv[k] = a.x[off + i];
+    }
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {  // (the last point may count twice)
+      if (wv[k] == 0.0) continue;
+      const double yi = xv[k] - xbar;
+      const double v = weighted ? wv[k] * yi : yi;
+      my = fmax(my, fabs(v));
+      mw = fmax(mw, wv[k]);
+    }
   }
-  double dummy = 0.0;
-  block_minmax(dummy, my, sa, sb);
-  dummy = 0.0;
-  block_minmax(dummy, mw, sa, sb);
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+    my = fmax(my, __shfl_xor(my, s, 64));
+    mw = fmax(mw, __shfl_xor(mw, s, 64));
+  }
+  if (lane == 0) {
+    s_m[0][wave] = my;
+    s_m[1][wave] = mw;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kBlock / 64; ++w) {
+    my = fmax(my, s_m[0][w]);
+    mw = fmax(mw, s_m[1][w]);
+  }
   const int es = scale_exponent(my, qbits);
   const int ew = weighted ? scale_exponent(mw, qbits) : qbits;
 
   // Pass 3: encode; exact totals of the encoded weights and values.
   long long sqw = 0, sq = 0;
-  double qwmin = INFINITY, unused_max = 0.0;
-  for (int64_t i = tid; i < n; i += kBlock) {
-    const double wi = weighted ? a.w[off + i] : 1.0;
-    if (wi == 0.0) {
-      a.dt[off + i] = 0.0;
-      a.q[off + i] = 0;
-      if (weighted) a.qw[off + i] = -1;
-      continue;
+  int qwmin = INT32_MAX;
+  for (int64_t i0 = tid; i0 < n; i0 += kU * kBlock) {
+    double wv[kU], tv[kU], xv[kU];
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {
+      const int64_t i = min(i0 + k * kBlock, n - 1);
+      wv[k] = weighted ? a.w[off + i] : 1.0;
+      tv[k] = a.t[off + i];
+      xv[k] = a.x[off + i];
     }
-    const double yi = a.x[off + i] - xbar;
-    const double v = weighted ? wi * yi : yi;
-    a.dt[off + i] = a.t[off + i] - tmin;
-    const int qi = __double2int_rn(ldexp(v, es));
-    a.q[off + i] = qi;
-    sq += qi;
-    if (weighted) {
-      const int qwi = __double2int_rn(ldexp(wi, ew));
-      a.qw[off + i] = qwi;
-      sqw += qwi;
-      qwmin = fmin(qwmin, (double)qwi);
+#pragma unroll
+    for (int k = 0; k < kU; ++k) {
+      const int64_t i = i0 + k * kBlock;
+      if (i >= n) break;
+      const double wi = wv[k];
+      if (wi == 0.0) {
+        a.dt[off + i] = 0.0;
+        a.q[off + i] = 0;
+        if (weighted) a.qw[off + i] = -1;
+        continue;
+      }
+      const double yi = xv[k] - xbar;
+      const double v = weighted ? wi * yi : yi;
+      a.dt[off + i] = tv[k] - tmin;
+      const int qi = __double2int_rn(ldexp(v, es));
+      a.q[off + i] = qi;
+      sq += qi;
+      if (weighted) {
+        const int qwi = __double2int_rn(ldexp(wi, ew));
+        a.qw[off + i] = qwi;
+        sqw += qwi;
+        qwmin = min(qwmin, qwi);
+      }
     }
   }
-  block_isum2(sqw, sq, ia, ib);
-  if (weighted) block_minmax(qwmin, unused_max, sa, sb);
+  sq = wave_sum_i64(sq);
+  if (weighted) {
+    sqw = wave_sum_i64(sqw);
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) qwmin = min(qwmin, __shfl_xor(qwmin, s, 64));
+  }
+  // (every thread has read s_w before the barrier of pass 2)
+  if (lane == 0) {
+    s_w[0][wave] = sq;
+    s_w[1][wave] = sqw;
+    s_w[2][wave] = qwmin;
+  }
+  __syncthreads();
 
   if (tid == 0) {
+    sq = sqw = 0;
+    for (int w = 0; w < kBlock / 64; ++w) {
+      sq += s_w[0][w];
+      sqw += s_w[1][w];
+      qwmin = min(qwmin, (int)s_w[2][w]);
+    }
     cd->t0 = tmin;
     cd->W = W;
     cd->xbar = xbar;
     cd->es = es;
     cd->ew = ew;
     cd->out_scale = ldexp(1.0, ew - es);
-    cd->Wf = weighted ? (float)ldexp((double)sqw, -qbits) : (float)cnt;
+    cd->Wf = weighted ? (float)ldexp((double)sqw, -qbits) : (float)kept;
     // |sums| < 2^53, so both totals are exact in FP64
-    cd->Wtot = weighted ? ldexp((double)sqw, -qbits) : (double)cnt;
+    cd->Wtot = weighted ? ldexp((double)sqw, -qbits) : (double)kept;
     cd->Stot = ldexp((double)sq, -qbits);
-    cd->n_eff = (int32_t)cnt;
-    cd->qwmin = weighted ? (int32_t)qwmin : 0;
+    cd->n_eff = (int32_t)kept;
+    cd->qwmin = weighted ? qwmin : 0;
     cd->status = kCurveOk;
   }
 }

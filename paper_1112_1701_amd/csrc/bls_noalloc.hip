@@ -254,9 +254,6 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
       return set_error_noplan(BLS_ERR_DEVICE, "launch of the descriptor kernel failed");
   }
   unsigned long long *keys = reinterpret_cast<unsigned long long *>(o->best_index);
-  if ((e = (hipError_t)launch_fill(d_counter, keys, nc, stream)) != hipSuccess)
-    return set_error_noplan(BLS_ERR_DEVICE, "launch of the fill kernel failed");
-
   PrepArgs pa;
   pa.curves = d_curves;
   pa.periods = b->periods;
@@ -267,6 +264,8 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   pa.dt = d_dt;
   pa.q = d_q;
   pa.qw = d_qw;
+  pa.counter = d_counter;
+  pa.keys = keys;
   if ((e = (hipError_t)launch_prep(pa, stream)) != hipSuccess)
     return set_error_noplan(BLS_ERR_DEVICE, "launch of the prep kernel failed");
 

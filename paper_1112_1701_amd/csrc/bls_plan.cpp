@@ -1,5 +1,5 @@
 // Host runtime of the BLS library: plan creation, validation, planning of
-// (curve, period tile) work items, launch sequencing, HIP graph replay and
+// (curve, period tile) work items, launch sequencing, reuse of plans and
 // the C ABI of include/bls.h.
 //
 // The operation and its conventions are those stated in include/bls.h (Law
@@ -587,9 +587,10 @@ int item_group(const bls_plan *p, const std::vector<CurveShape> &shapes) {
 int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted,
                const TileChoice &tc, PlannedBatch &out) {
   const int nc = (int)shapes.size();
-  // queued copies (or graph replays) may still read the pinned descriptors
+  // queued copies may still read the pinned descriptors
   const int ws = desc_wait(p);
   if (ws != BLS_OK) return ws;
+  place_desc(p, nc);
   out = PlannedBatch{};
   out.ncurves = nc;
   out.weighted = weighted;
@@ -660,6 +661,24 @@ int desc_wait(bls_plan *p) {
   return BLS_OK;
 }
 
+// One block holds a call's descriptors: the curves', then their segments'
+// (first items, curves, first tiles), so that one copy uploads them.
+size_t desc_bytes(int nc) {
+  static_assert(sizeof(CurveDesc) % 8 == 0, "the segments' 64-bit items follow the curves");
+  return sizeof(CurveDesc) * nc + 8 * ((size_t)nc + 1) + 4 * (size_t)nc * 2;
+}
+
+void place_desc(bls_plan *p, int nc) {
+  for (int dev = 0; dev < 2; ++dev) {
+    unsigned char *b = reinterpret_cast<unsigned char *>(dev ? p->d_curves : p->h_curves);
+    int64_t *start = reinterpret_cast<int64_t *>(b + sizeof(CurveDesc) * nc);
+    int32_t *curve = reinterpret_cast<int32_t *>(start + nc + 1);
+    (dev ? p->d_seg_start : p->h_seg_start) = start;
+    (dev ? p->d_seg_curve : p->h_seg_curve) = curve;
+    (dev ? p->d_seg_tile0 : p->h_seg_tile0) = curve + nc;
+  }
+}
+
 int desc_mark(bls_plan *p) {
   hipError_t e = hipEventRecord(p->ev_desc, p->stream);
   if (e != hipSuccess) return hip_error(p, e, "event record");
@@ -682,26 +701,14 @@ int ring_end(bls_plan *p) {
 }
 
 int enqueue_pre(bls_plan *p, const PlannedBatch &pb, const double *t, const double *x,
-                const double *w, const double *periods, int64_t *best) {
+                const double *w, const double *periods, int64_t *best, bool upload) {
   hipStream_t st = p->stream;
   hipError_t e;
   const int nc = pb.ncurves;
-  e = hipMemcpyAsync(p->d_curves, p->h_curves, sizeof(CurveDesc) * nc, hipMemcpyHostToDevice,
-                     st);
-  if (e != hipSuccess) return hip_error(p, e, "upload curve descriptors");
-  e = hipMemcpyAsync(p->d_seg_start, p->h_seg_start, sizeof(int64_t) * (pb.nseg + 1),
-                     hipMemcpyHostToDevice, st);
-  if (e != hipSuccess) return hip_error(p, e, "upload segments");
-  e = hipMemcpyAsync(p->d_seg_curve, p->h_seg_curve, sizeof(int32_t) * pb.nseg,
-                     hipMemcpyHostToDevice, st);
-  if (e != hipSuccess) return hip_error(p, e, "upload segments");
-  e = hipMemcpyAsync(p->d_seg_tile0, p->h_seg_tile0, sizeof(int32_t) * pb.nseg,
-                     hipMemcpyHostToDevice, st);
-  if (e != hipSuccess) return hip_error(p, e, "upload segments");
-
-  unsigned long long *keys = reinterpret_cast<unsigned long long *>(best);
-  e = (hipError_t)launch_fill(p->d_counter, keys, nc, st);
-  if (e != hipSuccess) return hip_error(p, e, "launch fill");
+  if (upload) {
+    e = hipMemcpyAsync(p->d_curves, p->h_curves, desc_bytes(nc), hipMemcpyHostToDevice, st);
+    if (e != hipSuccess) return hip_error(p, e, "upload descriptors");
+  }
 
   PrepArgs pa;
   pa.curves = p->d_curves;
@@ -713,6 +720,8 @@ int enqueue_pre(bls_plan *p, const PlannedBatch &pb, const double *t, const doub
   pa.dt = p->d_dt;
   pa.q = p->d_q;
   pa.qw = p->d_qw;
+  pa.counter = p->d_counter;
+  pa.keys = reinterpret_cast<unsigned long long *>(best);
   e = (hipError_t)launch_prep(pa, st);
   if (e != hipSuccess) return hip_error(p, e, "launch prep");
   return BLS_OK;
@@ -767,9 +776,9 @@ int enqueue_post(bls_plan *p, const PlannedBatch &pb, int64_t *best) {
 
 int enqueue_search(bls_plan *p, const PlannedBatch &pb, const double *t, const double *x,
                    const double *w, const double *periods, float *sr, float *depth, int32_t *js,
-                   int32_t *ks, int64_t *best, bool unbinned) {
-  int st = enqueue_pre(p, pb, t, x, w, periods, best);
-  if (st == BLS_OK) st = desc_mark(p);
+                   int32_t *ks, int64_t *best, bool unbinned, bool upload) {
+  int st = enqueue_pre(p, pb, t, x, w, periods, best, upload);
+  if (st == BLS_OK && upload) st = desc_mark(p);
   if (st == BLS_OK) st = ring_begin(p);
   if (st == BLS_OK) st = enqueue_kernel(p, pb, periods, sr, depth, js, ks, best, unbinned);
   if (st == BLS_OK) st = ring_end(p);
@@ -1007,7 +1016,7 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
   PlannedBatch pb;
   st = plan_batch(p, shapes, weighted, tc, pb);
   if (st != BLS_OK) return st;
-  p->graph_valid = false;  // descriptors were rewritten
+  p->replay_valid = false;  // descriptors were rewritten
 
   const int64_t npts = b.n_off[b.ncurves];
   const int64_t nper = b.p_off ? b.p_off[b.ncurves] : b.nperiods_shared;
@@ -1142,52 +1151,6 @@ uint64_t batch_signature(const bls_plan *p, const bls_batch &b, const bls_device
   return h;
 }
 
-void drop_graph(bls_plan *p) {
-  for (int g = 0; g < 3; ++g) {
-    if (p->gexec[g]) (void)hipGraphExecDestroy(p->gexec[g]);
-    if (p->graph[g]) (void)hipGraphDestroy(p->graph[g]);
-    p->gexec[g] = nullptr;
-    p->graph[g] = nullptr;
-  }
-  p->graph_valid = false;
-}
-
-// Capture one part of the launch sequence into graph g and instantiate it.
-template <class F>
-int capture_part(bls_plan *p, int g, F &&enqueue) {
-  hipError_t e = hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal);
-  if (e != hipSuccess) return hip_error(p, e, "begin capture");
-  const int st = enqueue();
-  hipGraph_t graph = nullptr;
-  e = hipStreamEndCapture(p->stream, &graph);
-  if (st != BLS_OK) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return st;
-  }
-  if (e != hipSuccess) return hip_error(p, e, "end capture");
-  p->graph[g] = graph;
-  e = hipGraphInstantiate(&p->gexec[g], graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) return hip_error(p, e, "instantiate graph");
-  return BLS_OK;
-}
-
-// Replay the three captured parts, the search kernel between the timing
-// ring's events and the descriptor mark after the uploads.
-int launch_graphs(bls_plan *p) {
-  hipError_t e = hipGraphLaunch(p->gexec[0], p->stream);
-  if (e != hipSuccess) return hip_error(p, e, "graph launch");
-  int st = desc_mark(p);
-  if (st == BLS_OK) st = ring_begin(p);
-  if (st != BLS_OK) return st;
-  if ((e = hipGraphLaunch(p->gexec[1], p->stream)) != hipSuccess)
-    return hip_error(p, e, "graph launch");
-  st = ring_end(p);
-  if (st != BLS_OK) return st;
-  if ((e = hipGraphLaunch(p->gexec[2], p->stream)) != hipSuccess)
-    return hip_error(p, e, "graph launch");
-  return BLS_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -1257,10 +1220,7 @@ int bls_plan_create(bls_plan **out, const bls_plan_config *cfg_in) {
   struct {
     void **ptr;
     size_t bytes;
-  } req[] = {{(void **)&p->d_curves, sizeof(CurveDesc) * nc},
-             {(void **)&p->d_seg_start, sizeof(int64_t) * (nc + 1)},
-             {(void **)&p->d_seg_curve, sizeof(int32_t) * nc},
-             {(void **)&p->d_seg_tile0, sizeof(int32_t) * nc},
+  } req[] = {{(void **)&p->d_curves, desc_bytes((int)nc)},
              {(void **)&p->d_dt, 8 * npt},
              {(void **)&p->d_q, 4 * npt},
              {(void **)&p->d_qw, 4 * npt},
@@ -1268,11 +1228,7 @@ int bls_plan_create(bls_plan **out, const bls_plan_config *cfg_in) {
   for (auto &r : req)
     if ((e = device_alloc(r.ptr, r.bytes)) != hipSuccess)
       return fail(hip_error(p, e, "allocate plan buffers"));
-  if ((e = hipHostMalloc((void **)&p->h_curves, sizeof(CurveDesc) * nc, 0)) != hipSuccess ||
-      (e = hipHostMalloc((void **)&p->h_seg_start, sizeof(int64_t) * (nc + 1), 0)) !=
-          hipSuccess ||
-      (e = hipHostMalloc((void **)&p->h_seg_curve, sizeof(int32_t) * nc, 0)) != hipSuccess ||
-      (e = hipHostMalloc((void **)&p->h_seg_tile0, sizeof(int32_t) * nc, 0)) != hipSuccess)
+  if ((e = hipHostMalloc((void **)&p->h_curves, desc_bytes((int)nc), 0)) != hipSuccess)
     return fail(hip_error(p, e, "allocate pinned descriptors"));
   *out = p;
   return BLS_OK;
@@ -1281,20 +1237,17 @@ int bls_plan_create(bls_plan **out, const bls_plan_config *cfg_in) {
 int bls_plan_destroy(bls_plan *p) {
   if (!p) return BLS_OK;
   if (p->stream) (void)hipStreamSynchronize(p->stream);
-  drop_graph(p);
   for (void *d : {(void *)p->d_detect_desc, (void *)p->d_detect_out,
                   (void *)p->d_window_desc, (void *)p->d_window_flag,
                   (void *)p->d_var_noff, (void *)p->d_var_alive, (void *)p->d_var_chip,
                   (void *)p->d_uws})
     free_dev(d);
-  for (void *d : {(void *)p->d_curves, (void *)p->d_seg_start, (void *)p->d_seg_curve,
-                  (void *)p->d_seg_tile0, (void *)p->d_dt, (void *)p->d_q, (void *)p->d_qw,
+  for (void *d : {(void *)p->d_curves, (void *)p->d_dt, (void *)p->d_q, (void *)p->d_qw,
                   (void *)p->d_counter, (void *)p->d_t, (void *)p->d_x, (void *)p->d_w,
                   (void *)p->d_periods, (void *)p->d_sr, (void *)p->d_depth, (void *)p->d_j,
                   (void *)p->d_k, (void *)p->d_best})
     free_dev(d);
-  for (void *h : {(void *)p->h_curves, (void *)p->h_seg_start, (void *)p->h_seg_curve,
-                  (void *)p->h_seg_tile0, (void *)p->h_stage})
+  for (void *h : {(void *)p->h_curves, (void *)p->h_stage})
     if (h) (void)hipHostFree(h);
   for (hipEvent_t ev : {p->ev_begin, p->ev_search0, p->ev_search1, p->ev_end, p->ev_desc})
     if (ev) (void)hipEventDestroy(ev);
@@ -1351,11 +1304,13 @@ int bls_search_device(bls_plan *p, const bls_batch *b, const bls_device_results 
   p->last_error.clear();
   hipError_t e = hipSetDevice(p->device);
   if (e != hipSuccess) return hip_error(p, e, "set device");
-  const bool use_graph = (p->cfg.flags & BLS_NO_GRAPH) == 0;
+  // A call like the last one finds its plan made and its descriptors uploaded.
+  const bool reuse = (p->cfg.flags & BLS_NO_GRAPH) == 0;
   const uint64_t sig = batch_signature(p, *b, *o);
-  if (use_graph && p->graph_valid && sig == p->graph_sig) {
+  if (reuse && p->replay_valid && sig == p->replay_sig) {
     if ((e = hipEventRecord(p->ev_begin, p->stream)) != hipSuccess) return hip_error(p, e, "event");
-    int st = launch_graphs(p);
+    const int st = enqueue_search(p, p->last, b->times, b->flux, b->weights, b->periods, o->sr,
+                                  o->depth, o->jstart, o->kwidth, o->best_index, false, false);
     if (st != BLS_OK) return st;
     if ((e = hipEventRecord(p->ev_end, p->stream)) != hipSuccess) return hip_error(p, e, "event");
     fill_stats(p, p->last, true);
@@ -1364,12 +1319,7 @@ int bls_search_device(bls_plan *p, const bls_batch *b, const bls_device_results 
   std::string err;
   int st = validate_batch(p->cfg, *b, false, p->shapes, err);
   if (st != BLS_OK) return set_error(p, st, err);
-  if (p->gexec[0]) {
-    // replays of the old graphs may still be queued: let them finish before
-    // their executables go
-    if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) return hip_error(p, e, "synchronize");
-    drop_graph(p);
-  }
+  p->replay_valid = false;
   const bool weighted = b->weights != nullptr;
   TileChoice tc = choose_tiles(p, p->shapes, weighted);
   PlannedBatch pb;
@@ -1377,28 +1327,11 @@ int bls_search_device(bls_plan *p, const bls_batch *b, const bls_device_results 
   if (st != BLS_OK) return st;
   p->last = pb;
   if ((e = hipEventRecord(p->ev_begin, p->stream)) != hipSuccess) return hip_error(p, e, "event");
-  if (use_graph) {
-    st = capture_part(p, 0, [&] {
-      return enqueue_pre(p, pb, b->times, b->flux, b->weights, b->periods, o->best_index);
-    });
-    if (st == BLS_OK)
-      st = capture_part(p, 1, [&] {
-        return enqueue_kernel(p, pb, b->periods, o->sr, o->depth, o->jstart, o->kwidth,
-                              o->best_index, false);
-      });
-    if (st == BLS_OK) st = capture_part(p, 2, [&] { return enqueue_post(p, pb, o->best_index); });
-    if (st == BLS_OK) st = launch_graphs(p);
-    if (st != BLS_OK) {
-      drop_graph(p);
-      return st;
-    }
-    p->graph_sig = sig;
-    p->graph_valid = true;
-  } else {
-    st = enqueue_search(p, pb, b->times, b->flux, b->weights, b->periods, o->sr, o->depth,
-                        o->jstart, o->kwidth, o->best_index);
-    if (st != BLS_OK) return st;
-  }
+  st = enqueue_search(p, pb, b->times, b->flux, b->weights, b->periods, o->sr, o->depth,
+                      o->jstart, o->kwidth, o->best_index);
+  if (st != BLS_OK) return st;
+  p->replay_sig = sig;
+  p->replay_valid = reuse;
   if ((e = hipEventRecord(p->ev_end, p->stream)) != hipSuccess) return hip_error(p, e, "event");
   fill_stats(p, pb, false);
   return BLS_OK;
@@ -1421,11 +1354,12 @@ int bls_search_unbinned_device(bls_plan *p, const bls_batch *b, const bls_unbinn
   pb.weighted = weighted;
   std::vector<double> cost(nc);
   int ucap = 1;
-  // the pinned descriptors are rewritten: a captured search graph goes
-  // stale, and queued copies may still read them
-  p->graph_valid = false;
+  // the pinned descriptors are rewritten: the last search's plan goes stale,
+  // and queued copies may still read them
+  p->replay_valid = false;
   st = desc_wait(p);
   if (st != BLS_OK) return st;
+  place_desc(p, nc);
   for (int c = 0; c < nc; ++c) {
     const CurveShape &s = p->shapes[c];
     CurveDesc &d = p->h_curves[c];
@@ -1788,7 +1722,7 @@ int bls_debug_phase_bins(bls_plan *p, const double *times, int64_t n, double per
   if (e != hipSuccess) return hip_error(p, e, "set device");
   int st = ensure_staging(p);
   if (st != BLS_OK) return st;
-  p->graph_valid = false;
+  p->replay_valid = false;
   st = desc_wait(p);
   if (st != BLS_OK) return st;
   CurveDesc &d = p->h_curves[0];

@@ -102,26 +102,24 @@ struct bls_plan {
   int64_t *d_var_chip = nullptr;      // [var_chip_cap + 1]
   int64_t var_chip_cap = 0;
 
-  // pinned host descriptors
+  // pinned host descriptors, one block (place_desc)
   bls::CurveDesc *h_curves = nullptr;
   int64_t *h_seg_start = nullptr;
   int32_t *h_seg_curve = nullptr;
   int32_t *h_seg_tile0 = nullptr;
 
-  // graph cache for bls_search_device: the launch sequence is captured as
-  // three graphs (uploads, fill and prep; the search kernel; the best-index
-  // read-out) so that the search kernel's own duration can be bracketed by
-  // events on every replay
-  hipGraph_t graph[3] = {nullptr, nullptr, nullptr};
-  hipGraphExec_t gexec[3] = {nullptr, nullptr, nullptr};
-  uint64_t graph_sig = 0;
-  bool graph_valid = false;
+  // bls_search_device: while nothing has rewritten the descriptors, a call
+  // like the last one launches its plan (last) again, without validation,
+  // planning and upload.  (As three captured graphs with the timing events
+  // between them the same sequence took 121 us instead of 105 for 1000 points
+  // and 5000 periods: graphs of one kernel launch slower than the kernel.)
+  uint64_t replay_sig = 0;
+  bool replay_valid = false;
 
   hipEvent_t ev_begin = nullptr, ev_search0 = nullptr, ev_search1 = nullptr,
              ev_end = nullptr;
 
-  // The pinned descriptors above are read by queued copies (or graph
-  // replays) until ev_desc, recorded after them, completes; a call that
+  // The pinned descriptors above are read by queued copies until ev_desc, recorded after them, completes; a call that
   // rewrites them first waits for it.
   hipEvent_t ev_desc = nullptr;
   bool desc_pending = false;
@@ -210,10 +208,9 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
 // The launch sequence of a search, in three parts: (1) upload descriptors,
 // clear counters and keys, prep; (2) the search kernel (with unbinned, the
 // unbinned kernel: js and ks then receive the first and last point of each
-// best box); (3) per-curve best index.  Nothing here records events, so each
-// part can be captured into a graph.
+// best box); (3) per-curve best index.  upload: the descriptors are new.
 int enqueue_pre(bls_plan *p, const PlannedBatch &pb, const double *t, const double *x,
-                const double *w, const double *periods, int64_t *best);
+                const double *w, const double *periods, int64_t *best, bool upload);
 int enqueue_kernel(bls_plan *p, const PlannedBatch &pb, const double *periods, float *sr,
                    float *depth, int32_t *js, int32_t *ks, int64_t *best, bool unbinned);
 int enqueue_post(bls_plan *p, const PlannedBatch &pb, int64_t *best);
@@ -221,8 +218,13 @@ int enqueue_post(bls_plan *p, const PlannedBatch &pb, int64_t *best);
 // timing ring's events (streams that are not capturing).
 int enqueue_search(bls_plan *p, const PlannedBatch &pb, const double *t, const double *x,
                    const double *w, const double *periods, float *sr, float *depth,
-                   int32_t *js, int32_t *ks, int64_t *best, bool unbinned = false);
-// Wait until no queued copy or graph still reads the pinned descriptors.
+                   int32_t *js, int32_t *ks, int64_t *best, bool unbinned = false,
+                   bool upload = true);
+// Bytes of the descriptors of nc curves, and their places in the pinned and
+// the device block.
+size_t desc_bytes(int nc);
+void place_desc(bls_plan *p, int nc);
+// Wait until no queued copy still reads the pinned descriptors.
 int desc_wait(bls_plan *p);
 // Mark the pinned descriptors as read by work queued so far on the stream.
 int desc_mark(bls_plan *p);

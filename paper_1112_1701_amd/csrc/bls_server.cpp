@@ -235,7 +235,6 @@ hipError_t start_request(bls_server *s, Req *r) {
                           st)) ||
       (e = hipMemcpyAsync(s->d_curves + r->slot, &d, sizeof d, hipMemcpyHostToDevice, st)))
     return e;
-  if ((e = (hipError_t)launch_fill(nullptr, s->d_keys + r->slot, 1, st))) return e;
   PrepArgs pa;
   pa.curves = s->d_curves + r->slot;
   pa.periods = s->d_per;
@@ -246,6 +245,7 @@ hipError_t start_request(bls_server *s, Req *r) {
   pa.dt = s->d_dt;
   pa.q = s->d_q;
   pa.qw = s->d_qw;
+  pa.keys = s->d_keys + r->slot;
   return (hipError_t)launch_prep(pa, st);
 }
 
