@@ -93,6 +93,7 @@ struct PrepArgs {
   // cleared if given: the call's partition counters, the curves' best keys
   unsigned long long *counter = nullptr;
   unsigned long long *keys = nullptr;
+  int32_t *status = nullptr;  // if given: the curves' status by itself
 };
 
 struct SearchArgs {

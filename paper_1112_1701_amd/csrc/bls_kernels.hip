@@ -172,7 +172,9 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
 
   if (bad_period || bad_data || kept < 2 || !(sw > 0.0) || !isfinite(sw)) {
     if (tid == 0) {
-      cd->status = bad_period ? kCurveBadPeriod : bad_data ? kCurveBadData : kCurveTooFew;
+      const int status = bad_period ? kCurveBadPeriod : bad_data ? kCurveBadData : kCurveTooFew;
+      cd->status = status;
+      if (a.status) a.status[c] = status;
       cd->n_eff = (int32_t)kept;
     }
     // zero the encoded points so that no kernel reads garbage
@@ -304,6 +306,7 @@ __global__ __launch_bounds__(kBlock) void prep_kernel(PrepArgs a) {
     cd->n_eff = (int32_t)kept;
     cd->qwmin = weighted ? qwmin : 0;
     cd->status = kCurveOk;
+    if (a.status) a.status[c] = kCurveOk;
   }
 }
 

@@ -722,6 +722,7 @@ int enqueue_pre(bls_plan *p, const PlannedBatch &pb, const double *t, const doub
   pa.qw = p->d_qw;
   pa.counter = p->d_counter;
   pa.keys = reinterpret_cast<unsigned long long *>(best);
+  pa.status = p->d_status;
   e = (hipError_t)launch_prep(pa, st);
   if (e != hipSuccess) return hip_error(p, e, "launch prep");
   return BLS_OK;
@@ -833,44 +834,57 @@ void fill_stats(bls_plan *p, const PlannedBatch &pb, bool replayed) {
   p->stats.graph_replayed = replayed ? 1 : 0;
 }
 
+// Elements of a result array in a block of them: whole lines.
+static size_t result_stride(int64_t n) { return ((size_t)n + 31) & ~(size_t)31; }
+
 int ensure_staging(bls_plan *p) {
   if (p->staging) return BLS_OK;
   const size_t np = (size_t)p->cfg.max_points, nr = (size_t)p->cfg.max_periods,
                nc = (size_t)p->cfg.max_curves;
-  struct {
-    void **ptr;
-    size_t bytes;
-  } req[] = {{(void **)&p->d_t, np * 8},      {(void **)&p->d_x, np * 8},
-             {(void **)&p->d_w, np * 8},      {(void **)&p->d_periods, nr * 8},
-             {(void **)&p->d_sr, nr * 4},     {(void **)&p->d_depth, nr * 4},
-             {(void **)&p->d_j, nr * 4},      {(void **)&p->d_k, nr * 4},
-             {(void **)&p->d_best, nc * 8}};
-  for (auto &r : req) {
-    hipError_t e = device_alloc(r.ptr, r.bytes);
+  // Inputs in one block and results in another, for one copy each way; a
+  // call lays them out compactly from the block's start (host_search), the
+  // other users have them at the plan's capacities.
+  const size_t nrp = result_stride((int64_t)nr);
+  hipError_t e = device_alloc((void **)&p->d_t, 3 * np * 8 + nr * 8);
+  if (e == hipSuccess) {
+    e = device_alloc((void **)&p->d_sr, nrp * 16 + nc * 8);
     if (e != hipSuccess) {
-      for (auto &q : req) {
-        free_dev(*q.ptr);
-        *q.ptr = nullptr;
-      }
-      return hip_error(p, e, "allocate host-path staging");
+      free_dev(p->d_t);
+      p->d_t = nullptr;
+      p->d_sr = nullptr;
     }
   }
+  if (e != hipSuccess) return hip_error(p, e, "allocate host-path staging");
+  p->d_x = p->d_t + np;
+  p->d_w = p->d_x + np;
+  p->d_periods = p->d_w + np;
+  p->d_depth = p->d_sr + nrp;
+  p->d_j = reinterpret_cast<int32_t *>(p->d_depth + nrp);
+  p->d_k = p->d_j + nrp;
+  p->d_best = reinterpret_cast<int64_t *>(p->d_k + nrp);
   p->staging = true;
   return BLS_OK;
 }
 
+// Waits for the stream; the curves' status is then in p->h_status.
+int read_device_status(bls_plan *p, int ncurves) {
+  hipError_t e;
+  if ((e = hipMemcpyAsync(p->h_status, p->d_status, sizeof(int32_t) * ncurves,
+                          hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
+      (e = hipStreamSynchronize(p->stream)) != hipSuccess)
+    return hip_error(p, e, "synchronize");
+  return BLS_OK;
+}
+
 int check_device_status(bls_plan *p, int ncurves) {
-  std::vector<CurveDesc> cds(ncurves);
-  hipError_t e = hipMemcpy(cds.data(), p->d_curves, sizeof(CurveDesc) * ncurves,
-                           hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return hip_error(p, e, "read curve status");
+  const int32_t *status = p->h_status;
   for (int c = 0; c < ncurves; ++c) {
-    if (cds[c].status != kCurveOk) {
+    if (status[c] != kCurveOk) {
       char msg[160];
       snprintf(msg, sizeof msg, "curve %d: %s", c,
-               cds[c].status == kCurveBadData
+               status[c] == kCurveBadData
                    ? "non-finite time/flux of a kept point, or a negative/non-finite weight"
-               : cds[c].status == kCurveBadPeriod
+               : status[c] == kCurveBadPeriod
                    ? "a trial period is not finite and > 0"
                    : "fewer than two points with positive weight");
       return set_error(p, BLS_ERR_INVALID_ARG, msg);
@@ -883,11 +897,9 @@ int check_device_status(bls_plan *p, int ncurves) {
 // Per-curve validity flags of the last prep (1 where the curve's data or
 // trial periods were invalid), read back from the device descriptors.
 int device_status_flags(bls_plan *p, int ncurves, int32_t *bad) {
-  std::vector<CurveDesc> cds(ncurves);
-  hipError_t e = hipMemcpy(cds.data(), p->d_curves, sizeof(CurveDesc) * ncurves,
-                           hipMemcpyDeviceToHost);
-  if (e != hipSuccess) return hip_error(p, e, "read curve status");
-  for (int c = 0; c < ncurves; ++c) bad[c] = cds[c].status != kCurveOk ? 1 : 0;
+  const int st = read_device_status(p, ncurves);
+  if (st != BLS_OK) return st;
+  for (int c = 0; c < ncurves; ++c) bad[c] = p->h_status[c] != kCurveOk ? 1 : 0;
   return BLS_OK;
 }
 
@@ -997,7 +1009,7 @@ bool ensure_host_stage(bls_plan *p) {
   if (hook && strcmp(hook, "pinned") == 0) return false;
   const size_t np = (size_t)p->cfg.max_points, nr = (size_t)p->cfg.max_periods,
                nc = (size_t)p->cfg.max_curves;
-  const size_t in = 3 * np * 8 + nr * 8 + 256, res = 4 * nr * 4 + nc * 8 + 256;
+  const size_t in = 3 * np * 8 + nr * 8 + 256, res = 16 * result_stride((int64_t)nr) + nc * 8;
   const size_t bytes = std::max(in, res);
   if (hipHostMalloc((void **)&p->h_stage, bytes, 0) != hipSuccess) {
     p->h_stage = nullptr;
@@ -1040,24 +1052,33 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
     src_p = sp;
   }
   if ((e = hipEventRecord(p->ev_begin, s)) != hipSuccess) return hip_error(p, e, "event");
-  if ((e = hipMemcpyAsync(p->d_t, src_t, npts * 8, hipMemcpyHostToDevice, s)) != hipSuccess)
-    return hip_error(p, e, "upload times");
-  if ((e = hipMemcpyAsync(p->d_x, src_x, npts * 8, hipMemcpyHostToDevice, s)) != hipSuccess)
-    return hip_error(p, e, "upload flux");
-  if (weighted &&
-      (e = hipMemcpyAsync(p->d_w, src_w, npts * 8, hipMemcpyHostToDevice, s)) != hipSuccess)
-    return hip_error(p, e, "upload weights");
-  if ((e = hipMemcpyAsync(p->d_periods, src_p, nper * 8, hipMemcpyHostToDevice, s)) !=
-      hipSuccess)
-    return hip_error(p, e, "upload periods");
-  st = enqueue_search(p, pb, p->d_t, p->d_x, weighted ? p->d_w : nullptr, p->d_periods, p->d_sr,
-                      p->d_depth, p->d_j, p->d_k, p->d_best);
+  // on the device as in the staging: arrays one after the other
+  double *d_t = p->d_t, *d_x = d_t + npts, *d_w = d_x + npts,
+         *d_per = weighted ? d_w + npts : d_w;
+  if (pinned) {
+    if ((e = hipMemcpyAsync(d_t, src_t, (npts * (weighted ? 3 : 2) + nper) * 8,
+                            hipMemcpyHostToDevice, s)) != hipSuccess)
+      return hip_error(p, e, "upload inputs");
+  } else if ((e = hipMemcpyAsync(d_t, src_t, npts * 8, hipMemcpyHostToDevice, s)) != hipSuccess ||
+             (e = hipMemcpyAsync(d_x, src_x, npts * 8, hipMemcpyHostToDevice, s)) != hipSuccess ||
+             (weighted && (e = hipMemcpyAsync(d_w, src_w, npts * 8, hipMemcpyHostToDevice, s)) !=
+                              hipSuccess) ||
+             (e = hipMemcpyAsync(d_per, src_p, nper * 8, hipMemcpyHostToDevice, s)) !=
+                 hipSuccess) {
+    return hip_error(p, e, "upload inputs");
+  }
+  const int64_t nres = pb.total_results;
+  const size_t nrp = result_stride(nres);
+  float *d_sr = p->d_sr, *d_depth = d_sr + nrp;
+  int32_t *d_j = reinterpret_cast<int32_t *>(d_depth + nrp), *d_k = d_j + nrp;
+  int64_t *d_best = reinterpret_cast<int64_t *>(d_k + nrp);
+  st = enqueue_search(p, pb, d_t, d_x, weighted ? d_w : nullptr, d_per, d_sr, d_depth, d_j, d_k,
+                      d_best);
   if (st != BLS_OK) return st;
   if ((e = hipEventRecord(p->ev_end, s)) != hipSuccess) return hip_error(p, e, "event");
 
   // Results into the pinned staging (the uploads from it have run by then:
   // same stream), else into pageable vectors.
-  const int64_t nres = pb.total_results;
   std::vector<float> v_sr, v_depth;
   std::vector<int32_t> v_js, v_ks;
   std::vector<int64_t> v_best;
@@ -1065,11 +1086,11 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
   int32_t *js, *ks;
   int64_t *best;
   if (pinned) {
-    best = reinterpret_cast<int64_t *>(p->h_stage);
-    sr = reinterpret_cast<float *>(best + b.ncurves);
-    depth = sr + nres;
-    js = reinterpret_cast<int32_t *>(depth + nres);
-    ks = js + nres;
+    sr = reinterpret_cast<float *>(p->h_stage);
+    depth = sr + nrp;
+    js = reinterpret_cast<int32_t *>(depth + nrp);
+    ks = js + nrp;
+    best = reinterpret_cast<int64_t *>(ks + nrp);
   } else {
     v_sr.resize(nres);
     v_depth.resize(nres);
@@ -1082,15 +1103,21 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
     ks = v_ks.data();
     best = v_best.data();
   }
-  if ((e = hipMemcpyAsync(sr, p->d_sr, nres * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(depth, p->d_depth, nres * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(js, p->d_j, nres * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(ks, p->d_k, nres * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
-      (e = hipMemcpyAsync(best, p->d_best, b.ncurves * 8, hipMemcpyDeviceToHost, s)) !=
-          hipSuccess)
+  if (pinned) {
+    if ((e = hipMemcpyAsync(sr, d_sr, nrp * 16 + (size_t)b.ncurves * 8, hipMemcpyDeviceToHost,
+                            s)) != hipSuccess)
+      return hip_error(p, e, "download results");
+  } else if ((e = hipMemcpyAsync(sr, d_sr, nres * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+             (e = hipMemcpyAsync(depth, d_depth, nres * 4, hipMemcpyDeviceToHost, s)) !=
+                 hipSuccess ||
+             (e = hipMemcpyAsync(js, d_j, nres * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+             (e = hipMemcpyAsync(ks, d_k, nres * 4, hipMemcpyDeviceToHost, s)) != hipSuccess ||
+             (e = hipMemcpyAsync(best, d_best, b.ncurves * 8, hipMemcpyDeviceToHost, s)) !=
+                 hipSuccess) {
     return hip_error(p, e, "download results");
-  if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_error(p, e, "search");
-  st = check_device_status(p, b.ncurves);
+  }
+  st = read_device_status(p, b.ncurves);
+  if (st == BLS_OK) st = check_device_status(p, b.ncurves);
   if (st != BLS_OK) return st;
 
   float ms = 0.f;
@@ -1224,11 +1251,16 @@ int bls_plan_create(bls_plan **out, const bls_plan_config *cfg_in) {
              {(void **)&p->d_dt, 8 * npt},
              {(void **)&p->d_q, 4 * npt},
              {(void **)&p->d_qw, 4 * npt},
+             {(void **)&p->d_status, 4 * nc},
              {(void **)&p->d_counter, 64}};
   for (auto &r : req)
     if ((e = device_alloc(r.ptr, r.bytes)) != hipSuccess)
       return fail(hip_error(p, e, "allocate plan buffers"));
-  if ((e = hipHostMalloc((void **)&p->h_curves, desc_bytes((int)nc), 0)) != hipSuccess)
+  static_assert(kCurveOk == 0, "a status not yet written is that of a valid curve");
+  if ((e = hipMemset(p->d_status, 0, 4 * nc)) != hipSuccess)
+    return fail(hip_error(p, e, "clear plan buffers"));
+  if ((e = hipHostMalloc((void **)&p->h_curves, desc_bytes((int)nc), 0)) != hipSuccess ||
+      (e = hipHostMalloc((void **)&p->h_status, 4 * nc, 0)) != hipSuccess)
     return fail(hip_error(p, e, "allocate pinned descriptors"));
   *out = p;
   return BLS_OK;
@@ -1243,11 +1275,10 @@ int bls_plan_destroy(bls_plan *p) {
                   (void *)p->d_uws})
     free_dev(d);
   for (void *d : {(void *)p->d_curves, (void *)p->d_dt, (void *)p->d_q, (void *)p->d_qw,
-                  (void *)p->d_counter, (void *)p->d_t, (void *)p->d_x, (void *)p->d_w,
-                  (void *)p->d_periods, (void *)p->d_sr, (void *)p->d_depth, (void *)p->d_j,
-                  (void *)p->d_k, (void *)p->d_best})
+                  (void *)p->d_counter, (void *)p->d_status, (void *)p->d_t,
+                  (void *)p->d_sr})
     free_dev(d);
-  for (void *h : {(void *)p->h_curves, (void *)p->h_stage})
+  for (void *h : {(void *)p->h_curves, (void *)p->h_status, (void *)p->h_stage})
     if (h) (void)hipHostFree(h);
   for (hipEvent_t ev : {p->ev_begin, p->ev_search0, p->ev_search1, p->ev_end, p->ev_desc})
     if (ev) (void)hipEventDestroy(ev);
@@ -1763,13 +1794,18 @@ int bls_synchronize(bls_plan *p) {
   if (!p) return BLS_ERR_INVALID_ARG;
   hipError_t e = hipSetDevice(p->device);
   if (e != hipSuccess) return hip_error(p, e, "set device");
-  if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) return hip_error(p, e, "synchronize");
+  // one wait for the results and the curves' status
+  if (p->last.ncurves > 0) {
+    const int st = read_device_status(p, p->last.ncurves);
+    if (st != BLS_OK) return st;
+  } else if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) {
+    return hip_error(p, e, "synchronize");
+  }
   float ms = 0.f;
   if (hipEventElapsedTime(&ms, p->ev_begin, p->ev_end) == hipSuccess) p->stats.total_ms = ms;
   p->desc_pending = false;
   p->stats.search_ms = last_kernel_ms(p);
-  if (p->last.ncurves > 0) return check_device_status(p, p->last.ncurves);
-  return BLS_OK;
+  return p->last.ncurves > 0 ? check_device_status(p, p->last.ncurves) : BLS_OK;
 }
 
 int bls_get_stream(const bls_plan *p, void **stream) {

@@ -63,6 +63,7 @@ struct bls_plan {
   int64_t *d_seg_start = nullptr;
   int32_t *d_seg_curve = nullptr;
   int32_t *d_seg_tile0 = nullptr;
+  int32_t *d_status = nullptr;
   double *d_dt = nullptr;
   int32_t *d_q = nullptr;
   int32_t *d_qw = nullptr;
@@ -107,6 +108,7 @@ struct bls_plan {
   int64_t *h_seg_start = nullptr;
   int32_t *h_seg_curve = nullptr;
   int32_t *h_seg_tile0 = nullptr;
+  int32_t *h_status = nullptr;  // the curves' status, read back
 
   // bls_search_device: while nothing has rewritten the descriptors, a call
   // like the last one launches its plan (last) again, without validation,
