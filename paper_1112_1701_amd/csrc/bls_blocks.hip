@@ -856,7 +856,7 @@ __attribute__((amdgpu_waves_per_eu(WEIGHTED ? 5 : 6))) void block_search_kernel(
       // The rest, 64 kPPT points a wave as long as they last.
       const int64_t first = base + wave * 64 * kPPT;
       if (first + 64 * kPPT <= n)
-        fold_chunk<WEIGHTED, true, false>(a, fd, base, np, s_f, s_hist, HS, 1);
+        fold_chunk<WEIGHTED, false>(a, fd, base, np, s_f, s_hist, HS, 1);
       else if (first < n)
         fold_tail<WEIGHTED>(a, fd, first, (int)(n - first), np, s_f, s_hist, HS);
       __syncthreads();

@@ -136,10 +136,9 @@ __device__ inline void fold_load(const SearchArgs &a, int64_t off, int k0, FoldR
 // Bin a thread's kPPT loaded points at the tile's np periods.  MERGE:
 // consecutive points of a thread that share a bin are summed first; without
 // it every point is one atomic (tiles whose periods are short against the
-// cadence, where neighbours almost never share a bin).  FULL: all points
-// exist, otherwise those with ok[r].
-template <bool WEIGHTED, bool FULL, bool MERGE>
-__device__ inline void fold_points(const FoldRegs &p, const bool *ok, int nbins, int shift, int np,
+// cadence, where neighbours almost never share a bin).
+template <bool WEIGHTED, bool MERGE>
+__device__ inline void fold_points(const FoldRegs &p, int nbins, int shift, int np,
                                    const double *s_f, unsigned long long *s_hist, int HS) {
   const double nbd = (double)nbins;
   const unsigned long long one = 1ull << shift;
@@ -168,65 +167,83 @@ __device__ inline void fold_points(const FoldRegs &p, const bool *ok, int nbins,
     if (!MERGE) {
 #pragma unroll
       for (int r = 0; r < kPPT; ++r) {
-        if (FULL || ok[r]) {
-          __hip_atomic_fetch_add(h + bin[r], va[r], __ATOMIC_RELAXED,
+        __hip_atomic_fetch_add(h + bin[r], va[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (WEIGHTED)
+          __hip_atomic_fetch_add(h + HS + bin[r], vb[r], __ATOMIC_RELAXED,
                                  __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (WEIGHTED)
-            __hip_atomic_fetch_add(h + HS + bin[r], vb[r], __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
       }
       continue;
     }
     unsigned long long accA = 0, accB = 0;
 #pragma unroll
     for (int r = 0; r < kPPT; ++r) {
-      if (FULL || ok[r]) {
-        accA += va[r];
-        if (WEIGHTED) accB += vb[r];
-        const int rn = r + 1 < kPPT ? r + 1 : r;
-        const bool run_ends = r == kPPT - 1 || !(FULL || ok[rn]) || bin[rn] != bin[r];
-        if (run_ends) {
-          __hip_atomic_fetch_add(h + bin[r], accA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          if (WEIGHTED)
-            __hip_atomic_fetch_add(h + HS + bin[r], accB, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_WORKGROUP);
-          accA = 0;
-          accB = 0;
-        }
+      accA += va[r];
+      if (WEIGHTED) accB += vb[r];
+      if (r == kPPT - 1 || bin[r + 1 < kPPT ? r + 1 : r] != bin[r]) {  // the run ends
+        __hip_atomic_fetch_add(h + bin[r], accA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (WEIGHTED)
+          __hip_atomic_fetch_add(h + HS + bin[r], accB, __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+        accA = 0;
+        accB = 0;
       }
     }
   }
 }
 
-// Load and bin one chunk of kBlock kPPT points (FULL: all of them exist).
-template <bool WEIGHTED, bool FULL, bool MERGE>
+// Load and bin one chunk of kBlock kPPT points (or, gap 1, the calling wave's
+// 64 kPPT of them).
+template <bool WEIGHTED, bool MERGE>
 __device__ inline void fold_chunk(const SearchArgs &a, const CurveDesc &cd, int64_t base,
                                   int np, const double *s_f, unsigned long long *s_hist,
                                   int HS, int gap) {
-  // The chunk's first point and the points left from there, kept in scalar
-  // registers.
-  const int64_t off = uniform_i64(cd.n_off + base);
-  const int64_t left = uniform_i64(cd.n - base);
   // The gap passes through an opaque copy so that the compiler recomputes
   // the offset per chunk instead of holding it in VGPRs through the item.
   asm volatile("" : "+s"(gap));
-  const int k0 = fold_offset(gap);
   FoldRegs p;
-  bool ok[kPPT];
-  if (FULL) {
-    fold_load<WEIGHTED>(a, off, k0, p);
-  } else {
+  fold_load<WEIGHTED>(a, uniform_i64(cd.n_off + base), fold_offset(gap), p);
+  fold_points<WEIGHTED, MERGE>(p, cd.nbins, cd.shift, np, s_f, s_hist, HS);
+}
+
+// The curve's last points, fewer than kBlock kPPT of them (`left` from point
+// `base` on), kPPT to a thread as in a whole chunk; each point is one atomic
+// (merging them, with a bounds check on every step, took 1.5% longer on 550
+// points, and 2.3% on 240 weighted curves of about 2500).
+template <bool WEIGHTED>
+__device__ inline void fold_rest(const SearchArgs &a, const CurveDesc &cd, int64_t base, int left,
+                                 int np, const double *s_f, unsigned long long *s_hist, int HS) {
+  const int64_t off = uniform_i64(cd.n_off + base);
+  const int k0 = fold_offset(1);
+  const double nbd = (double)cd.nbins;
+  const unsigned long long one = 1ull << cd.shift;
+  double d[kPPT];
+  unsigned long long va[kPPT], vb[kPPT];
+#pragma unroll
+  for (int r = 0; r < kPPT; ++r) {
+    const bool ok = k0 + r < left;
+    const int64_t i = off + (ok ? k0 + r : 0);
+    d[r] = a.dt[i];
+    const long long qi = a.q[i];
+    const int qwi = WEIGHTED ? a.qw[i] : 0;
+    va[r] = !WEIGHTED ? one + (unsigned long long)qi
+            : qwi >= 0 ? one + (unsigned long long)(long long)qwi : 0ull;
+    vb[r] = (unsigned long long)qi;
+  }
+  constexpr int wpb = WEIGHTED ? 2 : 1;
+  if (k0 >= left) return;
+  for (int t = 0; t < np; ++t) {
+    unsigned long long *h = s_hist + (size_t)t * HS * wpb;
+    const double f = s_f[t];
 #pragma unroll
     for (int r = 0; r < kPPT; ++r) {
-      const int k = k0 + r;
-      ok[r] = (int64_t)k < left;
-      p.d[r] = ok[r] ? a.dt[off + k] : 0.0;
-      p.q[r] = ok[r] ? a.q[off + k] : 0;
-      p.qw[r] = WEIGHTED && ok[r] ? a.qw[off + k] : 0;
+      if (k0 + r < left) {
+        unsigned long long *w = h + raw_bin(d[r], f, nbd);
+        __hip_atomic_fetch_add(w, va[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (WEIGHTED)
+          __hip_atomic_fetch_add(w + HS, vb[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
     }
   }
-  fold_points<WEIGHTED, FULL, MERGE>(p, ok, cd.nbins, cd.shift, np, s_f, s_hist, HS);
 }
 
 // The whole chunks of a curve, each one's points loaded while the one before
@@ -243,7 +260,7 @@ __device__ inline void fold_chunks(const SearchArgs &a, const CurveDesc &cd, int
     const FoldRegs p = next;
     off += kBlock * kPPT;
     if (i + 1 < nchunks) fold_load<WEIGHTED>(a, off, k0, next);
-    fold_points<WEIGHTED, true, MERGE>(p, nullptr, cd.nbins, cd.shift, np, s_f, s_hist, HS);
+    fold_points<WEIGHTED, MERGE>(p, cd.nbins, cd.shift, np, s_f, s_hist, HS);
   }
 }
 

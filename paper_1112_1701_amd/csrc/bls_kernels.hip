@@ -701,15 +701,16 @@ void search_kernel(SearchArgs a) {
     const bool merge = fold_merges(ftile, cd.nbins, cd.cadence, a.fold_policy, WEIGHTED);
 
     // Fold and bin: points in registers, reused for every period of the tile.
-    for (int64_t base = 0; base < cd.n; base += (int64_t)kBlock * kPPT) {
-      if (base + (int64_t)kBlock * kPPT <= cd.n) {
+    {
+      const int64_t base = cd.n / (kBlock * kPPT) * (kBlock * kPPT);
+      for (int64_t b = 0; b < base; b += (int64_t)kBlock * kPPT) {
         if (merge)
-          fold_chunk<WEIGHTED, true, true>(a, cd, base, np, s_f, s_hist, HS, lanes_gap);
+          fold_chunk<WEIGHTED, true>(a, cd, b, np, s_f, s_hist, HS, lanes_gap);
         else
-          fold_chunk<WEIGHTED, true, false>(a, cd, base, np, s_f, s_hist, HS, lanes_gap);
-      } else {
-        fold_chunk<WEIGHTED, false, true>(a, cd, base, np, s_f, s_hist, HS, 1);
+          fold_chunk<WEIGHTED, false>(a, cd, b, np, s_f, s_hist, HS, lanes_gap);
       }
+      if (base < cd.n)
+        fold_rest<WEIGHTED>(a, cd, base, (int)(cd.n - base), np, s_f, s_hist, HS);
     }
     __syncthreads();
 
