@@ -845,7 +845,8 @@ __attribute__((amdgpu_waves_per_eu(WEIGHTED ? 5 : 6))) void block_search_kernel(
       const double ftile = fmin(s_f[0], s_f[np - 1]);
       const int gap = uniform(fold_lane_gap(ftile, fd.nbins, cd.cadence));
       const bool merge =
-          uniform((int)fold_merges(ftile, fd.nbins, cd.cadence, a.fold_policy, WEIGHTED)) != 0;
+          uniform((int)fold_merges(ftile, fd.nbins, cd.cadence, a.fold_policy, WEIGHTED, 0.15)) !=
+          0;
       const int64_t nchunks = n / (kBlock * kPPT), base = nchunks * (kBlock * kPPT);
       if (nchunks > 0) {
         if (merge)

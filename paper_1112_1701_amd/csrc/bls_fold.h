@@ -85,12 +85,15 @@ __device__ inline int fold_lane_gap(double fmin, int nbins, float cadence) {
 // 2: never).  The merge costs VALU operations on every point and saves one
 // LDS atomic per point it joins; shorter runs do not repay it.  A weighted
 // point saves two atomics, and there the merge pays from one bin per step.
+// The block search, whose VALU is the busier, merges unit-weight points from
+// 0.15 bins per step (1000 bins, 1-minute cadence, 8 curves x 40000 periods of
+// 1.5 to 3 days: 7.2 ms merged, 6.8 not; 6 to 20 days: 7.4 and 7.9).
 // Any answer is correct; this one only picks the faster fold.
 __device__ inline bool fold_merges(double fmin, int nbins, float cadence, int policy,
-                                   bool weighted) {
+                                   bool weighted, double from = 0.3) {
   if (policy != 0) return policy == 1;
   const double x = fmin * (double)nbins * (double)cadence;
-  return !(x >= (weighted ? 1.0 : 0.3));
+  return !(x >= (weighted ? 1.0 : from));
 }
 
 // Fold and bin one chunk of kBlock * kPPT points into the tile's histograms.
@@ -137,7 +140,10 @@ __device__ inline void fold_load(const SearchArgs &a, int64_t off, int k0, FoldR
 // consecutive points of a thread that share a bin are summed first; without
 // it every point is one atomic (tiles whose periods are short against the
 // cadence, where neighbours almost never share a bin).
-template <bool WEIGHTED, bool MERGE>
+// AHEAD: the next period's frequency is read before this one's atomics (LDS
+// operations end in order, and a read after them waits for them all); for
+// kernels that have the registers.
+template <bool WEIGHTED, bool MERGE, bool AHEAD>
 __device__ inline void fold_points(const FoldRegs &p, int nbins, int shift, int np,
                                    const double *s_f, unsigned long long *s_hist, int HS) {
   const double nbd = (double)nbins;
@@ -156,8 +162,10 @@ __device__ inline void fold_points(const FoldRegs &p, int nbins, int shift, int 
     }
   }
   constexpr int wpb = WEIGHTED ? 2 : 1;
+  double fnext = AHEAD ? s_f[0] : 0.0;
   for (int t = 0; t < np; ++t) {
-    const double f = s_f[t];
+    const double f = AHEAD ? fnext : s_f[t];
+    if (AHEAD) fnext = s_f[min(t + 1, np - 1)];
     unsigned long long *h = s_hist + (size_t)t * HS * wpb;
     // A thread's consecutive points that share a bin (common at long
     // periods) are summed in registers and sent as one atomic.
@@ -202,7 +210,7 @@ __device__ inline void fold_chunk(const SearchArgs &a, const CurveDesc &cd, int6
   asm volatile("" : "+s"(gap));
   FoldRegs p;
   fold_load<WEIGHTED>(a, uniform_i64(cd.n_off + base), fold_offset(gap), p);
-  fold_points<WEIGHTED, MERGE>(p, cd.nbins, cd.shift, np, s_f, s_hist, HS);
+  fold_points<WEIGHTED, MERGE, false>(p, cd.nbins, cd.shift, np, s_f, s_hist, HS);
 }
 
 // The curve's last points, fewer than kBlock kPPT of them (`left` from point
@@ -260,7 +268,7 @@ __device__ inline void fold_chunks(const SearchArgs &a, const CurveDesc &cd, int
     const FoldRegs p = next;
     off += kBlock * kPPT;
     if (i + 1 < nchunks) fold_load<WEIGHTED>(a, off, k0, next);
-    fold_points<WEIGHTED, MERGE>(p, cd.nbins, cd.shift, np, s_f, s_hist, HS);
+    fold_points<WEIGHTED, MERGE, true>(p, cd.nbins, cd.shift, np, s_f, s_hist, HS);
   }
 }
 
