@@ -14,7 +14,7 @@
 // Measured, search_kernel against this one: 169 weighted curves x 859 points
 // x 6456 periods x 525 bins 21.9 / 8.6 ms; 6 x 24601 x 26314 x 897 (0.005 to
 // 0.08) 3.15 / 2.35; weighted 3 x 36710 x 42741 x 864 7.1 / 3.8; 24 x 50000 x
-// 100000 x 1000 (0.005 to 0.05) 51.5 / 46.7.  VALU-bound up to about 600
+// 100000 x 1000 (0.005 to 0.05) 51.5 / 44.4.  VALU-bound up to about 600
 // bins (0.95 instructions per SIMD and clock issued of 1); beyond that the
 // LDS leaves too few waves to fill the latencies.
 //
@@ -750,9 +750,17 @@ struct PeriodScan {
   }
 };
 
-template <bool WEIGHTED, bool DIP>
+// WIDE: the copy for launches of at most four workgroups per CU, which have
+// the registers of four waves per SIMD to themselves.  In the others' 80 (96
+// weighted) VGPRs a period's set-up spills 26 (32), 12.6 GB of writes for 256
+// x 50000 points x 100000 periods x 1000 bins; in 115 (128) none (one) does.
+// 24 x 50000 x 100000 x 1000: 44.9 / 44.4 ms; weighted 23 x 805 x 9306 x 585
+// 1.84 / 1.80; but 158 x 1346 x 5016 x 218, whose LDS leaves room for six,
+// 1.94 / 2.30.
+template <bool WEIGHTED, bool DIP, bool WIDE>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(WEIGHTED ? 5 : 6))) void block_search_kernel(SearchArgs a) {
+__attribute__((amdgpu_waves_per_eu(WIDE ? 4 : WEIGHTED ? 5 : 6))) void block_search_kernel(
+    SearchArgs a) {
   extern __shared__ __align__(16) u64 s_hist[];
   __shared__ double s_f[kTileMax];
   __shared__ CurveDesc s_cd;
@@ -919,14 +927,20 @@ __attribute__((amdgpu_waves_per_eu(WEIGHTED ? 5 : 6))) void block_search_kernel(
   }
 }
 
+template <bool WEIGHTED, bool DIP, bool WIDE>
+const void *block_fn() {
+  return reinterpret_cast<const void *>(&block_search_kernel<WEIGHTED, DIP, WIDE>);
+}
+
 }  // namespace
 
-const void *block_search_fn(bool weighted, bool dip) {
-  if (weighted)
-    return dip ? reinterpret_cast<const void *>(&block_search_kernel<true, true>)
-               : reinterpret_cast<const void *>(&block_search_kernel<true, false>);
-  return dip ? reinterpret_cast<const void *>(&block_search_kernel<false, true>)
-             : reinterpret_cast<const void *>(&block_search_kernel<false, false>);
+const void *block_search_fn(bool weighted, bool dip, bool wide) {
+  if (weighted) {
+    if (wide) return dip ? block_fn<true, true, true>() : block_fn<true, false, true>();
+    return dip ? block_fn<true, true, false>() : block_fn<true, false, false>();
+  }
+  if (wide) return dip ? block_fn<false, true, true>() : block_fn<false, false, true>();
+  return dip ? block_fn<false, true, false>() : block_fn<false, false, false>();
 }
 
 }  // namespace bls

@@ -162,8 +162,9 @@ inline int block_scratch_bytes(int nbins, const BlockGeom &g) {
                 4 * ((nbins + 31) / 32);
   return (n + 15) & ~15;
 }
-// The block kernel for a launch (bls_blocks.hip).
-const void *block_search_fn(bool weighted, bool dip);
+// The block kernel for a launch (bls_blocks.hip); wide: the copy of four waves
+// per SIMD.
+const void *block_search_fn(bool weighted, bool dip, bool wide);
 
 // One partition over all items (callers without an XCD split).
 inline void single_partition(SearchArgs &a) {

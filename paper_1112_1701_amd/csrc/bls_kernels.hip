@@ -13,8 +13,11 @@
 //                   LDS atomic max on (value, -index)
 //   fill_kernel / best_index_kernel  counter set-up (calls without a prep
 //                   kernel, which does it itself) and per-curve key read-out
-//                   (plain kernels so that the sequence can be captured in a
-//                   HIP graph)
+//                   (plain kernels, not memsets, so that the sequence can be
+//                   captured in a caller's HIP graph)
+//
+// Launches whose boxes are better searched by blocks run block_search_kernel
+// (bls_blocks.hip) in place of search_kernel.
 //
 // The unbinned search (bls_unbinned.hip), the detection statistics
 // (bls_detect.hip), the eclipse detection efficiency (bls_window.hip) and
@@ -984,6 +987,17 @@ const void *pick(bool weighted, bool dip, int hist_bytes) {
   return dip ? search_fn<false, true, true>() : search_fn<false, false, true>();
 }
 
+// The block kernel's copy for a launch: the wide one where the launch has at
+// most the four workgroups per CU that its registers allow, be it for LDS or
+// for want of items (BLS_WIDE_REGS=0/1 forces the choice).
+bool block_wide(int grid) {
+  if (const char *e = getenv("BLS_WIDE_REGS")) return atoi(e) != 0;
+  int dev = 0, cus = 0;
+  return hipGetDevice(&dev) == hipSuccess &&
+         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+         grid <= 4 * cus;
+}
+
 }  // namespace
 
 int launch_fill(unsigned long long *counter, unsigned long long *keys, int32_t nkeys,
@@ -1002,7 +1016,7 @@ int launch_prep(const PrepArgs &a, void *stream) {
 
 int launch_search(const SearchArgs &a, bool weighted, bool dip_only, int grid, void *stream) {
   if (a.nitems <= 0) return 0;
-  const void *fn = a.scr_bytes > 0 ? block_search_fn(weighted, dip_only)
+  const void *fn = a.scr_bytes > 0 ? block_search_fn(weighted, dip_only, block_wide(grid))
                                    : pick(weighted, dip_only, a.hist_bytes);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, a.hist_bytes);
   if (e != hipSuccess) return (int)e;
@@ -1030,7 +1044,7 @@ int launch_best_index(unsigned long long *keys, int32_t n, void *stream) {
 
 int search_blocks_per_cu(bool weighted, bool dip_only, bool block, int hist_bytes, int *blocks) {
   const void *fn =
-      block ? block_search_fn(weighted, dip_only) : pick(weighted, dip_only, hist_bytes);
+      block ? block_search_fn(weighted, dip_only, false) : pick(weighted, dip_only, hist_bytes);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, hist_bytes);
   if (e != hipSuccess) return (int)e;
   return (int)hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks, fn, kBlock, (size_t)hist_bytes);

@@ -78,3 +78,16 @@ def test_blocks_ties(bls, monkeypatch, kind, n, nbins, weights):
     print("[case] ties", kind, n, nbins, weights, flush=True)
     for cfg in (dict(), dict(flags=bls.BLS_DIP_ONLY, min_in_points=2)):
         _both(bls, monkeypatch, lc, **cfg)
+
+
+@pytest.mark.parametrize("nbins,qmin,qmax,n", [(64, 0.02, 0.2, 700), (1000, 0.005, 0.05, 4000)])
+@pytest.mark.parametrize("weighted,flags", [(False, 0), (True, 0), (False, 1), (True, 1)])
+def test_register_copies_agree(bls, monkeypatch, nbins, qmin, qmax, n, weighted, flags):
+    """The copies of four and of more waves per SIMD, each forced, return the
+    bits of the kernel that scores every box."""
+    lc = synth.small_curve(9300 + nbins, n, nperiods=1500, nbins=nbins, qmin=qmin, qmax=qmax,
+                           weighted=weighted)
+    print("[case] copies", nbins, n, weighted, flags, flush=True)
+    for wide in ("0", "1"):
+        monkeypatch.setenv("BLS_WIDE_REGS", wide)
+        _both(bls, monkeypatch, lc, flags=flags)
