@@ -6,8 +6,8 @@ high-cadence long-baseline workload (256 light curves x N = 50000 epochs on a
 0.1-20 d, 1000 phase bins, box duty cycles 0.005-0.05), the largest
 single-GPU workload in trial-period x points, with the inputs already in HBM:
 prep (centring, t0, fixed-point encoding), fold + bin, box scan, per-period
-argmax and per-curve best period, all in the HIP library, replayed as HIP
-graphs.  The search kernel's duration is read from the HIP events the library
+argmax and per-curve best period, all in the HIP library, with the last
+call's plan reused.  The search kernel's duration is read from the HIP events the library
 records around it on its stream in every timed step.  Prints ONE JSON line
 with the metric, the roofline of the dominant kernel (the search kernel,
 per-unit operation counts against the published FP64/FP32 peaks), its LDS
@@ -144,7 +144,7 @@ class DeviceBatch:
 
 
 def time_batched(bls, db, steps, warmup):
-    """Graph-replayed steps, bracketed by device synchronizations.
+    """Steps on a reused plan, bracketed by device synchronizations.
 
     Returns (ms per step, call statistics, search-kernel ms of each timed
     step from the events the library records around the kernel on its
@@ -170,7 +170,7 @@ def time_batched(bls, db, steps, warmup):
 
 
 def time_kernel(bls, db, reps):
-    """The search kernel of non-graph calls (HIP events around the launch)."""
+    """The search kernel of calls planned afresh (HIP events around the launch)."""
     kplan = bls.Plan(flags=bls.BLS_NO_GRAPH, **db.cap)
     kms = []
     for _ in range(max(reps, 3)):
@@ -183,7 +183,7 @@ def time_kernel(bls, db, reps):
 
 
 def time_plain(bls, db, max_curves, budget_s=5.0):
-    """Plain per-curve GPU form: one synchronous, non-graph call per curve."""
+    """Plain per-curve GPU form: one synchronous call per curve."""
     import torch
     b = db.b
     plan = bls.Plan(flags=bls.BLS_NO_GRAPH, **db.cap)
@@ -231,7 +231,10 @@ def time_host_arrays(bls, b, reps=2):
             "trial_points_per_s": b.trial_points() / el}
 
 
-KERNEL_SOURCE = os.path.join(ROOT, "paper_1112_1701_amd", "csrc", "bls_kernels.hip")
+# Sources of the search kernel a workload runs (the long baseline's boxes are
+# searched by blocks).
+BOX_SOURCES = ("bls_kernels.hip", "bls_fold.h")
+SEARCH_SOURCES = {"long": ("bls_blocks.hip", "bls_fold.h")}
 PROFILE_TAG = {"long": "long256", "uniform": "uniform4096",
                "uneven": "uneven10000", "plain": "plain1"}
 
@@ -239,7 +242,7 @@ PROFILE_TAG = {"long": "long256", "uniform": "uniform4096",
 def _profile_record(kind, workload):
     """key: value lines of profiles/search_kernel_<workload>_<kind>.txt, or
     None when missing or taken on another version of the kernel source (the
-    file records the SHA-256 of the source its counters were taken on)."""
+    file records the SHA-256 of the sources its counters were taken on)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "search_kernel_%s_%s.txt"
                         % (PROFILE_TAG.get(workload, workload), kind))
@@ -252,8 +255,11 @@ def _profile_record(kind, workload):
         if ":" in line and not line.startswith((" ", "#")):
             k, v = line.split(":", 1)
             vals[k.strip()] = v.strip()
-    src = hashlib.sha256(open(KERNEL_SOURCE, "rb").read()).hexdigest()
-    if vals.get("kernel_source_sha256") != src:
+    src = hashlib.sha256()
+    for name in SEARCH_SOURCES.get(workload, BOX_SOURCES):
+        with open(os.path.join(ROOT, "paper_1112_1701_amd", "csrc", name), "rb") as f:
+            src.update(f.read())
+    if vals.get("kernel_source_sha256") != src.hexdigest():
         return None
     return vals
 
@@ -270,7 +276,9 @@ def measured_traffic(workload):
 def roofline(pp, evals, k_ms, traffic=None):
     """The search kernel against the published FP64 and FP32 peaks: the
     algorithmic operations (FP64_OPS_PER_TRIAL_POINT, FP32_OPS_PER_BOX_EVAL)
-    over the launch's duration, in FP32-equivalent TFLOP/s."""
+    over the launch's duration, in FP32-equivalent TFLOP/s.  Every box counts
+    as evaluated, also where bounds on blocks of boxes exclude it: an
+    effective rate for the long baseline."""
     t = k_ms * 1e-3
     flop32 = 2 * FP64_OPS_PER_TRIAL_POINT * pp + FP32_OPS_PER_BOX_EVAL * evals
     achieved = flop32 / t / 1e12
@@ -327,7 +335,7 @@ def _generate(name):
 
 
 def extra_batch(bls, name, steps):
-    """Graph-replayed throughput of another batch workload."""
+    """Throughput of another batch workload."""
     b = _generate(name)
     db = DeviceBatch(b)
     ms_step, st, kms = time_batched(bls, db, steps, 1)

@@ -274,8 +274,8 @@ TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool
   if (!tuned) {
     // The built-in table, with the tile cut so that the call has work items
     // for two workgroups per CU.  Tiles any smaller only add per-item work:
-    // one 1000-point curve x 5000 periods (200 bins) took 69 / 50 / 62 /
-    // 93 us with tiles of 18 / 8 / 4 / 2 periods.
+    // one 1000-point curve x 5000 periods (200 bins) took 38 / 38 / 42 / 46 /
+    // 76 / 102 us of kernel with tiles of 9 / 6 / 4 / 3 / 2 / 1 periods.
     const int64_t cap = std::max<int64_t>(1, periods / (2 * (int64_t)std::max(p->num_cus, 1)));
     tc.tile_cap = (int)std::min<int64_t>(tc.tile_cap, cap);
     return tc;

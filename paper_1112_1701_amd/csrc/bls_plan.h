@@ -161,7 +161,7 @@ int validate_batch_into(const bls_plan_config &cfg, const bls_batch &b, bool che
 // layout, and the period tile and plane stride that fit tc's LDS budget.
 // memo: keep the bank-conflict costs of plane strides in the process-wide
 // cache (false: compute them afresh, with no heap use).
-// block: the layout of the block search (see block_curve).
+// block: the layout of the block search (bls_blocks.hip).
 void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
                      bool check_periods, bool memo, bool block, CurveDesc &d);
 

@@ -30,9 +30,9 @@ namespace {
 //
 // What bounds it, and what it measured against the walk over every start's
 // ends, eight at a time, that the screens replace.  8 curves of 1000 points x
-// 5000 periods: 1.87 / 1.13 ms, instruction issue (10000 wave instructions a
+// 5000 periods: 1.79 / 1.03 ms, instruction issue (10000 wave instructions a
 // period, of which the walk alone took that many; two thirds now the screens,
-// one third the sort).  2 curves of 20000 points x 1500 periods: 30.9 / 2.75
+// one third the sort).  2 curves of 20000 points x 1500 periods: 31.0 / 2.67
 // ms, latency of the workspace: the sort with its cell counts in device
 // memory took two thirds of the time, and now, the counts in LDS and four
 // points of a thread in flight, about half.
