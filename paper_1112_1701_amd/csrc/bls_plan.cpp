@@ -722,7 +722,7 @@ int enqueue_pre(bls_plan *p, const PlannedBatch &pb, const double *t, const doub
   pa.qw = p->d_qw;
   pa.counter = p->d_counter;
   pa.keys = reinterpret_cast<unsigned long long *>(best);
-  pa.status = p->d_status;
+  pa.status = p->status_dev;
   e = (hipError_t)launch_prep(pa, st);
   if (e != hipSuccess) return hip_error(p, e, "launch prep");
   return BLS_OK;
@@ -867,13 +867,9 @@ int ensure_staging(bls_plan *p) {
 }
 
 // Waits for the stream; the curves' status is then in p->h_status.
-int read_device_status(bls_plan *p, int ncurves) {
-  hipError_t e;
-  if ((e = hipMemcpyAsync(p->h_status, p->d_status, sizeof(int32_t) * ncurves,
-                          hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
-      (e = hipStreamSynchronize(p->stream)) != hipSuccess)
-    return hip_error(p, e, "synchronize");
-  return BLS_OK;
+int wait_for_status(bls_plan *p) {
+  const hipError_t e = hipStreamSynchronize(p->stream);
+  return e == hipSuccess ? BLS_OK : hip_error(p, e, "synchronize");
 }
 
 int check_device_status(bls_plan *p, int ncurves) {
@@ -897,7 +893,7 @@ int check_device_status(bls_plan *p, int ncurves) {
 // Per-curve validity flags of the last prep (1 where the curve's data or
 // trial periods were invalid), read back from the device descriptors.
 int device_status_flags(bls_plan *p, int ncurves, int32_t *bad) {
-  const int st = read_device_status(p, ncurves);
+  const int st = wait_for_status(p);
   if (st != BLS_OK) return st;
   for (int c = 0; c < ncurves; ++c) bad[c] = p->h_status[c] != kCurveOk ? 1 : 0;
   return BLS_OK;
@@ -1116,7 +1112,7 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
                  hipSuccess) {
     return hip_error(p, e, "download results");
   }
-  st = read_device_status(p, b.ncurves);
+  st = wait_for_status(p);
   if (st == BLS_OK) st = check_device_status(p, b.ncurves);
   if (st != BLS_OK) return st;
 
@@ -1251,19 +1247,16 @@ int bls_plan_create(bls_plan **out, const bls_plan_config *cfg_in) {
              {(void **)&p->d_dt, 8 * npt},
              {(void **)&p->d_q, 4 * npt},
              {(void **)&p->d_qw, 4 * npt},
-             {(void **)&p->d_status, 8 * ((nc + 1) / 2)},
              {(void **)&p->d_counter, 64}};
   for (auto &r : req)
     if ((e = device_alloc(r.ptr, r.bytes)) != hipSuccess)
       return fail(hip_error(p, e, "allocate plan buffers"));
-  static_assert(kCurveOk == 0, "a status not yet written is that of a valid curve");
-  // (a kernel on the plan's stream: a hipMemset would be waited for, 70 us)
-  if ((e = (hipError_t)launch_fill(p->d_counter, (unsigned long long *)p->d_status,
-                                   (int32_t)((nc + 1) / 2), p->stream)) != hipSuccess)
-    return fail(hip_error(p, e, "clear plan buffers"));
   if ((e = hipHostMalloc((void **)&p->h_curves, desc_bytes((int)nc), 0)) != hipSuccess ||
-      (e = hipHostMalloc((void **)&p->h_status, 4 * nc, 0)) != hipSuccess)
+      (e = hipHostMalloc((void **)&p->h_status, 4 * nc, hipHostMallocCoherent)) != hipSuccess ||
+      (e = hipHostGetDevicePointer((void **)&p->status_dev, p->h_status, 0)) != hipSuccess)
     return fail(hip_error(p, e, "allocate pinned descriptors"));
+  static_assert(kCurveOk == 0, "a status not yet written is that of a valid curve");
+  memset(p->h_status, 0, 4 * nc);
   *out = p;
   return BLS_OK;
 }
@@ -1277,8 +1270,7 @@ int bls_plan_destroy(bls_plan *p) {
                   (void *)p->d_uws})
     free_dev(d);
   for (void *d : {(void *)p->d_curves, (void *)p->d_dt, (void *)p->d_q, (void *)p->d_qw,
-                  (void *)p->d_counter, (void *)p->d_status, (void *)p->d_t,
-                  (void *)p->d_sr})
+                  (void *)p->d_counter, (void *)p->d_t, (void *)p->d_sr})
     free_dev(d);
   for (void *h : {(void *)p->h_curves, (void *)p->h_status, (void *)p->h_stage})
     if (h) (void)hipHostFree(h);
@@ -1797,12 +1789,8 @@ int bls_synchronize(bls_plan *p) {
   hipError_t e = hipSetDevice(p->device);
   if (e != hipSuccess) return hip_error(p, e, "set device");
   // one wait for the results and the curves' status
-  if (p->last.ncurves > 0) {
-    const int st = read_device_status(p, p->last.ncurves);
-    if (st != BLS_OK) return st;
-  } else if ((e = hipStreamSynchronize(p->stream)) != hipSuccess) {
-    return hip_error(p, e, "synchronize");
-  }
+  const int st = wait_for_status(p);
+  if (st != BLS_OK) return st;
   float ms = 0.f;
   if (hipEventElapsedTime(&ms, p->ev_begin, p->ev_end) == hipSuccess) p->stats.total_ms = ms;
   p->desc_pending = false;

@@ -63,3 +63,35 @@ def test_reused_plan():
             assert bls.bls_last_stats(q.handle)["graph_replayed"] == 0
             for a, b, c in zip(first, again, want):
                 assert np.array_equal(a, c) and np.array_equal(b, c), (k, between)
+
+
+@pytest.mark.parametrize("nc", [1, 5, 300])
+def test_status_of_queued_calls(nc):
+    """The status that a wait reports is that of the last call queued before
+    it, whichever curve it is of."""
+    import torch
+
+    import paper_1112_1701_amd as bls
+    bls._lib.load()
+    dev = lambda a: torch.tensor(a, device="cuda:0")
+    n, m = 70, 40
+    lc = synth.small_curve(90, n, nperiods=m, nbins=50, qmin=0.02, qmax=0.2)
+    t, good = dev(np.tile(lc.t, nc)), dev(np.tile(lc.x, nc))
+    bad = good.clone()
+    bad[(nc - 1) * n + 5] = float("inf")
+    per, off = dev(lc.periods), np.arange(nc + 1) * n
+    out = [torch.empty(nc * m, device="cuda:0", dtype=d) for d in (
+        torch.float32, torch.float32, torch.int32, torch.int32)]
+    best = torch.empty(nc, device="cuda:0", dtype=torch.int64)
+    torch.cuda.synchronize()
+    with bls.Plan(max_curves=nc, max_points=nc * n, max_periods=nc * m) as p:
+        for x in ([good], [bad], [bad, good], [good, bad], [good]):
+            print("[case] status", nc, len(x), flush=True)
+            for v in x:
+                bls.bls_search_device(p.handle, off, t, v, None, per, None, 50, 0.02, 0.2,
+                                      *out, best)
+            if x[-1] is good:
+                bls.bls_synchronize(p.handle)
+            else:
+                with pytest.raises(bls.BlsError, match="curve %d" % (nc - 1)):
+                    bls.bls_synchronize(p.handle)
