@@ -298,7 +298,9 @@ int launch_fill(unsigned long long *counter, unsigned long long *keys,
 int launch_prep(const PrepArgs &a, void *stream);
 int launch_search(const SearchArgs &a, bool weighted, bool dip_only, int grid,
                   void *stream);
-int launch_best_index(unsigned long long *keys, int32_t n, void *stream);
+// (out may be keys)
+int launch_best_index(const unsigned long long *keys, unsigned long long *out, int32_t n,
+                      void *stream);
 // Phase bin of every prepared point at one period (diagnostic).
 int launch_bins(const double *dt, int64_t n, const double *period, int32_t nbins, int32_t *bins,
                 void *stream);

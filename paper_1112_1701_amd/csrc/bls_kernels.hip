@@ -948,11 +948,12 @@ __global__ void fill_kernel(unsigned long long *counter, unsigned long long *key
   if (i < nkeys) keys[i] = 0ull;
 }
 
-__global__ void best_index_kernel(unsigned long long *keys, int32_t n) {
+__global__ void best_index_kernel(const unsigned long long *keys, unsigned long long *out,
+                                  int32_t n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) {
     const unsigned long long k = keys[i];
-    keys[i] = (unsigned long long)(0xFFFFFFFFu - (unsigned)(k & 0xFFFFFFFFull));
+    out[i] = (unsigned long long)(0xFFFFFFFFu - (unsigned)(k & 0xFFFFFFFFull));
   }
 }
 
@@ -1035,10 +1036,11 @@ int launch_bins(const double *dt, int64_t n, const double *period, int32_t nbins
   return (int)hipGetLastError();
 }
 
-int launch_best_index(unsigned long long *keys, int32_t n, void *stream) {
+int launch_best_index(const unsigned long long *keys, unsigned long long *out, int32_t n,
+                      void *stream) {
   if (n <= 0) return 0;
   hipLaunchKernelGGL(best_index_kernel, dim3((n + 255) / 256), dim3(256), 0, (hipStream_t)stream,
-                     keys, n);
+                     keys, out, n);
   return (int)hipGetLastError();
 }
 

@@ -296,7 +296,7 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   if ((e = (hipError_t)launch_search(sa, weighted, (flags & BLS_DIP_ONLY) != 0, (int)grid,
                                      stream)) != hipSuccess)
     return set_error_noplan(BLS_ERR_DEVICE, "launch of the search kernel failed");
-  if ((e = (hipError_t)launch_best_index(keys, nc, stream)) != hipSuccess)
+  if ((e = (hipError_t)launch_best_index(keys, keys, nc, stream)) != hipSuccess)
     return set_error_noplan(BLS_ERR_DEVICE, "launch of the best-index kernel failed");
   return BLS_OK;
 }

@@ -225,7 +225,7 @@ int enqueue_post(bls_plan *p, const PlannedBatch &pb, int64_t *best);
 int enqueue_search(bls_plan *p, const PlannedBatch &pb, const double *t, const double *x,
                    const double *w, const double *periods, float *sr, float *depth,
                    int32_t *js, int32_t *ks, int64_t *best, bool unbinned = false,
-                   bool upload = true);
+                   bool upload = true, int64_t *keys = nullptr);
 // Bytes of the descriptors of nc curves, and their places in the pinned and
 // the device block.
 size_t desc_bytes(int nc);

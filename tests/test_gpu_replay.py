@@ -95,3 +95,28 @@ def test_status_of_queued_calls(nc):
             else:
                 with pytest.raises(bls.BlsError, match="curve %d" % (nc - 1)):
                     bls.bls_synchronize(p.handle)
+
+
+@pytest.mark.parametrize("nc,m", [(1, 1), (1, 31), (3, 33), (70, 96), (2, 5000)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_host_results_where_the_kernels_write_them(monkeypatch, nc, m, weighted):
+    """Results that the kernels write to pinned memory are those that a plan
+    without it copies from the device."""
+    import paper_1112_1701_amd as bls
+    bls._lib.load()
+    n = 90
+    lcs = [synth.small_curve(70 + k, n, nperiods=m, nbins=60, qmin=0.02, qmax=0.2,
+                             weighted=weighted) for k in range(nc)]
+    t, x = (np.concatenate([getattr(c, a) for c in lcs]) for a in "tx")
+    w = np.concatenate([c.w for c in lcs]) if weighted else None
+    got = []
+    for hook in (None, "pinned"):
+        print("[case] host results", nc, m, weighted, hook, flush=True)
+        monkeypatch.setenv("BLS_DEBUG_FAIL_ALLOC", hook) if hook else None
+        with bls.Plan(max_curves=nc + 1, max_points=nc * n + 9, max_periods=nc * m + 5) as p:
+            for _ in range(2):
+                got.append(bls.bls_search_batch(p.handle, np.arange(nc + 1) * n, t, x, w,
+                                                lcs[0].periods, None, 60, 0.02, 0.2))
+    for g in got[1:]:
+        for key in got[0]:
+            assert np.array_equal(g[key], got[0][key], equal_nan=True), key
