@@ -129,8 +129,7 @@ double time_candidate(bls_plan *p, std::vector<CurveShape> &shapes, bool weighte
   a.kwidth = ks;
   a.best_key = keys;
   a.hist_bytes = pb.hist_bytes;
-  a.scr_bytes = pb.scr_bytes;
-  a.scr_offset = pb.scr_offset;
+  a.block = pb.block ? 1 : 0;
   a.ucap = 0;
   a.uws = nullptr;
   a.uws_stride = 0;

@@ -776,8 +776,6 @@ __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : WEIGHTED ? 5 : 6))) void block_sea
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   constexpr int wpb = WEIGHTED ? 2 : 1;
-  unsigned char *scr =
-      reinterpret_cast<unsigned char *>(s_hist) + a.scr_offset + wave * a.scr_bytes;
   // Items and groups as in search_kernel: thread 0 claims one group ahead and
   // steps through the group's tiles.
   ItemRef nx = {-1, 0, 0};
@@ -870,6 +868,8 @@ __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : WEIGHTED ? 5 : 6))) void block_sea
         fold_tail<WEIGHTED>(a, fd, first, (int)(n - first), np, s_f, s_hist, HS);
       __syncthreads();
       // One wave per period.
+      unsigned char *scr = reinterpret_cast<unsigned char *>(s_hist) + uniform(cd.scr_offset) +
+                           wave * uniform(cd.scr_bytes);
       for (int t = wave; t < np; t += kBlock / 64) {
         u64 *u = s_hist + (size_t)t * HS * wpb;
         PeriodScan<WEIGHTED, DIP> ps(cd, a.min_in_points, u, u + HS, scr);

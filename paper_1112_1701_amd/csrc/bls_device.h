@@ -78,6 +78,11 @@ struct CurveDesc {
   int32_t bmagic;
   // ---- written by the prep kernel: smallest encoded weight of a kept point
   int32_t qwmin;
+  // ---- written by the host planner: block search: where the waves' scratch
+  // begins in dynamic LDS (behind the curve's own planes, so that a launch
+  // needs what its largest curve needs alone), and the bytes of one wave
+  int32_t scr_offset;
+  int32_t scr_bytes;
 };
 
 struct PrepArgs {
@@ -132,11 +137,7 @@ struct SearchArgs {
   // (workgroups are dispatched to the XCDs round-robin, so a partition's
   // curves stay in one XCD's L2); counter[x] counts its items taken.
   int32_t nparts;
-  // block search: the waves' scratch in dynamic LDS, scr_bytes each from
-  // scr_offset on (0 bytes: the launch runs search_kernel)
-  int32_t scr_bytes;
-  int32_t scr_offset;
-  int32_t pad_parts;
+  int32_t block;   // 1: the launch runs block_search_kernel
   int64_t part_begin[kMaxParts + 1];
 };
 
@@ -169,7 +170,6 @@ const void *block_search_fn(bool weighted, bool dip, bool wide);
 // One partition over all items (callers without an XCD split).
 inline void single_partition(SearchArgs &a) {
   a.nparts = 1;
-  a.pad_parts = 0;
   for (int x = 0; x <= kMaxParts; ++x) a.part_begin[x] = x == 0 ? 0 : a.nitems;
 }
 

@@ -1017,7 +1017,7 @@ int launch_prep(const PrepArgs &a, void *stream) {
 
 int launch_search(const SearchArgs &a, bool weighted, bool dip_only, int grid, void *stream) {
   if (a.nitems <= 0) return 0;
-  const void *fn = a.scr_bytes > 0 ? block_search_fn(weighted, dip_only, block_wide(grid))
+  const void *fn = a.block ? block_search_fn(weighted, dip_only, block_wide(grid))
                                    : pick(weighted, dip_only, a.hist_bytes);
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, a.hist_bytes);
   if (e != hipSuccess) return (int)e;

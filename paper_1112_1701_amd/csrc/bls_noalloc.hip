@@ -289,8 +289,7 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   sa.kwidth = o->kwidth;
   sa.best_key = keys;
   sa.hist_bytes = hist_bytes;
-  sa.scr_bytes = lds.scratch;
-  sa.scr_offset = lds.planes;
+  sa.block = block ? 1 : 0;
   sa.ucap = 0;
   single_partition(sa);
   if ((e = (hipError_t)launch_search(sa, weighted, (flags & BLS_DIP_ONLY) != 0, (int)grid,

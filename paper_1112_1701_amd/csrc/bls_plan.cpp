@@ -321,14 +321,19 @@ void fit_block_tile(int nbins, int kmin, int kmax, int64_t nperiods, int lds_bud
   *stride = block_plane_words(nbins, kmax, *g);
 }
 
+void set_block_layout(CurveDesc &d, const BlockGeom &g) {
+  d.bsize = g.bsize;
+  d.nblocks = g.nblocks;
+  d.omin = g.omin;
+  d.omax = g.omax;
+  d.bmagic = g.magic;
+  d.scr_offset = (d.tile * d.hstride * 8 * (d.weighted ? 2 : 1) + 15) & ~15;
+  d.scr_bytes = block_scratch_bytes(d.nbins, g);
+}
+
 void LdsLayout::add(const CurveDesc &d, bool block) {
-  planes = std::max(planes, d.tile * d.hstride * 8 * (d.weighted ? 2 : 1));
-  if (block) {
-    const BlockGeom g{d.bsize, d.nblocks, d.omin, d.omax, d.bmagic};
-    planes = (planes + 15) & ~15;
-    waves = std::max(waves, std::min(d.tile, 4));
-    scratch = std::max(scratch, block_scratch_bytes(d.nbins, g));
-  }
+  bytes = std::max(bytes, block ? d.scr_offset + std::min(d.tile, 4) * d.scr_bytes
+                                : d.tile * d.hstride * 8 * (d.weighted ? 2 : 1));
 }
 
 void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
@@ -350,20 +355,15 @@ void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
   // bins, then the clamp word / wrap-around copy, per period and plane,
   // padded against LDS bank conflicts, as the kernel lays them out
   int T = 1, hs = 0;
-  if (block) {
-    BlockGeom g;
+  BlockGeom g;
+  if (block)
     fit_block_tile(s.nbins, s.kmin, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T,
                    &hs, &g);
-    d.bsize = g.bsize;
-    d.nblocks = g.nblocks;
-    d.omin = g.omin;
-    d.omax = g.omax;
-    d.bmagic = g.magic;
-  } else {
+  else
     fit_tile(s.nbins, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T, &hs, memo);
-  }
   d.tile = T;
   d.hstride = hs;
+  if (block) set_block_layout(d, g);
 }
 
 int validate_batch_into(const bls_plan_config &cfg, const bls_batch &b, bool check_data,
@@ -639,8 +639,7 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
   layout_partitions(p, item_cost, items_of, out);
   const int64_t items = out.nitems;
   out.hist_bytes = hist_bytes;
-  out.scr_bytes = lds.scratch;
-  out.scr_offset = lds.planes;
+  out.block = block;
 
   int per_cu = 0;
   hipError_t e = (hipError_t)search_blocks_per_cu(weighted, (p->cfg.flags & BLS_DIP_ONLY) != 0, block,
@@ -749,8 +748,7 @@ int enqueue_kernel(bls_plan *p, const PlannedBatch &pb, const double *periods, f
   sa.kwidth = ks;
   sa.best_key = reinterpret_cast<unsigned long long *>(best);
   sa.hist_bytes = pb.hist_bytes;
-  sa.scr_bytes = pb.scr_bytes;
-  sa.scr_offset = pb.scr_offset;
+  sa.block = pb.block ? 1 : 0;
   sa.ucap = pb.ucap;
   sa.uws = pb.uws;
   sa.uws_stride = pb.uws_stride;
@@ -759,7 +757,6 @@ int enqueue_kernel(bls_plan *p, const PlannedBatch &pb, const double *periods, f
   if (const char *fm = getenv("BLS_FOLD_MERGE")) sa.fold_policy = atoi(fm) == 1 ? 1 : 2;
   if (const char *su = getenv("BLS_SEED_UNIT")) sa.seed_unit = atoi(su) != 0 ? 1 : 0;
   sa.nparts = pb.nparts;
-  sa.pad_parts = 0;
   for (int x = 0; x <= kMaxParts; ++x) sa.part_begin[x] = pb.part_begin[x];
   const bool dip = (p->cfg.flags & BLS_DIP_ONLY) != 0;
   hipError_t e = unbinned ? (hipError_t)launch_unbinned(sa, pb.weighted, dip, pb.grid, p->stream)

@@ -30,8 +30,7 @@ struct PlannedBatch {
   int64_t nitems = 0;
   int32_t nseg = 0;
   int32_t hist_bytes = 0;  // dynamic LDS of a workgroup
-  int32_t scr_bytes = 0;   // block search: scratch per wave (0: search_kernel)
-  int32_t scr_offset = 0;
+  bool block = false;      // block_search_kernel
   int32_t grid = 0;
   double trial_points = 0.0;
   double box_evals = 0.0;
@@ -182,12 +181,15 @@ constexpr int kBlockStaticLds = 1536;  // static LDS of block_search_kernel, rou
 // one), its plane stride and geometry.
 void fit_block_tile(int nbins, int kmin, int kmax, int64_t nperiods, int lds_budget, int tile_cap,
                     bool weighted, int *tile, int *stride, BlockGeom *g);
-// LDS layout of a launch, extended by one curve at a time: dynamic LDS bytes
-// and, for the block search, the waves' scratch behind the planes.
+// Block search: a curve's geometry and the place of the waves' scratch into
+// its descriptor (tile, stride, bins and weighted are set).
+void set_block_layout(CurveDesc &d, const BlockGeom &g);
+// Dynamic LDS of a launch, extended by one curve at a time: the most that any
+// of its curves needs.
 struct LdsLayout {
-  int planes = 0, scratch = 0, waves = 0;
+  int bytes = 0;
   void add(const CurveDesc &d, bool block);
-  int total() const { return planes + waves * scratch; }
+  int total() const { return bytes; }
 };
 // LDS of a block-search tile of T periods: its planes, and scratch for the
 // waves that have a period.

@@ -206,15 +206,11 @@ hipError_t start_request(bls_server *s, Req *r) {
   d.kmax = r->kmax;
   d.tile = r->tile;
   d.hstride = r->hstride;
-  d.bsize = r->geom.bsize;
-  d.nblocks = r->geom.nblocks;
-  d.omin = r->geom.omin;
-  d.omax = r->geom.omax;
-  d.bmagic = r->geom.magic;
+  d.weighted = r->weighted ? 1 : 0;
+  if (r->block) set_block_layout(d, r->geom);
   const int cb = cbits_of(r->n);
   d.shift = 64 - cb;
   d.qbits = std::min(kQBitsMax, 63 - 2 * cb);
-  d.weighted = r->weighted ? 1 : 0;
   d.check_periods = 0;  // checked on the host at submit
   hipStream_t st = s->up_stream;
   hipError_t e;
@@ -275,8 +271,7 @@ hipError_t launch_kind(bls_server *s, int b, int kind, int s0, int sbase, int n,
   a.kwidth = s->d_ks;
   a.best_key = s->d_keys;
   a.hist_bytes = lds.total();
-  a.scr_bytes = lds.scratch;
-  a.scr_offset = lds.planes;
+  a.block = block ? 1 : 0;
   single_partition(a);
   const bool dip = (s->cfg.flags & BLS_DIP_ONLY) != 0;
   int per_cu = 1;
