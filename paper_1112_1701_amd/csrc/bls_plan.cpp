@@ -587,6 +587,9 @@ int item_group(const bls_plan *p, const std::vector<CurveShape> &shapes) {
 int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted,
                const TileChoice &tc, PlannedBatch &out) {
   const int nc = (int)shapes.size();
+  // The descriptors and the places of the segments change from here on, also
+  // where planning fails: the last search's plan goes stale.
+  p->replay_valid = false;
   // queued copies may still read the pinned descriptors
   const int ws = desc_wait(p);
   if (ws != BLS_OK) return ws;
@@ -1023,7 +1026,6 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
   PlannedBatch pb;
   st = plan_batch(p, shapes, weighted, tc, pb);
   if (st != BLS_OK) return st;
-  p->replay_valid = false;  // descriptors were rewritten
 
   const int64_t npts = b.n_off[b.ncurves];
   const int64_t nper = b.p_off ? b.p_off[b.ncurves] : b.nperiods_shared;
@@ -1345,7 +1347,6 @@ int bls_search_device(bls_plan *p, const bls_batch *b, const bls_device_results 
   std::string err;
   int st = validate_batch(p->cfg, *b, false, p->shapes, err);
   if (st != BLS_OK) return set_error(p, st, err);
-  p->replay_valid = false;
   const bool weighted = b->weights != nullptr;
   TileChoice tc = choose_tiles(p, p->shapes, weighted);
   PlannedBatch pb;

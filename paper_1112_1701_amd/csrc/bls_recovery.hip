@@ -157,7 +157,6 @@ extern "C" int bls_injection_recovery_device(bls_plan *p, const bls_recovery_con
   PlannedBatch pb;
   st = plan_batch(p, p->shapes, weighted, tc, pb);
   if (st != BLS_OK) return st;
-  p->replay_valid = false;  // descriptors were rewritten
   st = ensure_recovery_buffers(p);
   if (st != BLS_OK) return st;
 
