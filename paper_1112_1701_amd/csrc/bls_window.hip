@@ -216,6 +216,15 @@ __device__ __forceinline__ int window_period(const int2 *row, int nb, int k) {
   return wave_isum(cnt);
 }
 
+// trunc(x) as v_cvt_i32_f64 gives it, saturated where it is no int (the
+// language leaves that conversion undefined; a clamp in FP64 before it would
+// cost an operation per point and period).
+__device__ __forceinline__ int saturated_int(double x) {
+  int r;
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(x));
+  return r;
+}
+
 // One kept time in its bin: the cycle numbers' extremes (clamped at kMaxCycle,
 // which the period's set-up has flagged: the largest d f of the cadence is its
 // last kept time's).
@@ -223,7 +232,7 @@ __device__ __forceinline__ void fold_cycle(double d, double f, double nbd, unsig
                                            int2 *row) {
   const double cyc = d * f;  // not negative: the conversion is the floor
   const int b = (int)min((unsigned)(int)(__builtin_amdgcn_fract(cyc) * nbd), nbm1);
-  const int e = min((int)cyc, kMaxCycle);
+  const int e = min(saturated_int(cyc), kMaxCycle);
   int *w2 = reinterpret_cast<int *>(row + b);
   atomicMin(w2, e);
   atomicMax(w2 + 1, e);
