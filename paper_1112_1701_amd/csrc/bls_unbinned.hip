@@ -55,6 +55,13 @@ constexpr int kUnbPad = 16;
 // Ranks per small block of run starts or ends.
 constexpr int kUnbSub = 4;
 
+// Where the screens' threshold starts: below the value of any run that holds a
+// signal (|S| >= 1 and R (W - R) < 2^102 in the integers' units), so that runs
+// without one never pass, and its product with any R (W - R) is a normal float.
+// From 0 all of them would: 20000 points of one flux took 124 ms for 64 periods
+// (0.4 ms so; curves with a signal the same).
+constexpr float kUnbThetaMin = 0x1p-110f;
+
 // Bounds as floats, wide enough for the float arithmetic on them: sums and
 // differences of a few such values and of cycle totals up to t.
 __device__ inline float at_least(double v, float t) {
@@ -177,7 +184,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void unbinned_kernel(SearchArgs a) {
     for (int i = tid; i <= M; i += kBlock) cnt[i] = 0;
     if (tid == 0) {
       s_vbits = 0ull;
-      s_theta = 0u;
+      s_theta = __float_as_uint(kUnbThetaMin);
       s_tie = 0xFFFFFFFFu;
     }
     __syncthreads();
@@ -489,7 +496,7 @@ __attribute__((amdgpu_waves_per_eu(4))) void unbinned_kernel(SearchArgs a) {
     // R (W - R) can be neither the best nor a tie of it.
     double bnum = 0.0, bden = 1.0;
     unsigned int btie = 0xFFFFFFFFu;
-    float thr = 0.0f;
+    float thr = kUnbThetaMin;
     bool raised = false;  // thr since the last publish()
     auto reload_theta = [&]() {  // (any value read is one some run reached)
       const unsigned tb =

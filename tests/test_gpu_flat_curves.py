@@ -1,0 +1,54 @@
+"""Curves without a signal (one flux throughout, a filled or saturated star):
+no box or run of them has a value, and the searches' screens see that.  Their
+kernels take no longer than on noise, within a factor that no screen passing
+everything stays below."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def bls():
+    import paper_1112_1701_amd as bls
+    bls._lib.load()
+    return bls
+
+
+def _flux(kind, rng, n):
+    """(flux, weights): noise, one flux (its mean exact or not), with weights."""
+    x = rng.normal(0.0, 1.0, n) if kind[0] == "noise" else np.full(n, kind[0])
+    return x, 10.0 ** rng.uniform(-1.0, 1.0, n) if kind[1] else None
+
+
+# (a flux whose mean is not exact leaves a remainder of one sign: no dips)
+@pytest.mark.parametrize("kind,flags", [((1.0, False), 0), ((1.0, True), 0), ((0.1, False), 1),
+                                        ((0.1, True), 1)])
+@pytest.mark.parametrize("n,m", [(1000, 2000), (5000, 400), (40000, 32)])
+def test_unbinned(bls, kind, flags, n, m):
+    import torch
+    dev = lambda a: None if a is None else torch.tensor(a, device="cuda:0")
+    print("[case] flat unbinned", kind, flags, n, m, flush=True)
+    rng = np.random.default_rng(n)
+    t = dev(np.sort(rng.uniform(0.0, 60.0, n)))
+    per = dev(synth.log_period_grid(0.3, 9.0, m))
+    out = [torch.empty(m, device="cuda:0", dtype=d) for d in (
+        torch.float32, torch.float32, torch.int32, torch.int32)]
+    best = torch.empty(1, device="cuda:0", dtype=torch.int64)
+    ms = []
+    for k in (("noise", kind[1]), kind):
+        x, w = _flux(k, rng, n)
+        x, w = dev(x), dev(w)
+        torch.cuda.synchronize()
+        with bls.Plan(max_points=n, max_periods=m, flags=flags) as p:
+            for _ in range(4):
+                bls.bls_search_unbinned_device(p.handle, np.array([0, n]), t, x, w, per, None,
+                                               0.01, 0.1, *out, best)
+                bls.bls_synchronize(p.handle)
+            ms.append(min(bls.bls_kernel_times(p.handle)))
+    print("[ms] noise, flat:", ms, flush=True)
+    if kind[0] == 1.0 and not kind[1]:      # the mean is exact
+        assert (out[0].cpu().numpy() == 0.0).all() and (out[2].cpu().numpy() == -1).all()
+    assert ms[1] <= 2.0 * ms[0], ms
