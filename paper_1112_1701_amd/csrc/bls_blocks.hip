@@ -38,6 +38,17 @@ namespace {
 
 typedef unsigned long long u64;
 
+// Prunings of the candidate list after which a sweep is left (on noise it is
+// pruned once at its end), and the error of a difference of two prefix words'
+// weights, in quanta.
+constexpr int kMaxPrunes = 8;
+constexpr float kWordError = 3.0f;
+// Theta where no box is known to be valid: below the value of any that holds a
+// signal (its bound is at least 2^-20, R (W - R) below 2^62).  With 0 there
+// the boxes that cannot be dips (a bound of 0) would pass the screens.
+constexpr float kThetaMin = 0x1p-110f;
+constexpr int kEvery = -2;  // PeriodScan::best: left to every_start
+
 // LDS operations of one wave complete in order; this keeps the compiler from
 // moving them across.
 __device__ __forceinline__ void wave_sync() {
@@ -132,12 +143,14 @@ struct PeriodScan {
   float E;       // error of a signal difference, all roundings (quanta)
   float c0, eR;  // weighted: absolute and relative error of a weight difference
   float Ws, es;  // screens: R (Ws - R) (1 - es) is at most what a box may give
-  float wlo;     // least weight of a valid box
+                 // whose weight is at least R
+  float wlo;     // least weight of a valid box (positive)
   float theta, thr;  // largest lower value of a valid box; the same, relaxed
   float thrs, tW;    // the screens' threshold, and times Ws
   int qn;            // queued block pairs
   int ncand;         // candidates
-  bool over;         // some were dropped: more than the list holds
+  int prunes;        // times the list was pruned in this sweep; kMaxPrunes: the
+                     // sweep is left, for more candidates than that resolves
 
   __device__ __forceinline__ PeriodScan(const CurveDesc &d, int mip, u64 *u, u64 *v,
                                         unsigned char *scr)
@@ -325,9 +338,9 @@ struct PeriodScan {
     E = uniform(8.0f + (wave_fmax(rhi) + wave_fmax(rlo)) * ((float)(2 * kmax + 16) * 0x1.01p-24f));
     c0 = WEIGHTED ? uniform(3.0f + Wt * 0x1p-22f) : 0.0f;
     eR = uniform((float)(kmax + 8) * 0x1p-24f);
-    wlo = WEIGHTED ? uniform(max_raw(mipf * (float)(qwmin >> x), 1.0f)) : mipf;
-    // Least weight of kmin consecutive bins from each block's starts.
-    int heavy = 0x7fffffff;
+    wlo = WEIGHTED ? uniform(max_raw(mipf * (float)qwmin, 1.0f) * ldexpf(1.0f, -x)) : mipf;
+    // Least weight of kmin consecutive bins from each block's starts (weights:
+    // two quanta less, the floors of both prefixes).
     for (int a = lane; a < NB; a += 64) {
       int least = 0x7fffffff, m = 0;
       const u64 *u = U + a * s;
@@ -336,27 +349,37 @@ struct PeriodScan {
         narrowest<3>(u + m, least);
       else
         narrowest<1>(u + m, least);
-      tab2[a].y = (float)least;
-      heavy = min(heavy, least);
+      tab2[a].y = (float)(WEIGHTED ? least - 2 : least);
     }
-    // The screens take R (W - R) from prefix weights: an error of er = R eR +
-    // c0 each in R and in W - R, the former relative to the least R.
+    // The screens take R and W - R at their least: R less its absolute error
+    // where it comes from prefix weights (c0 from the blocks' table, two quanta
+    // from the words), W - R with Ws for W; then the rounding of the running
+    // weight, which is relative.
     Ws = Wt;
     if (WEIGHTED) {
-      const unsigned most = 0x7fffffffu;
-      const float least = (float)(most - wave_umax(most - (unsigned)max(heavy, 0)));
       Ws = uniform(Wt - 2.0f * (Wt * eR + c0));
-      es = uniform(2.0f * (eR + c0 * __builtin_amdgcn_rcpf(max_raw(wlo, least))));
+      es = uniform(2.0f * eR);
     }
     wave_sync();
   }
-  // Least and largest R (W - R) that the FP32 sums of a box may give.
-  __device__ __forceinline__ void denominators(float R, float &den_lo, float &den_hi) const {
+  // Whether no bin holds a signal (a constant curve): no box has a value then.
+  __device__ __forceinline__ bool flat() const {
+    bool any = false;
+    for (int i = lane; i < nb; i += 64)
+      any |= WEIGHTED ? V[i + 1] != V[i] : ((U[i + 1] - U[i]) << (32 - sh)) != 0ull;
+    return __builtin_amdgcn_ballot_w64(any) == 0ull;
+  }
+  // Least and largest R (W - R) that the FP32 sums of a valid box may give (c:
+  // the absolute error of R; that of W - R is c0, by the rounding of W).
+  __device__ __forceinline__ void denominators(float R, float c, float &den_lo,
+                                               float &den_hi) const {
     const float d = Wt - R;
     if (WEIGHTED) {
-      const float er = fmaf(R, eR, c0);
-      den_lo = max_raw(R - er, 0.0f) * max_raw(d - er, 0.0f);
-      den_hi = (R + er) * (d + er);
+      const float er = fmaf(R, eR, c), ed = fmaf(R, eR, c0);
+      // (points of encoded weight 0 do not make a box valid)
+      const float least = qwmin > 0 ? wlo * (1.0f - 0x1p-12f) : 0.0f;
+      den_lo = max_raw(R - er, least) * max_raw(d - ed, 0.0f);
+      den_hi = (R + er) * (d + ed);
     } else {
       den_lo = den_hi = R * d;
     }
@@ -366,7 +389,7 @@ struct PeriodScan {
   // curves with a minimum count: cnt is its count).
   __device__ __forceinline__ float lower(float S, float R, int cnt) const {
     float lo, hi;
-    denominators(R, lo, hi);
+    denominators(R, kWordError, lo, hi);
     const float sl = (DIP ? -S : fabsf(S)) - E;
     bool ok = sl > 0.0f;
     if (WEIGHTED)
@@ -386,9 +409,7 @@ struct PeriodScan {
   __device__ __forceinline__ void raise(float t) {
     theta = uniform(t);
     thr = uniform(t * (1.0f - 0x1p-17f));
-    // (es can reach 1 where single points weigh next to nothing: then the
-    // screens pass everything)
-    thrs = WEIGHTED ? uniform(thr * max_raw(1.0f - es, 0.0f)) : thr;
+    thrs = WEIGHTED ? uniform(thr * (1.0f - es)) : thr;
     tW = uniform(thrs * Ws);
   }
 
@@ -415,7 +436,7 @@ struct PeriodScan {
         const float S = t.z - t0.z;
         const float sl = max_raw((DIP ? -S : fabsf(S)) - E, 0.0f);
         float lo, hi;
-        denominators(R, lo, hi);
+        denominators(R, c0, lo, hi);
         const float v = sl * sl * __builtin_amdgcn_rcpf(hi);
         bool ok = v > bv;
         if (WEIGHTED) {
@@ -441,7 +462,7 @@ struct PeriodScan {
       if (j >= 0 && j < nb && k >= kmin && k <= kmax) v = lower_at(j, j + k);
       t = max_raw(t, wave_fmax(v));
     }
-    raise(t);
+    raise(max_raw(t, kThetaMin));
   }
 
   // K boxes from start j (ends e0 + i on; len boxes in all), scored against
@@ -484,10 +505,9 @@ struct PeriodScan {
         if (ncand > kBlockCand / 2) {
           wave_sync();
           prune();
-          if (ncand > kBlockCand / 2) {  // more ties than the list holds
-            over = true;
-            ncand = kBlockCand / 2;
-          }
+          prunes += ncand > kBlockCand / 2 ? kMaxPrunes : 1;
+          ncand = min(ncand, kBlockCand / 2);
+          qn = prunes >= kMaxPrunes ? 0 : qn;  // (ends the loop over the queue)
         }
       }
     }
@@ -516,7 +536,7 @@ struct PeriodScan {
       // on, which is narrower and so preferred, unless it is of least width.
       if (!MARK && points(high(u1), h0) == 0) e2 = min(e2, j + kmin);
       const int len = in ? e2 - e1 + 1 : 0;
-      const int l0 = low(u0), s0 = WEIGHTED ? low(V[j]) : l0;
+      const int l0 = low(u0) + 2, s0 = WEIGHTED ? low(V[j]) : low(u0);
       const int e0 = len > 0 ? e1 : j;  // (lanes without boxes read in range)
       int i = 0;
       for (; i + 4 <= s; i += 4) boxes<4, MARK>(i, e0, j, len, h0, l0, s0);
@@ -539,8 +559,12 @@ struct PeriodScan {
     for (int r = 0; r < NB; r += 64) {
       const u64 live = NB - r >= 64 ? ~0ull : (1ull << (NB - r)) - 1ull;
       const int a = min(r + lane, NB - 1);
-      const float4 t0 = tab[a];
-      const float2 u0 = tab2[a];
+      float4 t0 = tab[a];
+      float2 u0 = tab2[a];
+      if (WEIGHTED) {
+        t0.w -= c0;
+        u0.x += c0;
+      }
       const float4 *tp = tab + a + omin;
       float4 t = tp[0], tn = tp[1];
       for (int o = omin; o <= omax; ++o) {
@@ -560,7 +584,13 @@ struct PeriodScan {
           if (__builtin_amdgcn_inverse_ballot_w64(m))
             queue[qn + lanes_below(m)] = (unsigned short)(a | (o << 8));
           qn += (int)__popcll(m);
-          if (qn >= 64) drain<MARK>();
+          if (qn >= 64) {
+            drain<MARK>();
+            if (!MARK) {  // (a return here would cost 25 to 40 spilled SGPRs)
+              o = prunes >= kMaxPrunes ? omax : o;
+              r = prunes >= kMaxPrunes ? NB : r;
+            }
+          }
         }
       }
     }
@@ -644,6 +674,56 @@ struct PeriodScan {
     }
     return max(key, bm < 0 ? 0ull : key_of(bn, bd, bm + 1, j));
   }
+  // Every width from every start bin, a lane each, by the same sums, tests and
+  // order as exact_start: where that has too many starts to take one by one.
+  __device__ __forceinline__ int every_start() const {
+    u64 key = 0ull;
+    for (int r = 0; r < nb; r += 64) {
+      const int j = min(r + lane, nb - 1);
+      const int sq = (j * 32 + nb - 1) / nb;
+      const bool seeded = sq < 32 && sq * nb / 32 == j;
+      float S = 0.0f, R = 0.0f, bn = 0.0f, bd = 1.0f;
+      int bm = -1, C = 0;
+#pragma unroll 1
+      for (int m = 0; m < kmax; ++m) {
+        int c;
+        const float2 e = bin(j + m, qscale, c);
+        S += e.y;
+        C += c;
+        if (WEIGHTED)
+          R += e.x;
+        else
+          R = (float)C;
+        if (m + 1 < kmin) continue;
+        const float d = Wf - R;
+        const float num = S * S, den = R * d;
+        bool ok = num * bd > bn * den;
+        if (WEIGHTED)
+          ok = ok & (den > 0.0f) & ((float)C <= nf - 1.0f) & ((float)C >= mipf);
+        else
+          ok = ok & (d >= 1.0f) & (mip1 | (R >= mipf));
+        if (DIP) ok = ok & (S < 0.0f);
+        if (ok) {
+          bn = num;
+          bd = den;
+          bm = m;
+          if (m + 1 == kmin && seeded) key = max(key, key_of(num, den, kmin, j));
+        }
+      }
+      if (bm >= 0) key = max(key, key_of(bn, bd, bm + 1, j));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) key = max(key, (u64)__shfl_xor(key, o, 64));
+    return box_of(lane_u64(key, 0));
+  }
+  // The box of a key: j | k << 16, or -1.
+  __device__ __forceinline__ int box_of(u64 key) const {
+    if (key == 0ull) return -1;
+    const unsigned idx = 0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull);
+    const int k = (int)(idx / (unsigned)nb);
+    const int j = (int)(idx - (unsigned)k * (unsigned)nb);
+    return j | (k << 16);
+  }
   // Key of a box: its value, then the smaller width and start.
   __device__ __forceinline__ u64 key_of(float bn, float bd, int k, int j) const {
     const float v = bn * __builtin_amdgcn_rcpf(bd);
@@ -675,7 +755,7 @@ struct PeriodScan {
         if (n > 64 && pass == 0) continue;
         if (pass == 0) raise(max_raw(theta, wave_fmax(top)));
         float lo, hi;
-        denominators(max_raw(R, wlo), lo, hi);
+        denominators(max_raw(R, wlo), kWordError, lo, hi);
         const float su = DIP ? max_raw(E - S, 0.0f) : E + fabsf(S);
         const bool last_empty = points(high(u1), high(ul) - half) == 0;
         const bool same_before = (j > 0) & (points(high(u0), high(U[max(j - 1, 0)]) - half) == 0);
@@ -694,30 +774,39 @@ struct PeriodScan {
     return jkept;
   }
 
-  // Best box of the period: j | k << 16, or -1.
+  // Best box of the period: j | k << 16, -1 if there is none, kEvery where
+  // every_start has to find it.
   __device__ __forceinline__ int best() {
     prefix();
     seed();
-    for (int tries = 0; tries < 3; ++tries) {
+    if (!(theta > kThetaMin) && flat()) return -1;
+    // A sweep that is left for its many candidates is taken once more if theta
+    // has risen since its start (a seed of little value); where it has not,
+    // boxes in question are the rule.
+    float before;
+    int tries = 0;
+    do {
+      before = theta;
       ncand = 0;
-      over = false;
+      prunes = 0;
       sweep<false>();
-      if (!over) {
-        // With every candidate at hand, a single box not below theta is the
-        // best.
-        if (ncand == 0) return -1;
-        int jk = cand[0];
-        if (ncand > 1 || !(theta > 0.0f)) jk = prune();
-        if (ncand == 1 && theta > 0.0f) return jk;
-        break;
-      }
-      prune();
-    }
+    } while (prunes >= kMaxPrunes && ++tries < 2 && theta > 1.1f * before);
+    if (prunes >= kMaxPrunes) return kEvery;
+    // With every candidate at hand, a single box not below theta is the best.
+    if (ncand == 0) return -1;
+    int jk = cand[0];
+    if (ncand > 1 || !(theta > kThetaMin)) jk = prune();
+    if (ncand == 0) return -1;
+    if (ncand == 1 && theta > kThetaMin) return jk;
     // Boxes within the error of each other: all of them once more, their
-    // start bins marked, and those starts by the definition's running sums.
+    // start bins marked, and those starts by the definition's running sums
+    // (about 3 kmax + 100 instructions a start; 30 kmax for 64 at a time).
     for (int i = lane; i < (nb + 31) / 32; i += 64) marks[i] = 0u;
     wave_sync();
     sweep<true>();
+    int starts = 0;
+    for (int i = lane; i < (nb + 31) / 32; i += 64) starts += (int)__popc(marks[i]);
+    if (wave_isum(starts) * (3 * kmax + 100) > (nb + 63) / 64 * 30 * kmax) return kEvery;
     u64 key = 0ull;
     for (int i = 0; i < (nb + 31) / 32; ++i) {
       unsigned word = (unsigned)__builtin_amdgcn_readfirstlane((int)marks[i]);
@@ -728,11 +817,7 @@ struct PeriodScan {
         key = k > key ? k : key;
       }
     }
-    if (key == 0ull) return -1;
-    const unsigned idx = 0xFFFFFFFFu - (unsigned)(key & 0xFFFFFFFFull);
-    const int k = (int)(idx / (unsigned)nb);
-    const int j = (int)(idx - (unsigned)k * (unsigned)nb);
-    return j | (k << 16);
+    return box_of(key);
   }
 
   // The box's sums in FP64 from its FP32 bins (every lane's result).
@@ -873,7 +958,14 @@ __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : WEIGHTED ? 5 : 6))) void block_sea
       for (int t = wave; t < np; t += kBlock / 64) {
         u64 *u = s_hist + (size_t)t * HS * wpb;
         PeriodScan<WEIGHTED, DIP> ps(cd, a.min_in_points, u, u + HS, scr);
-        const int jk = __builtin_amdgcn_readfirstlane(ps.best());
+        int jk = __builtin_amdgcn_readfirstlane(ps.best());
+        if (jk == kEvery) {
+          // (the curve's record is read again: what only this needs of it
+          // occupies no registers through the search)
+          wave_sync();
+          const PeriodScan<WEIGHTED, DIP> es(cd, a.min_in_points, u, u + HS, scr);
+          jk = __builtin_amdgcn_readfirstlane(es.every_start());
+        }
         double Rs = 0.0, Ss = 0.0;
         if (jk >= 0) ps.sums(jk, Rs, Ss);
         if ((tid & 63) == 0) {

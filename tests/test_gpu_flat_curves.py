@@ -52,3 +52,47 @@ def test_unbinned(bls, kind, flags, n, m):
     if kind[0] == 1.0 and not kind[1]:      # the mean is exact
         assert (out[0].cpu().numpy() == 0.0).all() and (out[2].cpu().numpy() == -1).all()
     assert ms[1] <= 2.0 * ms[0], ms
+
+
+# The block search against the kernel that scores every box: no signal, one
+# sign under BLS_DIP_ONLY, weights of any range, a minimum count that no box
+# reaches (every box is then in question, or none).
+@pytest.mark.parametrize("kind,flags,mip", [
+    ("one", 0, 1), ("tenth", 1, 1), ("one, weights", 0, 1), ("tenth, weights", 1, 1),
+    ("errors over 10", 0, 1), ("errors over 1000", 0, 1), ("errors over 1000", 1, 3),
+    ("noise", 0, 100), ("two values", 0, 1)])
+@pytest.mark.parametrize("n,m,nbins,qmin,qmax", [(300, 4000, 300, 0.01, 0.1),
+                                                 (1000, 4000, 525, 0.005, 0.06),
+                                                 (5000, 2000, 1000, 0.005, 0.05)])
+def test_blocks(bls, monkeypatch, kind, flags, mip, n, m, nbins, qmin, qmax):
+    print("[case] flat blocks", kind, flags, mip, n, nbins, flush=True)
+    nc = 8
+    rng = np.random.default_rng(n)
+    t = np.sort(rng.uniform(0.0, 60.0, (nc, n)), axis=1)
+    x, w = rng.normal(0.0, 1.0, (nc, n)), None
+    if kind.startswith("errors"):
+        s = np.log10(float(kind.split()[-1]))
+        w = 10.0 ** rng.uniform(-s, s, (nc, n))      # weights: errors to the -2
+        x /= np.sqrt(w)
+    elif kind == "two values":
+        x = (x > 1.0) * 1.0
+    elif kind != "noise":
+        x[:] = 1.0 if kind.startswith("one") else 0.1
+        if kind.endswith("weights"):
+            w = 10.0 ** rng.uniform(-1.0, 1.0, (nc, n))
+    per = synth.log_period_grid(0.2, 10.0, m)
+    got, ms = [], []
+    for mode in ("0", "1"):
+        monkeypatch.setenv("BLS_BLOCK_SEARCH", mode)
+        with bls.Plan(max_curves=nc, max_points=nc * n, max_periods=nc * m, flags=flags,
+                      min_in_points=mip) as p:
+            for _ in range(4):
+                r = bls.bls_search_batch(p.handle, np.arange(nc + 1) * n, t.ravel(), x.ravel(),
+                                         None if w is None else w.ravel(), per, None, nbins,
+                                         qmin, qmax)
+            got.append(r)
+            ms.append(min(bls.bls_kernel_times(p.handle)))
+    print("[ms] every box, blocks:", ms, flush=True)
+    for key in got[0]:
+        assert np.array_equal(got[0][key], got[1][key], equal_nan=True), key
+    assert ms[1] <= 4.0 * ms[0], ms
