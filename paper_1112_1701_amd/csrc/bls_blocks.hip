@@ -47,7 +47,7 @@ constexpr float kWordError = 3.0f;
 // signal (its bound is at least 2^-20, R (W - R) below 2^62).  With 0 there
 // the boxes that cannot be dips (a bound of 0) would pass the screens.
 constexpr float kThetaMin = 0x1p-110f;
-constexpr int kEvery = -2;  // PeriodScan::best: left to every_start
+constexpr int kMarked = -2;  // PeriodScan::best: left to marked_starts
 
 // LDS operations of one wave complete in order; this keeps the compiler from
 // moving them across.
@@ -674,12 +674,27 @@ struct PeriodScan {
     }
     return max(key, bm < 0 ? 0ull : key_of(bn, bd, bm + 1, j));
   }
-  // Every width from every start bin, a lane each, by the same sums, tests and
-  // order as exact_start: where that has too many starts to take one by one.
-  __device__ __forceinline__ int every_start() const {
+  // Every width from the marked start bins, a lane each, by the same sums, tests
+  // and order as exact_start: where there are too many to take one by one.
+  __device__ __forceinline__ int marked_starts() const {
     u64 key = 0ull;
-    for (int r = 0; r < nb; r += 64) {
-      const int j = min(r + lane, nb - 1);
+    int n = 0;  // marked starts in hand (cand)
+    for (int base = 0; base < nb || n > 0; base += 64) {
+      if (base < nb) {
+        const bool in = base + lane < nb && ((marks[(base + lane) >> 5] >> (lane & 31)) & 1u) != 0u;
+        const u64 m = __builtin_amdgcn_ballot_w64(in);
+        if (in) cand[n + lanes_below(m)] = base + lane;
+        n += (int)__popcll(m);
+        wave_sync();
+        if (n < 64 && base + 64 < nb) continue;
+        if (n == 0) break;
+      }
+      const int j = cand[min(lane, n - 1)];  // (the last one again where there are fewer)
+      const int left = cand[min(64 + lane, kBlockCand - 1)];
+      n = max(n - 64, 0);
+      wave_sync();
+      cand[lane] = left;
+      wave_sync();
       const int sq = (j * 32 + nb - 1) / nb;
       const bool seeded = sq < 32 && sq * nb / 32 == j;
       float S = 0.0f, R = 0.0f, bn = 0.0f, bd = 1.0f;
@@ -774,8 +789,23 @@ struct PeriodScan {
     return jkept;
   }
 
-  // Best box of the period: j | k << 16, -1 if there is none, kEvery where
-  // every_start has to find it.
+  // Of a pruned list, without the boxes of least width that run past the end of
+  // the cycle and hold the same points as the one from bin 0 (the first point
+  // is always there): how many are left, and the last of them.
+  __device__ __forceinline__ int distinct(int &jk) const {
+    const bool in = lane < ncand;
+    const int c = cand[in ? lane : 0];
+    const int j = c & 0xFFFF, k = c >> 16, e = j + k;
+    const int other = points(high(U[nb]), high(U[j]) - half) +
+                      points(high(U[kmin]), high(U[min(max(e - nb, 0), kmin)]) - half);
+    const u64 m =
+        __builtin_amdgcn_ballot_w64(in & !((e > nb) & (k == kmin) & (other == 0)));
+    if (m != 0ull) jk = __builtin_amdgcn_readlane(c, 63 - (int)__builtin_clzll(m));
+    return (int)__popcll(m);
+  }
+
+  // Best box of the period: j | k << 16, -1 if there is none, kMarked where
+  // marked_starts has to find it.
   __device__ __forceinline__ int best() {
     prefix();
     seed();
@@ -791,22 +821,26 @@ struct PeriodScan {
       prunes = 0;
       sweep<false>();
     } while (prunes >= kMaxPrunes && ++tries < 2 && theta > 1.1f * before);
-    if (prunes >= kMaxPrunes) return kEvery;
+    if (prunes >= kMaxPrunes) {
+      for (int i = lane; i < (nb + 31) / 32; i += 64) marks[i] = ~0u;
+      return kMarked;
+    }
     // With every candidate at hand, a single box not below theta is the best.
     if (ncand == 0) return -1;
     int jk = cand[0];
     if (ncand > 1 || !(theta > kThetaMin)) jk = prune();
     if (ncand == 0) return -1;
-    if (ncand == 1 && theta > kThetaMin) return jk;
+    if (theta > kThetaMin && (ncand == 1 || distinct(jk) == 1)) return jk;
     // Boxes within the error of each other: all of them once more, their
     // start bins marked, and those starts by the definition's running sums
-    // (about 3 kmax + 100 instructions a start; 30 kmax for 64 at a time).
+    // (about 3 kmax + 100 instructions a start, 35 kmax for 64 at a time).
     for (int i = lane; i < (nb + 31) / 32; i += 64) marks[i] = 0u;
     wave_sync();
     sweep<true>();
     int starts = 0;
     for (int i = lane; i < (nb + 31) / 32; i += 64) starts += (int)__popc(marks[i]);
-    if (wave_isum(starts) * (3 * kmax + 100) > (nb + 63) / 64 * 30 * kmax) return kEvery;
+    starts = wave_isum(starts);
+    if (starts * (3 * kmax + 100) > (starts + 63) / 64 * 35 * kmax) return kMarked;
     u64 key = 0ull;
     for (int i = 0; i < (nb + 31) / 32; ++i) {
       unsigned word = (unsigned)__builtin_amdgcn_readfirstlane((int)marks[i]);
@@ -959,12 +993,12 @@ __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : WEIGHTED ? 5 : 6))) void block_sea
         u64 *u = s_hist + (size_t)t * HS * wpb;
         PeriodScan<WEIGHTED, DIP> ps(cd, a.min_in_points, u, u + HS, scr);
         int jk = __builtin_amdgcn_readfirstlane(ps.best());
-        if (jk == kEvery) {
+        if (jk == kMarked) {
           // (the curve's record is read again: what only this needs of it
           // occupies no registers through the search)
           wave_sync();
           const PeriodScan<WEIGHTED, DIP> es(cd, a.min_in_points, u, u + HS, scr);
-          jk = __builtin_amdgcn_readfirstlane(es.every_start());
+          jk = __builtin_amdgcn_readfirstlane(es.marked_starts());
         }
         double Rs = 0.0, Ss = 0.0;
         if (jk >= 0) ps.sums(jk, Rs, Ss);

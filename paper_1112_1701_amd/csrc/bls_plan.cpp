@@ -258,7 +258,13 @@ int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom 
 // share a CU (untuned_lds_budget).  The block search: its parts for the curve's geometry,
 // 1.4 times that for weights, more where the LDS holds fewer than 20 periods
 // per CU.  The choice costs 1.6% against the faster kernel of each call; the
-// block search always, 7%, never, 18%.
+// block search always, 7%, never, 18%.  (Beyond 1000 bins it was only checked:
+// 192 calls of 1000 to 4096 bins cost 1% where it takes the block search, but
+// it leaves some of 3000 bins and more to the other kernel that would take half
+// as long, 4 x 2000 points x 4000 periods x 4096 bins, 0.005 to 0.05, 2.0 / 1.0
+// ms.)  A unit-weight curve of fewer points than a thirty-second of its bins has
+// boxes that tie over many start bins: 91 x 12 points x 40 periods x 2585 bins
+// 0.44 / 1.03 ms, 1000 bins 0.14 / 0.22; 50 points, 1000 bins 0.14 / 0.17.
 namespace {
 double every_box_cost(const CurveShape &s, bool weighted, bool counts, bool eight) {
   const double instr = s.nbins / 64.0 * (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
@@ -269,7 +275,8 @@ double block_cost(const CurveShape &s, bool weighted, const BlockGeom &g, int pe
   const double batches = ceil((20.0 + s.nbins / 25.0) / per);
   const double instr = 330.0 + rounds * (60.0 + 24.0 * g.bsize + 27.0 * (g.omax - g.omin + 1)) +
                        batches * (32.0 + 13.5 * g.bsize);
-  return instr * (weighted ? 1.4 : 1.0) * std::max(1.0, pow(20.0 / periods_per_cu, 0.8));
+  return instr * (weighted ? 1.4 : 32 * s.n < s.nbins ? 3.0 : 1.0) *
+         std::max(1.0, pow(20.0 / periods_per_cu, 0.8));
 }
 }  // namespace
 

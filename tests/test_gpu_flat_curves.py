@@ -96,3 +96,35 @@ def test_blocks(bls, monkeypatch, kind, flags, mip, n, m, nbins, qmin, qmax):
     for key in got[0]:
         assert np.array_equal(got[0][key], got[1][key], equal_nan=True), key
     assert ms[1] <= 4.0 * ms[0], ms
+
+
+# Far fewer points than bins: many boxes hold the same points, and tie.  The
+# first point is in bin 0 at every period, so that some of the boxes that tie
+# with the one from there run past the end of the cycle.
+@pytest.mark.parametrize("n,limit", [(4, 12.0), (12, 6.0), (50, 3.0), (200, 3.0)])
+@pytest.mark.parametrize("nbins,qmin,qmax", [(300, 0.01, 0.1), (1000, 0.005, 0.05),
+                                             (2585, 0.0058, 0.0454)])
+@pytest.mark.parametrize("rounded", [False, True])
+@pytest.mark.parametrize("weighted,flags", [(False, 0), (True, 1)])
+def test_few_points(bls, monkeypatch, n, limit, nbins, qmin, qmax, rounded, weighted, flags):
+    print("[case] few points", n, nbins, rounded, weighted, flags, flush=True)
+    nc, m = 90, 40
+    rng = np.random.default_rng(n)
+    t = np.sort(rng.uniform(0.0, 60.0, (nc, n)), axis=1).ravel()
+    x = rng.normal(0.0, 1.0, nc * n)
+    x = np.round(x) if rounded else x
+    w = rng.uniform(0.5, 2.0, nc * n) if weighted else None
+    per = synth.log_period_grid(0.2, 20.0, m)
+    got, ms = [], []
+    for mode in ("0", "1"):
+        monkeypatch.setenv("BLS_BLOCK_SEARCH", mode)
+        with bls.Plan(max_curves=nc, max_points=nc * n, max_periods=nc * m, flags=flags) as p:
+            for _ in range(5):
+                r = bls.bls_search_batch(p.handle, np.arange(nc + 1) * n, t, x, w, per, None, nbins,
+                                         qmin, qmax)
+            got.append(r)
+            ms.append(min(bls.bls_kernel_times(p.handle)))
+    print("[ms] every box, blocks:", ms, flush=True)
+    for key in got[0]:
+        assert np.array_equal(got[0][key], got[1][key], equal_nan=True), key
+    assert ms[1] <= limit * ms[0], ms
