@@ -979,9 +979,12 @@ __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : WEIGHTED ? 5 : 6))) void block_sea
         else
           fold_chunks<WEIGHTED, false>(a, fd, nchunks, np, s_f, s_hist, HS, gap);
       }
-      // The rest, 64 kPPT points a wave as long as they last.
+      // The rest: merged, or 64 kPPT points a wave as long as they last.
       const int64_t first = base + wave * 64 * kPPT;
-      if (first + 64 * kPPT <= n)
+      if (merge) {
+        if (base < n)
+          fold_rest<WEIGHTED, true>(a, fd, base, (int)(n - base), np, s_f, s_hist, HS);
+      } else if (first + 64 * kPPT <= n)
         fold_chunk<WEIGHTED, false>(a, fd, base, np, s_f, s_hist, HS, 1);
       else if (first < n)
         fold_tail<WEIGHTED>(a, fd, first, (int)(n - first), np, s_f, s_hist, HS);

@@ -88,6 +88,10 @@ __device__ inline int fold_lane_gap(double fmin, int nbins, float cadence) {
 // The block search, whose VALU is the busier, merges unit-weight points from
 // 0.15 bins per step (1000 bins, 1-minute cadence, 8 curves x 40000 periods of
 // 1.5 to 3 days: 7.2 ms merged, 6.8 not; 6 to 20 days: 7.4 and 7.9).
+// The points past the last whole chunk follow the same rule: merged always, 550
+// points took 1.5% longer and 240 weighted curves of about 2500 2.3%; never,
+// 100 curves of 1000 points 2 minutes apart x 4000 periods x 24 bins 2.13 ms
+// instead of 0.76 (weighted), 3000 points a minute apart x 10000 x 250 1.55 / 1.26.
 // Any answer is correct; this one only picks the faster fold.
 __device__ inline bool fold_merges(double fmin, int nbins, float cadence, int policy,
                                    bool weighted, double from = 0.3) {
@@ -214,10 +218,8 @@ __device__ inline void fold_chunk(const SearchArgs &a, const CurveDesc &cd, int6
 }
 
 // The curve's last points, fewer than kBlock kPPT of them (`left` from point
-// `base` on), kPPT to a thread as in a whole chunk; each point is one atomic
-// (merging them, with a bounds check on every step, took 1.5% longer on 550
-// points, and 2.3% on 240 weighted curves of about 2500).
-template <bool WEIGHTED>
+// `base` on), kPPT to a thread as in a whole chunk, merged or not likewise.
+template <bool WEIGHTED, bool MERGE>
 __device__ inline void fold_rest(const SearchArgs &a, const CurveDesc &cd, int64_t base, int left,
                                  int np, const double *s_f, unsigned long long *s_hist, int HS) {
   const int64_t off = uniform_i64(cd.n_off + base);
@@ -242,13 +244,25 @@ __device__ inline void fold_rest(const SearchArgs &a, const CurveDesc &cd, int64
   for (int t = 0; t < np; ++t) {
     unsigned long long *h = s_hist + (size_t)t * HS * wpb;
     const double f = s_f[t];
+    int bin[kPPT];
+    if (MERGE) {
+#pragma unroll
+      for (int r = 0; r < kPPT; ++r) bin[r] = raw_bin(d[r], f, nbd);
+    }
+    unsigned long long accA = 0, accB = 0;
 #pragma unroll
     for (int r = 0; r < kPPT; ++r) {
       if (k0 + r < left) {
-        unsigned long long *w = h + raw_bin(d[r], f, nbd);
-        __hip_atomic_fetch_add(w, va[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (WEIGHTED)
-          __hip_atomic_fetch_add(w + HS, vb[r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        accA = MERGE ? accA + va[r] : va[r];
+        if (WEIGHTED) accB = MERGE ? accB + vb[r] : vb[r];
+        const int rn = r + 1 < kPPT ? r + 1 : r;
+        if (!MERGE || r == kPPT - 1 || k0 + rn >= left || bin[rn] != bin[r]) {  // the run ends
+          unsigned long long *w = h + (MERGE ? bin[r] : raw_bin(d[r], f, nbd));
+          __hip_atomic_fetch_add(w, accA, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (WEIGHTED)
+            __hip_atomic_fetch_add(w + HS, accB, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          accA = accB = 0;
+        }
       }
     }
   }

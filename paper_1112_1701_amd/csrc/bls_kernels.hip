@@ -712,8 +712,12 @@ void search_kernel(SearchArgs a) {
         else
           fold_chunk<WEIGHTED, false>(a, cd, b, np, s_f, s_hist, HS, lanes_gap);
       }
-      if (base < cd.n)
-        fold_rest<WEIGHTED>(a, cd, base, (int)(cd.n - base), np, s_f, s_hist, HS);
+      if (base < cd.n) {
+        if (merge)
+          fold_rest<WEIGHTED, true>(a, cd, base, (int)(cd.n - base), np, s_f, s_hist, HS);
+        else
+          fold_rest<WEIGHTED, false>(a, cd, base, (int)(cd.n - base), np, s_f, s_hist, HS);
+      }
     }
     __syncthreads();
 
