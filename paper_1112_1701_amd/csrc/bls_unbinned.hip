@@ -440,23 +440,40 @@ __attribute__((amdgpu_waves_per_eu(4))) void unbinned_kernel(SearchArgs a) {
       }
     }
     if (MODE == kUnbCells) __syncthreads();
-    // (a thread per small block, joined across its large block's)
+    // (a thread per small block, joined across its large block's; a run does not
+    // split equal phases, so ranks after an equal phase are not starts and
+    // ranks before one no ends: a block without any has NaN extremes, which no
+    // pair passes)
     for (int i0 = 0; i0 < NS; i0 += kBlock) {
       const int i = i0 + tid, r0 = i * kUnbSub;
       double hi = -INFINITY, lo = INFINITY, bhi = -INFINITY, blo = INFINITY;
       int wm = 0x7fffffff;
-      double before = r0 > 0 && r0 < nk ? Pq[r0 - 1] : 0.0;
-      double wbefore = WEIGHTED && r0 > 0 && r0 < nk ? Pw[r0 - 1] : 0.0;
+      // (the block's four ranks and their neighbours, loaded together)
+      const int rc = min(r0, (nk - 1) & ~(kUnbSub - 1)), rb = max(rc - 1, 0);
+      const double2 p0 = *reinterpret_cast<const double2 *>(sph + rc),
+                    p1 = *reinterpret_cast<const double2 *>(sph + rc + 2),
+                    v0 = *reinterpret_cast<const double2 *>(Pq + rc),
+                    v1 = *reinterpret_cast<const double2 *>(Pq + rc + 2);
+      const double ph[kUnbSub + 1] = {p0.x, p0.y, p1.x, p1.y, sph[min(rc + kUnbSub, nk - 1)]};
+      const double v[kUnbSub] = {v0.x, v0.y, v1.x, v1.y};
+      double before = rc > 0 ? Pq[rb] : 0.0;
+      double wbefore = WEIGHTED && rc > 0 ? Pw[rb] : 0.0;
+      bool start = rc == 0 || sph[rb] < ph[0];
 #pragma unroll
       for (int k = 0; k < kUnbSub; ++k) {
         const int r = r0 + k;
         if (r < nk) {
-          const double v = Pq[r];
-          hi = fmax(hi, v);
-          lo = fmin(lo, v);
-          bhi = fmax(bhi, before);
-          blo = fmin(blo, before);
-          before = v;
+          const bool end = r == nk - 1 || ph[k] < ph[k + 1];
+          if (end) {
+            hi = fmax(hi, v[k]);
+            lo = fmin(lo, v[k]);
+          }
+          if (start) {
+            bhi = fmax(bhi, before);
+            blo = fmin(blo, before);
+          }
+          start = end;
+          before = v[k];
           if (WEIGHTED) {
             const double w = Pw[r];
             wm = min(wm, (int)(w - wbefore));

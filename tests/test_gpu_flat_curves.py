@@ -128,3 +128,35 @@ def test_few_points(bls, monkeypatch, n, limit, nbins, qmin, qmax, rounded, weig
     for key in got[0]:
         assert np.array_equal(got[0][key], got[1][key], equal_nan=True), key
     assert ms[1] <= limit * ms[0], ms
+
+
+@pytest.mark.parametrize("n,step", [(1700, 0.05), (20000, 0.01)])
+@pytest.mark.parametrize("weighted,flags", [(False, 0), (True, 0), (False, 1)])
+def test_unbinned_equal_times(bls, n, step, weighted, flags):
+    """Times on a coarse grid, several points a time: a run does not split equal
+    phases, and the screens see only the edges that runs can have.  The search
+    then takes what its sort takes, which is all that a flat curve on the same
+    times needs."""
+    import torch
+    dev = lambda a: None if a is None else torch.tensor(a, device="cuda:0")
+    print("[case] equal times", n, step, weighted, flags, flush=True)
+    rng = np.random.default_rng(n)
+    t = dev(np.round(np.sort(rng.uniform(0.0, 30.0, n)) / step) * step)
+    x, w = rng.normal(0.0, 1.0, n), dev(rng.uniform(0.5, 2.0, n)) if weighted else None
+    m = max(16, 300000 // n)
+    per = dev(synth.log_period_grid(0.2, 20.0, m))
+    out = [torch.empty(m, device="cuda:0", dtype=d) for d in (
+        torch.float32, torch.float32, torch.int32, torch.int32)]
+    best = torch.empty(1, device="cuda:0", dtype=torch.int64)
+    ms = []
+    for flux in (np.ones(n), x):
+        flux = dev(flux)
+        torch.cuda.synchronize()
+        with bls.Plan(max_points=n, max_periods=m, flags=flags) as p:
+            for _ in range(4):
+                bls.bls_search_unbinned_device(p.handle, np.array([0, n]), t, flux, w, per, None,
+                                               0.05, 0.28, *out, best)
+                bls.bls_synchronize(p.handle)
+            ms.append(min(bls.bls_kernel_times(p.handle)))
+    print("[ms] flat, noise:", ms, flush=True)
+    assert ms[1] <= 1.25 * ms[0], ms
