@@ -253,6 +253,9 @@ constexpr int window_lds_bytes(int tile, int nphase, bool per_wave) {
   return ((per_wave ? kBlock / 64 * window_stride(nphase) : tile * nphase) +
           window_pad(nphase)) * 8;
 }
+// Longest cadence of a launch with a wave per period: its times are in the
+// wave's registers.
+constexpr int kWindowWavePoints = 1024;
 // Static LDS of the window kernel (period frequencies and window lengths).
 constexpr int kWindowStaticLds = kTileMax * (8 + 4);
 

@@ -1544,13 +1544,19 @@ int bls_eclipse_window_device(bls_plan *p, const bls_batch *b, int32_t nphase, d
   // / a wave each: 24 x 100000 periods, 200 bins 2.00 / 1.79 ms, 1000 bins 3.13
   // / 2.64; 24 x 50000, 2000 bins 4.89 / 3.06; 12 x 50000, 3000 bins, one
   // workgroup per CU, 3.27 / 3.82; 4 x 20000, 1000 bins 0.212 / 0.189, but 2 x
-  // 4500 0.097 / 0.100), up to eight periods per wave and item.
+  // 4500 0.097 / 0.100), up to eight periods per wave and item; and where the
+  // waves hold every cadence in registers: read again for each period, 24 x
+  // 20000 periods of 1100 weighted points, 300 bins 0.51 / 0.85 ms, 10 x 2725 of
+  // 20000 points, 2000 bins 0.52 / 1.18.
   const double waves = std::max(p->num_cus, 1) * 4.0 * (kBlock / 64);
   double periods = 0.0;  // (checked below)
-  for (int c = 0; c < nc; ++c)
+  int64_t longest = 0;
+  for (int c = 0; c < nc; ++c) {
     periods += b->p_off ? (double)b->p_off[c + 1] - (double)b->p_off[c] : (double)b->nperiods_shared;
-  const bool per_wave =
-      2 * window_lds_bytes(tile, nphase, true) <= p->max_lds && periods >= 4 * waves;
+    longest = std::max(longest, b->n_off[c + 1] - b->n_off[c]);
+  }
+  const bool per_wave = 2 * window_lds_bytes(tile, nphase, true) <= p->max_lds &&
+                        periods >= 4 * waves && longest <= kWindowWavePoints;
   if (per_wave) tile = (int)std::min(8.0, periods / waves) * (kBlock / 64);
   std::vector<WindowDesc> wd(nc);
   int64_t items = 0, results = 0;

@@ -264,7 +264,7 @@ __global__ __launch_bounds__(kBlock) void window_wave_kernel(WindowArgs a) {
   int cur = 0;
   int64_t next0 = a.ncurves > 1 ? a.desc[1].item0 : a.nitems;
   WindowDesc wd = a.desc[0];
-  constexpr int kRegs = 16;
+  constexpr int kRegs = kWindowWavePoints / 64;
   double d[kRegs];
   int cached = -1;
   for (int64_t item = blockIdx.x; item < a.nitems; item += gridDim.x) {
@@ -289,9 +289,8 @@ __global__ __launch_bounds__(kBlock) void window_wave_kernel(WindowArgs a) {
       kl = window_bins(a.duration, fl, nb);
       if (wd.dmax * fl >= (double)kMaxCycle) atomicOr(a.overflow, 1u);
     }
-    const int n = __builtin_amdgcn_readfirstlane((int)min(wd.n, (int64_t)INT32_MAX));
-    const bool regs = n <= 64 * kRegs;
-    if (regs && cached != cur) {
+    const int n = __builtin_amdgcn_readfirstlane((int)min(wd.n, (int64_t)kWindowWavePoints));
+    if (cached != cur) {
 #pragma unroll
       for (int r = 0; r < kRegs; ++r) {
         const int i = lane + 64 * r;
@@ -311,18 +310,9 @@ __global__ __launch_bounds__(kBlock) void window_wave_kernel(WindowArgs a) {
       // (LDS operations of one wave complete in order)
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
-      if (regs) {
 #pragma unroll
-        for (int r = 0; r < kRegs; ++r)
-          if (64 * r < n && d[r] >= 0.0) fold_cycle(d[r], f, nbd, nbm1, row);
-      } else {
-#pragma unroll 4
-        for (int64_t i = lane; i < wd.n; i += 64) {
-          const double w = a.w ? a.w[wd.n_off + i] : 1.0;
-          const double ti = a.t[wd.n_off + i];
-          if (w != 0.0) fold_cycle(ti - wd.t0, f, nbd, nbm1, row);
-        }
-      }
+      for (int r = 0; r < kRegs; ++r)
+        if (64 * r < n && d[r] >= 0.0) fold_cycle(d[r], f, nbd, nbm1, row);
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
       __builtin_amdgcn_wave_barrier();
       const int c = window_period<GAP>(row, nb, k);
