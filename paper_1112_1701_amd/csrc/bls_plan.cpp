@@ -264,19 +264,22 @@ int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom 
 // as long, 4 x 2000 points x 4000 periods x 4096 bins, 0.005 to 0.05, 2.0 / 1.0
 // ms.)  A unit-weight curve of fewer points than a thirty-second of its bins has
 // boxes that tie over many start bins: 91 x 12 points x 40 periods x 2585 bins
-// 0.44 / 1.03 ms, 1000 bins 0.14 / 0.22; 50 points, 1000 bins 0.14 / 0.17.
+// 0.44 / 1.03 ms, 1000 bins 0.14 / 0.22; 50 points, 1000 bins 0.14 / 0.17.  So
+// has a weighted one with a minimum count, which hardly a box reaches: 132 x 6 x
+// 244 x 1740, a minimum of three 4.0 / 12.1 ms (of one, 2.4 / 0.73).
 namespace {
 double every_box_cost(const CurveShape &s, bool weighted, bool counts, bool eight) {
   const double instr = s.nbins / 64.0 * (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
   return instr * (!weighted ? (eight ? 0.9 : 1.0) : counts ? 3.0 : eight ? 1.25 : 1.55);
 }
-double block_cost(const CurveShape &s, bool weighted, const BlockGeom &g, int periods_per_cu) {
+double block_cost(const CurveShape &s, bool weighted, bool counts, const BlockGeom &g,
+                  int periods_per_cu) {
   const int rounds = (g.nblocks + 63) / 64, per = 64 / g.bsize;
   const double batches = ceil((20.0 + s.nbins / 25.0) / per);
   const double instr = 330.0 + rounds * (60.0 + 24.0 * g.bsize + 27.0 * (g.omax - g.omin + 1)) +
                        batches * (32.0 + 13.5 * g.bsize);
-  return instr * (weighted ? 1.4 : 32 * s.n < s.nbins ? 3.0 : 1.0) *
-         std::max(1.0, pow(20.0 / periods_per_cu, 0.8));
+  const double ties = 32 * s.n < s.nbins && (!weighted || counts) ? 3.0 : 1.0;
+  return instr * (weighted ? 1.4 : 1.0) * ties * std::max(1.0, pow(20.0 / periods_per_cu, 0.8));
 }
 }  // namespace
 
@@ -297,7 +300,7 @@ bool block_batch(const CurveShape *shapes, int n, bool weighted, int min_in_poin
     const bool eight = tuned || untuned_lds_budget(s, periods, weighted, num_cus) <
                                     default_tiles(weighted).lds_budget;
     every += (double)s.nperiods * every_box_cost(s, weighted, min_in_points > 1, eight);
-    block += (double)s.nperiods * block_cost(s, weighted, g, T * groups);
+    block += (double)s.nperiods * block_cost(s, weighted, min_in_points > 1, g, T * groups);
   }
   // Fewer periods than seven waves per CU: a period takes a wave 25 us or more,
   // and the four of a workgroup less (461 bins, 1497 periods 44 / 35 us; 400

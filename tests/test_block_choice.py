@@ -1,5 +1,6 @@
-"""The choice between the two binned kernels (no GPU): unit-weight curves of far
-fewer points than bins stay with the kernel that scores every box."""
+"""The choice between the two binned kernels (no GPU): curves of far fewer points
+than bins stay with the kernel that scores every box, but for weighted ones
+without a minimum count."""
 import ctypes as C
 import os
 
@@ -14,14 +15,15 @@ class Shape(C.Structure):
                [(k, C.c_int32) for k in ("nperiods", "nbins", "kmin", "kmax")]
 
 
-@pytest.mark.parametrize("n,weighted,want", [(12, False, False), (80, False, False),
-                                             (81, False, True), (5000, False, True),
-                                             (12, True, True)])
-def test_few_points(monkeypatch, n, weighted, want):
+@pytest.mark.parametrize("n,weighted,mip,want", [
+    (12, False, 1, False), (54, False, 1, False), (55, False, 1, True), (5000, False, 1, True),
+    (12, True, 1, True), (12, True, 3, False), (55, True, 3, True)])
+def test_few_points(monkeypatch, n, weighted, mip, want):
     import paper_1112_1701_amd._lib as L
     L.load()
     monkeypatch.delenv("BLS_BLOCK_SEARCH", raising=False)
     f = getattr(C.CDLL(LIB), "_ZN3bls11block_batchEPKNS_10CurveShapeEibibii")
     f.restype = C.c_bool
-    s = Shape(0, n, 0, 0, 20000, 2585, 15, 260)
-    assert f(C.byref(s), 1, C.c_bool(weighted), 1, C.c_bool(False), 256, 160 * 1024) == want
+    kmax = 62 if weighted and mip > 1 else 170
+    s = Shape(0, n, 0, 0, 20000, 1740, 26, kmax)
+    assert f(C.byref(s), 1, C.c_bool(weighted), mip, C.c_bool(False), 256, 160 * 1024) == want
