@@ -1794,9 +1794,10 @@ int bls_debug_phase_bins(bls_plan *p, const double *times, int64_t n, double per
   pa.q = p->d_q;
   pa.qw = p->d_qw;
   if ((e = (hipError_t)launch_prep(pa, s)) != hipSuccess) return hip_error(p, e, "launch prep");
-  if ((e = (hipError_t)launch_bins(p->d_dt, n, p->d_periods, nbins, p->d_j, s)) != hipSuccess)
+  // into the encoded fluxes, which hold max_points values and are not needed
+  if ((e = (hipError_t)launch_bins(p->d_dt, n, p->d_periods, nbins, p->d_q, s)) != hipSuccess)
     return hip_error(p, e, "launch bins");
-  if ((e = hipMemcpyAsync(bins, p->d_j, n * 4, hipMemcpyDeviceToHost, s)) != hipSuccess)
+  if ((e = hipMemcpyAsync(bins, p->d_q, n * 4, hipMemcpyDeviceToHost, s)) != hipSuccess)
     return hip_error(p, e, "download bins");
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return hip_error(p, e, "synchronize");
   return BLS_OK;
