@@ -850,31 +850,36 @@ void fill_stats(bls_plan *p, const PlannedBatch &pb, bool replayed) {
 static size_t result_stride(int64_t n) { return ((size_t)n + 31) & ~(size_t)31; }
 
 int ensure_staging(bls_plan *p) {
-  if (p->staging) return BLS_OK;
+  if (p->d_t) return BLS_OK;
   const size_t np = (size_t)p->cfg.max_points, nr = (size_t)p->cfg.max_periods,
                nc = (size_t)p->cfg.max_curves;
-  // Inputs in one block and results in another, for one copy each way; a
-  // call lays them out compactly from the block's start (host_search), the
-  // other users have them at the plan's capacities.
-  const size_t nrp = result_stride((int64_t)nr);
-  hipError_t e = device_alloc((void **)&p->d_t, 3 * np * 8 + nr * 8);
-  if (e == hipSuccess) {
-    e = device_alloc((void **)&p->d_sr, nrp * 16 + nc * 8);
-    if (e != hipSuccess) {
-      free_dev(p->d_t);
-      p->d_t = nullptr;
-      p->d_sr = nullptr;
-    }
+  // One block, for one copy; a call lays its inputs out compactly from the
+  // block's start (host_search), the other users have them at the plan's
+  // capacities.  The best keys follow on a line of their own.
+  const size_t in = (3 * np + nr + 15) & ~(size_t)15;
+  const hipError_t e = device_alloc((void **)&p->d_t, (in + nc) * 8);
+  if (e != hipSuccess) {
+    p->d_t = nullptr;
+    return hip_error(p, e, "allocate host-path staging");
   }
-  if (e != hipSuccess) return hip_error(p, e, "allocate host-path staging");
   p->d_x = p->d_t + np;
   p->d_w = p->d_x + np;
   p->d_periods = p->d_w + np;
+  p->d_best = reinterpret_cast<int64_t *>(p->d_t + in);
+  return BLS_OK;
+}
+
+int ensure_result_staging(bls_plan *p) {
+  if (p->d_sr) return BLS_OK;
+  const size_t nrp = result_stride(p->cfg.max_periods);
+  const hipError_t e = device_alloc((void **)&p->d_sr, nrp * 16);
+  if (e != hipSuccess) {
+    p->d_sr = nullptr;
+    return hip_error(p, e, "allocate host-path staging");
+  }
   p->d_depth = p->d_sr + nrp;
   p->d_j = reinterpret_cast<int32_t *>(p->d_depth + nrp);
   p->d_k = p->d_j + nrp;
-  p->d_best = reinterpret_cast<int64_t *>(p->d_k + nrp);
-  p->staging = true;
   return BLS_OK;
 }
 
@@ -1045,6 +1050,7 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
   // into it, then DMA (pageable copies run at a fraction of that rate).  The
   // previous call's copies from or into it ended with that call.
   const bool pinned = ensure_host_stage(p);
+  if (!pinned && (st = ensure_result_staging(p)) != BLS_OK) return st;
   const double *src_t = b.times, *src_x = b.flux, *src_w = b.weights, *src_p = b.periods;
   if (pinned) {
     double *st = reinterpret_cast<double *>(p->h_stage);
@@ -1077,7 +1083,6 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
   const int64_t nres = pb.total_results;
   const size_t nrp = result_stride(nres);
   float *d_sr = p->d_sr;
-  int64_t *keys = reinterpret_cast<int64_t *>(d_sr + 4 * nrp);
   // With pinned staging the kernels write the results there themselves (the
   // inputs' upload from it has ended by then: same stream), and only the best
   // keys, which they update by atomics, stay in device memory.  A copy after
@@ -1087,9 +1092,9 @@ int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &
     return hip_error(p, e, "address of the results");
   float *d_depth = d_sr + nrp;
   int32_t *d_j = reinterpret_cast<int32_t *>(d_depth + nrp), *d_k = d_j + nrp;
-  int64_t *d_best = reinterpret_cast<int64_t *>(d_k + nrp);
+  int64_t *d_best = pinned ? reinterpret_cast<int64_t *>(d_k + nrp) : p->d_best;
   st = enqueue_search(p, pb, d_t, d_x, weighted ? d_w : nullptr, d_per, d_sr, d_depth, d_j, d_k,
-                      d_best, false, true, keys);
+                      d_best, false, true, p->d_best);
   if (st != BLS_OK) return st;
   if ((e = hipEventRecord(p->ev_end, s)) != hipSuccess) return hip_error(p, e, "event");
 

@@ -67,12 +67,13 @@ struct bls_plan {
   int32_t *d_qw = nullptr;
   unsigned long long *d_counter = nullptr;
 
-  // host-API staging (allocated on first use)
-  bool staging = false;
+  // staging of the host-array and recovery calls (allocated on first use):
+  // inputs and best keys; results where the host call has no pinned memory
+  // for them, and of the recovery
   double *d_t = nullptr, *d_x = nullptr, *d_w = nullptr, *d_periods = nullptr;
+  int64_t *d_best = nullptr;
   float *d_sr = nullptr, *d_depth = nullptr;
   int32_t *d_j = nullptr, *d_k = nullptr;
-  int64_t *d_best = nullptr;
   // pinned host staging of the host API (allocated on first use): a call's
   // inputs on the way in, its results on the way out
   char *h_stage = nullptr;
@@ -251,9 +252,12 @@ int width_range(int32_t nbins, double qmin, double qmax, int32_t *kmin, int32_t 
 double last_kernel_ms(bls_plan *p);
 // Call statistics of a planned batch.
 void fill_stats(bls_plan *p, const PlannedBatch &pb, bool replayed);
-// Device buffers of the host-array calls (max_points, max_periods,
-// max_curves sized), allocated on first use.
+// Device inputs and best keys of the host-array and recovery calls
+// (max_points, max_periods, max_curves sized), allocated on first use.
 int ensure_staging(bls_plan *p);
+// The same for their results, for calls whose kernels write them to device
+// memory.
+int ensure_result_staging(bls_plan *p);
 // INVALID_ARG naming the first curve whose prep found invalid data.
 int check_device_status(bls_plan *p, int ncurves);
 // Per-curve flags (1: invalid data or trial periods) of the last prep.

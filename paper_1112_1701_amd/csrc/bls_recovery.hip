@@ -132,10 +132,11 @@ extern "C" int bls_injection_recovery_device(bls_plan *p, const bls_recovery_con
                 "injections x points, injections or injections x periods exceed the plan");
   std::vector<int64_t> n_off(ninj + 1);
   for (int32_t k = 0; k <= ninj; ++k) n_off[k] = (int64_t)k * n;
-  int st = ensure_staging(p);
-  if (st != BLS_OK) return st;
   hipError_t e = hipSetDevice(p->device);
   if (e != hipSuccess) return hip_error(p, e, "set device");
+  int st = ensure_staging(p);
+  if (st == BLS_OK) st = ensure_result_staging(p);
+  if (st != BLS_OK) return st;
   bls_batch b;
   memset(&b, 0, sizeof b);
   b.ncurves = ninj;
