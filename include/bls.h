@@ -262,7 +262,8 @@ const char *bls_status_string(int status);
  * nbins is ignored and qmin/qmax are phase fractions; at most 2^20 points
  * per curve (curves above 4096 points keep their per-point arrays in a
  * plan-owned device workspace instead of LDS, about 36 bytes per point per
- * resident workgroup, at most about 1 GiB, and run slower).  out: device arrays [results]: FP32 SR and depth, and the
+ * resident workgroup, at most about 1 GiB, and run slower).
+ * out: device arrays [results]: FP32 SR and depth, and the
  * input indices (within the curve) of the best box's first and last points
  * in phase order (-1 where no box); best_index per curve.  Asynchronous on
  * the plan's stream: bls_synchronize reports invalid data.  Errors:

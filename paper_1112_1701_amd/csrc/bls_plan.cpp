@@ -906,9 +906,8 @@ int check_device_status(bls_plan *p, int ncurves) {
   return BLS_OK;
 }
 
-
 // Per-curve validity flags of the last prep (1 where the curve's data or
-// trial periods were invalid), read back from the device descriptors.
+// trial periods were invalid); the prep kernel writes them to host memory.
 int device_status_flags(bls_plan *p, int ncurves, int32_t *bad) {
   const int st = wait_for_status(p);
   if (st != BLS_OK) return st;
@@ -977,10 +976,6 @@ using namespace bls;
 
 namespace {
 
-// Duration of the most recent bracketed kernel launch (the stream must have
-// reached its end event); 0 if there is none.
-// Host-array search of a validated batch (shared by bls_search and
-// bls_search_batch).
 // f(i0, i1) over [0, n) in contiguous pieces on up to 16 host threads, one
 // piece per `grain` items at least (the calling thread takes the last).
 template <class F>
@@ -1032,6 +1027,8 @@ bool ensure_host_stage(bls_plan *p) {
   return true;
 }
 
+// Host-array search of a validated batch (shared by bls_search and
+// bls_search_batch).
 int host_search(bls_plan *p, const bls_batch &b, const std::vector<CurveShape> &shapes,
                 const bls_results &out) {
   int st = ensure_staging(p);

@@ -125,8 +125,9 @@ struct bls_plan {
   hipEvent_t ev_begin = nullptr, ev_search0 = nullptr, ev_search1 = nullptr,
              ev_end = nullptr;
 
-  // The pinned descriptors above are read by queued copies until ev_desc, recorded after them, completes; a call that
-  // rewrites them first waits for it.
+  // The pinned descriptors above are read by queued copies until ev_desc,
+  // recorded after them, completes; a call that rewrites them first waits for
+  // it.
   hipEvent_t ev_desc = nullptr;
   bool desc_pending = false;
 
@@ -217,12 +218,13 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
 // The launch sequence of a search, in three parts: (1) upload descriptors,
 // clear counters and keys, prep; (2) the search kernel (with unbinned, the
 // unbinned kernel: js and ks then receive the first and last point of each
-// best box); (3) per-curve best index.  upload: the descriptors are new.
+// best box); (3) per-curve best index from the best keys, in their place or
+// elsewhere.  upload: the descriptors are new.
 int enqueue_pre(bls_plan *p, const PlannedBatch &pb, const double *t, const double *x,
                 const double *w, const double *periods, int64_t *best, bool upload);
 int enqueue_kernel(bls_plan *p, const PlannedBatch &pb, const double *periods, float *sr,
                    float *depth, int32_t *js, int32_t *ks, int64_t *best, bool unbinned);
-int enqueue_post(bls_plan *p, const PlannedBatch &pb, int64_t *best);
+int enqueue_post(bls_plan *p, const PlannedBatch &pb, const int64_t *keys, int64_t *best);
 // All three, with ev_desc after the uploads and the kernel bracketed by the
 // timing ring's events (streams that are not capturing).
 int enqueue_search(bls_plan *p, const PlannedBatch &pb, const double *t, const double *x,
