@@ -9,14 +9,22 @@
 // consecutive prefix sums keep their extremes, and one test per pair of
 // blocks (25 to 80 boxes) rejects all but about a twentieth of the pairs; the
 // boxes of the rest are scored from prefix differences.  What is left is the
-// fold: its FP64 operations and LDS atomics.
+// fold, its FP64 operations and LDS atomics; below about 500 bins the search
+// itself is still the larger part (a period of 2000 points and 300 bins takes
+// 1270 VALU instructions, 1480 in search_kernel).
 //
-// Measured, search_kernel against this one: 169 weighted curves x 859 points
-// x 6456 periods x 525 bins 21.9 / 8.6 ms; 6 x 24601 x 26314 x 897 (0.005 to
-// 0.08) 3.15 / 2.35; weighted 3 x 36710 x 42741 x 864 7.1 / 3.8; 24 x 50000 x
-// 100000 x 1000 (0.005 to 0.05) 51.5 / 44.4.  VALU-bound up to about 600
-// bins (0.95 instructions per SIMD and clock issued of 1); beyond that the
-// LDS leaves too few waves to fill the latencies.
+// Measured, search_kernel against this one (weights within a factor of four,
+// boxes of 0.01 to 0.1 cycle where not stated): 169 weighted curves x 859
+// points x 6456 periods x 525 bins 8.8 / 5.9 ms; 6 x 24601 x 26314 x 897 (0.005
+// to 0.08) 3.1 / 2.2; weighted 3 x 36710 x 42741 x 864 (0.005 to 0.08) 4.2 /
+// 3.6; 24 x 50000 x 100000 x 1000 (0.005 to 0.05) 51.5 / 44.2.
+//
+// VALU instructions per CU and clock (1.15 is what search_kernel reaches at
+// 300 bins), and the share of the clocks in which the LDS is active: 300 bins
+// 0.92 and 0.62, weighted 0.75 and 0.61; 525 bins 0.87 and 0.43, weighted 0.71
+// and 0.43; 1000 bins and 20000 points 0.75 and 0.71, weighted 0.63 and 0.60.
+// So neither is full: the registers and the LDS leave six to three waves per
+// SIMD, whose latencies (LDS, cross-lane sums) show.
 //
 // The answer is exactly the one that scoring every box in FP32 gives: bounds
 // and scores carry an error term that covers every rounding on both sides,
@@ -871,11 +879,12 @@ struct PeriodScan {
 
 // WIDE: the copy for launches of at most four workgroups per CU, which have
 // the registers of four waves per SIMD to themselves.  In the others' 80 (96
-// weighted) VGPRs a period's set-up spills 26 (32), 12.6 GB of writes for 256
-// x 50000 points x 100000 periods x 1000 bins; in 115 (128) none (one) does.
-// 24 x 50000 x 100000 x 1000: 44.9 / 44.4 ms; weighted 23 x 805 x 9306 x 585
-// 1.84 / 1.80; but 158 x 1346 x 5016 x 218, whose LDS leaves room for six,
-// 1.94 / 2.30.
+// weighted) VGPRs a period's set-up spills 31 (35), 12.6 GB of writes for 256
+// x 50000 points x 100000 periods x 1000 bins; in 121 (128) none does.
+// Narrow / wide: 24 x 50000 x 100000 x 1000 (0.005 to 0.05) 47.9 / 46.5 ms;
+// weighted 24 x 20000 x 20000 x 700 8.5 / 8.3; but where the LDS leaves room
+// for five or six, weighted 23 x 805 x 9306 x 585 1.53 / 1.74 and 158 x 1346 x
+// 5016 x 218 1.98 / 2.52.
 template <bool WEIGHTED, bool DIP, bool WIDE>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : WEIGHTED ? 5 : 6))) void block_search_kernel(

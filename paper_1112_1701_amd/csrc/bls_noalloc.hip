@@ -179,8 +179,7 @@ extern "C" int bls_search_device_noalloc(const bls_batch *b, const bls_device_re
   LdsLayout lds;
   for (int c = 0; c < nc; ++c) {
     const CurveShape &s = shapes[c];
-    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, false, block,
-                    desc[c]);
+    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, block, desc[c]);
     const int T = desc[c].tile;
     lds.add(desc[c], block);
     const double nw = (double)(s.kmax - s.kmin + 1);

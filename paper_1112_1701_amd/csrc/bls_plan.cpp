@@ -14,11 +14,9 @@
 #include <algorithm>
 #include <atomic>
 #include <chrono>
-#include <mutex>
 #include <new>
 #include <numeric>
 #include <thread>
-#include <unordered_map>
 
 namespace bls {
 namespace {
@@ -105,40 +103,38 @@ namespace {
 // of 16 lanes takes as many cycles as the busiest bank has accesses.  Lane
 // task q is (start bin, period) = divmod(q, tile); every lane reads at the
 // same offset m past its own start, which moves all banks alike, so m = 0.
+// Both banks of a read are an even one and the next, so pairs of them are
+// counted.
 int scan_read_cycles(int S, int tile, int nbins) {
-  int cycles = 0;
-  for (int round = 0; round < 4; ++round) {
-    for (int g = 0; g < kBlock / 16; ++g) {
-      int bank[32] = {0};
-      int worst = 0;
-      for (int l = 0; l < 16; ++l) {
-        const int q = round * kBlock + g * 16 + l;
-        const int j = q / tile, t = q - (q / tile) * tile;
-        if (j >= nbins) continue;
-        const int b0 = (int)((2 * ((int64_t)t * S + j)) & 31);
-        worst = std::max(worst, ++bank[b0]);
-        worst = std::max(worst, ++bank[(b0 + 1) & 31]);
-      }
-      cycles += worst;
+  const int tasks = std::min(4 * kBlock, nbins * tile);
+  int cycles = 0, t = 0, pair = 0;
+  for (int q = 0; q < tasks; q += 16) {
+    uint8_t count[16] = {0};
+    int worst = 0;
+    for (int l = q; l < std::min(q + 16, tasks); ++l) {
+      worst = std::max<int>(worst, ++count[pair & 15]);
+      const bool next = ++t == tile;  // the next start bin
+      pair += next ? 1 - (tile - 1) * S : S;
+      t = next ? 0 : t;
     }
+    cycles += worst;
   }
   return cycles;
 }
 
-// Banks depend on S mod 16 only; the cost of each residue is kept.
+// Banks depend on S mod 16 only; the costs are kept, each where its key falls,
+// without a lock or heap use (a stride takes 16 of them, 33 us; 59 equal curves
+// in a call without a plan, which kept none and took up to three each, 3.1 ms).
 int cached_read_cycles(int S, int tile, int nbins) {
-  static std::mutex mu;
-  static std::unordered_map<uint64_t, int> memo;
-  const int nb = std::min(nbins, 4 * kBlock);  // lanes reach no further start bin
+  constexpr int kBits = 12;
+  static std::atomic<uint64_t> memo[1 << kBits];  // key << 16 | cost (at most 1024)
+  const int nb = std::min(nbins, 4 * kBlock);     // lanes reach no further start bin
   const uint64_t key = ((uint64_t)nb << 16) | ((uint64_t)tile << 4) | (uint64_t)(S & 15);
-  {
-    std::lock_guard<std::mutex> g(mu);
-    auto it = memo.find(key);
-    if (it != memo.end()) return it->second;
-  }
+  std::atomic<uint64_t> &place = memo[(key * 0x9E3779B97F4A7C15ull) >> (64 - kBits)];
+  const uint64_t kept = place.load(std::memory_order_relaxed);
+  if (kept >> 16 == key) return (int)(kept & 0xFFFF);
   const int c = scan_read_cycles(S & 15, tile, nb);
-  std::lock_guard<std::mutex> g(mu);
-  memo.emplace(key, c);
+  place.store(key << 16 | (uint64_t)c, std::memory_order_relaxed);
   return c;
 }
 
@@ -150,13 +146,12 @@ int hist_words(int nbins, int kmax) {
   return nbins + std::max(std::min(kmax, nbins / 2) - 1, 1);
 }
 
-int hist_stride(int nbins, int kmax, int tile, bool weighted, bool memo) {
+int hist_stride(int nbins, int kmax, int tile, bool weighted) {
   const int hb = hist_words(nbins, kmax);
   const int wpb = weighted ? 2 : 1;  // the scan reads the first plane of wpb
   int best = hb, best_cost = 0;
   for (int hs = hb; hs < hb + 16; ++hs) {
-    const int c = memo ? cached_read_cycles(hs * wpb, tile, nbins)
-                       : scan_read_cycles((hs * wpb) & 15, tile, std::min(nbins, 4 * kBlock));
+    const int c = cached_read_cycles(hs * wpb, tile, nbins);
     if (hs == hb || c < best_cost) {
       best = hs;
       best_cost = c;
@@ -166,16 +161,16 @@ int hist_stride(int nbins, int kmax, int tile, bool weighted, bool memo) {
 }
 
 void fit_tile(int nbins, int kmax, int64_t nperiods, int lds_budget, int tile_cap,
-              bool weighted, int *tile, int *stride, bool memo) {
+              bool weighted, int *tile, int *stride) {
   const int wpb = weighted ? 2 : 1;
   int T = std::max(1, lds_budget / (hist_words(nbins, kmax) * 8 * wpb));
   T = std::min(T, std::min(tile_cap, kTileMax));
   T = (int)std::min<int64_t>(T, std::max<int64_t>(nperiods, 1));
   T = std::max(T, 1);
-  int hs = hist_stride(nbins, kmax, T, weighted, memo);
+  int hs = hist_stride(nbins, kmax, T, weighted);
   while (T > 1 && T * hs * 8 * wpb > lds_budget) {
     --T;
-    hs = hist_stride(nbins, kmax, T, weighted, memo);
+    hs = hist_stride(nbins, kmax, T, weighted);
   }
   *tile = T;
   *stride = hs;
@@ -255,18 +250,26 @@ int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom 
 // quarters as many again for weights, and twice that where a box that passes
 // the screen has its points counted (weighted, a minimum of two or more); 0.8
 // to 0.9 of it where the call's tiles are tuned or let eight (six) workgroups
-// share a CU (untuned_lds_budget).  The block search: its parts for the curve's geometry,
-// 1.4 times that for weights, more where the LDS holds fewer than 20 periods
-// per CU.  The choice costs 1.6% against the faster kernel of each call; the
-// block search always, 7%, never, 18%.  (Beyond 1000 bins it was only checked:
-// 192 calls of 1000 to 4096 bins cost 1% where it takes the block search, but
-// it leaves some of 3000 bins and more to the other kernel that would take half
-// as long, 4 x 2000 points x 4000 periods x 4096 bins, 0.005 to 0.05, 2.0 / 1.0
-// ms.)  A unit-weight curve of fewer points than a thirty-second of its bins has
-// boxes that tie over many start bins: 91 x 12 points x 40 periods x 2585 bins
-// 0.44 / 1.03 ms, 1000 bins 0.14 / 0.22; 50 points, 1000 bins 0.14 / 0.17.  So
-// has a weighted one with a minimum count, which hardly a box reaches: 132 x 6 x
-// 244 x 1740, a minimum of three 4.0 / 12.1 ms (of one, 2.4 / 0.73).
+// share a CU (untuned_lds_budget).  The block search: its parts for the curve's
+// geometry, 1.4 times that for weights, more where the LDS holds fewer than 20
+// periods per CU.  The choice costs 1.6% against the faster kernel of each
+// call; the block search always, 7%, never, 18%.  (Beyond 1000 bins it was only
+// checked: 192 calls of 1000 to 4096 bins cost 1% where it takes the block
+// search, but it leaves some of 3000 bins and more to the other kernel that
+// would take half as long, 4 x 2000 points x 4000 periods x 4096 bins, 0.005 to
+// 0.05, 2.0 / 1.0 ms.)  A unit-weight curve of fewer points than a thirty-second
+// of its bins has boxes that tie over many start bins: 91 x 12 points x 40
+// periods x 2585 bins 0.44 / 1.03 ms, 1000 bins 0.14 / 0.22; 50 points, 1000
+// bins 0.14 / 0.17.  So has a weighted one with a minimum count, which hardly a
+// box reaches: 132 x 6 x 244 x 1740, a minimum of three 4.0 / 12.1 ms (of one,
+// 2.4 / 0.73).
+//
+// The rule sees sizes and not the data, on which the block search's time
+// depends more than the other's: narrow boxes and weights over four decades
+// (105 x 500 points x 192 periods x 2000 bins, 0.0038 to 0.046) 1.03 / 1.76 ms
+// where weights within a factor of four take 0.95 / 0.88; data that cover less
+// than a third of the period (8 x 1120 x 3232 x 1455, 0.011 to 0.21, periods to
+// 20 d in 4 d) 2.0 / 2.35 where 60 d take 1.63 / 0.46.
 namespace {
 double every_box_cost(const CurveShape &s, bool weighted, bool counts, bool eight) {
   const double instr = s.nbins / 64.0 * (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
@@ -347,7 +350,7 @@ void LdsLayout::add(const CurveDesc &d, bool block) {
 }
 
 void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
-                     bool check_periods, bool memo, bool block, CurveDesc &d) {
+                     bool check_periods, bool block, CurveDesc &d) {
   memset(&d, 0, sizeof d);
   d.n_off = s.n_off;
   d.n = s.n;
@@ -370,7 +373,7 @@ void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
     fit_block_tile(s.nbins, s.kmin, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T,
                    &hs, &g);
   else
-    fit_tile(s.nbins, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T, &hs, memo);
+    fit_tile(s.nbins, s.kmax, s.nperiods, tc.lds_budget, tc.tile_cap, weighted, &T, &hs);
   d.tile = T;
   d.hstride = hs;
   if (block) set_block_layout(d, g);
@@ -620,7 +623,7 @@ int plan_batch(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted
     const CurveShape &s = shapes[c];
     CurveDesc &d = p->h_curves[c];
     // each distinct period range is checked once (a shared grid by curve 0)
-    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, true, block, d);
+    fill_curve_desc(s, weighted, tc, c == 0 || s.p_off != shapes[0].p_off, block, d);
     const int T = d.tile;
     if (G > 0) {
       d.group = G;

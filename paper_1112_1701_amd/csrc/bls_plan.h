@@ -164,11 +164,9 @@ int validate_batch_into(const bls_plan_config &cfg, const bls_batch &b, bool che
                         bool binned = true);
 // Host fields of one curve's descriptor (prep fields zero): fixed-point
 // layout, and the period tile and plane stride that fit tc's LDS budget.
-// memo: keep the bank-conflict costs of plane strides in the process-wide
-// cache (false: compute them afresh, with no heap use).
 // block: the layout of the block search (bls_blocks.hip).
 void fill_curve_desc(const CurveShape &s, bool weighted, const TileChoice &tc,
-                     bool check_periods, bool memo, bool block, CurveDesc &d);
+                     bool check_periods, bool block, CurveDesc &d);
 
 // Whether the block search can run every curve of a launch (boxes of at most
 // half the bins) and is the faster kernel for it.  tuned: the tiles of the
@@ -283,11 +281,11 @@ int hist_words(int nbins, int kmax);
 // at least hist_words, padded so that the scan's 64-bit reads, served 16
 // lanes at a time across 32 four-byte banks, meet as few bank conflicts as
 // the layout allows (lane task (start bin, period) = divmod(lane, tile)).
-int hist_stride(int nbins, int kmax, int tile, bool weighted, bool memo = true);
+int hist_stride(int nbins, int kmax, int tile, bool weighted);
 // Periods per work item that fit an LDS budget (at least one, at most
 // tile_cap and nperiods) and the padded stride that goes with it.
 void fit_tile(int nbins, int kmax, int64_t nperiods, int lds_budget, int tile_cap,
-              bool weighted, int *tile, int *stride, bool memo = true);
+              bool weighted, int *tile, int *stride);
 
 // Tile choice for a batch: autotuned (cached) unless disabled.
 TileChoice choose_tiles(bls_plan *p, const std::vector<CurveShape> &shapes, bool weighted);

@@ -36,7 +36,7 @@ void launch(const char *what, const std::vector<CurveShape> &v, bool weighted,
     tc.tile_cap = 4;
     tc.block = true;
     CurveDesc d;
-    fill_curve_desc(v[c], weighted, tc, false, false, true, d);
+    fill_curve_desc(v[c], weighted, tc, false, true, d);
     lds.add(d, true);
   }
   ++g_block;
