@@ -260,16 +260,20 @@ int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom 
 // 0.05, 2.0 / 1.0 ms.)  A unit-weight curve of fewer points than a thirty-second
 // of its bins has boxes that tie over many start bins: 91 x 12 points x 40
 // periods x 2585 bins 0.44 / 1.03 ms, 1000 bins 0.14 / 0.22; 50 points, 1000
-// bins 0.14 / 0.17.  So has a weighted one with a minimum count, which hardly a
-// box reaches: 132 x 6 x 244 x 1740, a minimum of three 4.0 / 12.1 ms (of one,
-// 2.4 / 0.73).
+// bins 0.14 / 0.17; and more the fewer they are: 4 x 4510 periods x 1393 bins,
+// 0.024 to 0.16, of 6, 10, 20 and 40 points 1.46 / 2.70, 1.33 / 1.75, 1.13 /
+// 0.94 and 0.95 / 0.46.  So has a weighted one with a minimum count, which
+// hardly a box reaches: 132 x 6 x 244 x 1740, a minimum of three 4.0 / 12.1 ms
+// (of one, 2.4 / 0.73).
 //
 // The rule sees sizes and not the data, on which the block search's time
 // depends more than the other's: narrow boxes and weights over four decades
 // (105 x 500 points x 192 periods x 2000 bins, 0.0038 to 0.046) 1.03 / 1.76 ms
 // where weights within a factor of four take 0.95 / 0.88; data that cover less
 // than a third of the period (8 x 1120 x 3232 x 1455, 0.011 to 0.21, periods to
-// 20 d in 4 d) 2.0 / 2.35 where 60 d take 1.63 / 0.46.
+// 20 d in 4 d) 2.0 / 2.35 where 60 d take 1.63 / 0.46; dips alone beside rare
+// points far above them (1 x 1214 x 19830 x 743, 0.003 to 0.047, 0.5% of the
+// points 500 sigma up) 0.24 / 0.36 where noise takes 0.20 / 0.18.
 namespace {
 double every_box_cost(const CurveShape &s, bool weighted, bool counts, bool eight) {
   const double instr = s.nbins / 64.0 * (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
@@ -281,7 +285,9 @@ double block_cost(const CurveShape &s, bool weighted, bool counts, const BlockGe
   const double batches = ceil((20.0 + s.nbins / 25.0) / per);
   const double instr = 330.0 + rounds * (60.0 + 24.0 * g.bsize + 27.0 * (g.omax - g.omin + 1)) +
                        batches * (32.0 + 13.5 * g.bsize);
-  const double ties = 32 * s.n < s.nbins && (!weighted || counts) ? 3.0 : 1.0;
+  const double ties = 32 * s.n < s.nbins && (!weighted || counts)
+                          ? 3.0 * std::max(1.0, pow(s.nbins / (96.0 * s.n), 0.7))
+                          : 1.0;
   return instr * (weighted ? 1.4 : 1.0) * ties * std::max(1.0, pow(20.0 / periods_per_cu, 0.8));
 }
 }  // namespace

@@ -27,3 +27,15 @@ def test_few_points(monkeypatch, n, weighted, mip, want):
     kmax = 62 if weighted and mip > 1 else 170
     s = Shape(0, n, 0, 0, 20000, 1740, 26, kmax)
     assert f(C.byref(s), 1, C.c_bool(weighted), mip, C.c_bool(False), 256, 160 * 1024) == want
+
+
+@pytest.mark.parametrize("n,want", [(3, False), (6, False), (10, False), (20, True), (40, True),
+                                    (1000, True)])
+def test_fewer_points_tie_more(monkeypatch, n, want):
+    import paper_1112_1701_amd._lib as L
+    L.load()
+    monkeypatch.delenv("BLS_BLOCK_SEARCH", raising=False)
+    f = getattr(C.CDLL(LIB), "_ZN3bls11block_batchEPKNS_10CurveShapeEibibii")
+    f.restype = C.c_bool
+    s = Shape(0, n, 0, 0, 4 * 4510, 1393, 33, 223)
+    assert f(C.byref(s), 1, C.c_bool(False), 1, C.c_bool(False), 256, 160 * 1024) == want
