@@ -257,14 +257,16 @@ int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom 
 // checked: 192 calls of 1000 to 4096 bins cost 1% where it takes the block
 // search, but it leaves some of 3000 bins and more to the other kernel that
 // would take half as long, 4 x 2000 points x 4000 periods x 4096 bins, 0.005 to
-// 0.05, 2.0 / 1.0 ms.)  A unit-weight curve of fewer points than a thirty-second
-// of its bins has boxes that tie over many start bins: 91 x 12 points x 40
-// periods x 2585 bins 0.44 / 1.03 ms, 1000 bins 0.14 / 0.22; 50 points, 1000
-// bins 0.14 / 0.17; and more the fewer they are: 4 x 4510 periods x 1393 bins,
-// 0.024 to 0.16, of 6, 10, 20 and 40 points 1.46 / 2.70, 1.33 / 1.75, 1.13 /
-// 0.94 and 0.95 / 0.46.  So has a weighted one with a minimum count, which
-// hardly a box reaches: 132 x 6 x 244 x 1740, a minimum of three 4.0 / 12.1 ms
-// (of one, 2.4 / 0.73).
+// 0.05, 2.0 / 1.0 ms.)  A curve of few points for its bins has boxes
+// that tie over many start bins, each of which is scored: up to several times
+// the other kernel's time, in proportion to the bins per point (weighted curves
+// only with a minimum count that hardly a box reaches; where boxes do, the other
+// kernel's counting of their points costs more).  Over 2383 calls of 3 to 120
+// points and 150 to 3500 bins the choice costs 1.7% (unit) and 2.9% (weighted, a
+// minimum of three); 4 x 4510 periods x 1393 bins, 0.024 to 0.16, of 6, 10, 20
+// and 40 points 1.46 / 2.70 ms, 1.33 / 1.75, 1.13 / 0.94 and 0.95 / 0.46;
+// weighted with a minimum of three, 132 x 244 x 1740, 0.015 to 0.036, of 6 and
+// 30 points 6.1 / 11.7 and 6.5 / 1.9.
 //
 // The rule sees sizes and not the data, on which the block search's time
 // depends more than the other's: narrow boxes and weights over four decades
@@ -279,16 +281,16 @@ double every_box_cost(const CurveShape &s, bool weighted, bool counts, bool eigh
   const double instr = s.nbins / 64.0 * (2.0 * s.kmin + 7.0 * (s.kmax - s.kmin + 1) + 30.0);
   return instr * (!weighted ? (eight ? 0.9 : 1.0) : counts ? 3.0 : eight ? 1.25 : 1.55);
 }
-double block_cost(const CurveShape &s, bool weighted, bool counts, const BlockGeom &g,
-                  int periods_per_cu) {
+double block_cost(const CurveShape &s, bool weighted, int counts, const BlockGeom &g,
+                  int periods_per_cu, double every) {
   const int rounds = (g.nblocks + 63) / 64, per = 64 / g.bsize;
   const double batches = ceil((20.0 + s.nbins / 25.0) / per);
   const double instr = 330.0 + rounds * (60.0 + 24.0 * g.bsize + 27.0 * (g.omax - g.omin + 1)) +
                        batches * (32.0 + 13.5 * g.bsize);
-  const double ties = 32 * s.n < s.nbins && (!weighted || counts)
-                          ? 3.0 * std::max(1.0, pow(s.nbins / (96.0 * s.n), 0.7))
-                          : 1.0;
-  return instr * (weighted ? 1.4 : 1.0) * ties * std::max(1.0, pow(20.0 / periods_per_cu, 0.8));
+  const bool empty = counts > 1 && 10.0 * s.n * s.kmax < (double)counts * s.nbins;
+  const double ties = (!weighted ? 0.012 : empty ? 0.01 : 0.0) * s.nbins / (double)s.n;
+  return instr * (weighted ? 1.4 : 1.0) * std::max(1.0, pow(20.0 / periods_per_cu, 0.8)) +
+         ties * every;
 }
 }  // namespace
 
@@ -308,8 +310,9 @@ bool block_batch(const CurveShape *shapes, int n, bool weighted, int min_in_poin
     if (T < 1) return false;
     const bool eight = tuned || untuned_lds_budget(s, periods, weighted, num_cus) <
                                     default_tiles(weighted).lds_budget;
-    every += (double)s.nperiods * every_box_cost(s, weighted, min_in_points > 1, eight);
-    block += (double)s.nperiods * block_cost(s, weighted, min_in_points > 1, g, T * groups);
+    const double boxes = every_box_cost(s, weighted, min_in_points > 1, eight);
+    every += (double)s.nperiods * boxes;
+    block += (double)s.nperiods * block_cost(s, weighted, min_in_points, g, T * groups, boxes);
   }
   // Fewer periods than seven waves per CU: a period takes a wave 25 us or more,
   // and the four of a workgroup less (461 bins, 1497 periods 44 / 35 us; 400

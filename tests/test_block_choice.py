@@ -1,7 +1,9 @@
 """The choice between the two binned kernels (no GPU): curves of far fewer points
-than bins stay with the kernel that scores every box, but for weighted ones
-without a minimum count."""
+than bins, whose boxes tie, stay with the kernel that scores every box, weighted
+ones only with a minimum count that hardly a box reaches.  The calls are ones
+where the other choice took at least half as long again."""
 import ctypes as C
+import math
 import os
 
 import pytest
@@ -15,27 +17,28 @@ class Shape(C.Structure):
                [(k, C.c_int32) for k in ("nperiods", "nbins", "kmin", "kmax")]
 
 
-@pytest.mark.parametrize("n,weighted,mip,want", [
-    (12, False, 1, False), (54, False, 1, False), (55, False, 1, True), (5000, False, 1, True),
-    (12, True, 1, True), (12, True, 3, False), (55, True, 3, True)])
-def test_few_points(monkeypatch, n, weighted, mip, want):
+@pytest.mark.parametrize("n,periods,nbins,qmin,qmax,weighted,mip,want", [
+    (3, 29400, 407, 0.0503, 0.49, False, 1, False),
+    (6, 18040, 1393, 0.0236, 0.16, False, 1, False),
+    (10, 18040, 1393, 0.0236, 0.16, False, 1, False),
+    (40, 18040, 1393, 0.0236, 0.16, False, 1, True),
+    (1000, 18040, 1393, 0.0236, 0.16, False, 1, True),
+    (12, 3640, 2585, 0.01, 0.03, False, 1, False),
+    (18, 11558, 2242, 0.0552, 0.49, False, 1, False),
+    (22, 2295, 2291, 0.0456, 0.441, False, 1, False),
+    (30, 2192, 1939, 0.0358, 0.4224, False, 3, False),
+    (12, 20000, 1740, 0.015, 0.098, True, 1, True),
+    (6, 32208, 1740, 0.015, 0.036, True, 3, False),
+    (30, 32208, 1740, 0.015, 0.036, True, 3, True),
+    (3, 113680, 771, 0.0038, 0.0363, True, 3, False),
+    (28, 237120, 1581, 0.0285, 0.0828, True, 3, True),
+    (7, 3283, 2648, 0.0435, 0.3513, True, 3, True),
+    (8, 5474, 3328, 0.011, 0.1251, True, 3, True)])
+def test_few_points(monkeypatch, n, periods, nbins, qmin, qmax, weighted, mip, want):
     import paper_1112_1701_amd._lib as L
     L.load()
     monkeypatch.delenv("BLS_BLOCK_SEARCH", raising=False)
     f = getattr(C.CDLL(LIB), "_ZN3bls11block_batchEPKNS_10CurveShapeEibibii")
     f.restype = C.c_bool
-    kmax = 62 if weighted and mip > 1 else 170
-    s = Shape(0, n, 0, 0, 20000, 1740, 26, kmax)
+    s = Shape(0, n, 0, 0, periods, nbins, math.ceil(qmin * nbins - 0.5), int(qmax * nbins + 0.5))
     assert f(C.byref(s), 1, C.c_bool(weighted), mip, C.c_bool(False), 256, 160 * 1024) == want
-
-
-@pytest.mark.parametrize("n,want", [(3, False), (6, False), (10, False), (20, True), (40, True),
-                                    (1000, True)])
-def test_fewer_points_tie_more(monkeypatch, n, want):
-    import paper_1112_1701_amd._lib as L
-    L.load()
-    monkeypatch.delenv("BLS_BLOCK_SEARCH", raising=False)
-    f = getattr(C.CDLL(LIB), "_ZN3bls11block_batchEPKNS_10CurveShapeEibibii")
-    f.restype = C.c_bool
-    s = Shape(0, n, 0, 0, 4 * 4510, 1393, 33, 223)
-    assert f(C.byref(s), 1, C.c_bool(False), 1, C.c_bool(False), 256, 160 * 1024) == want
