@@ -122,22 +122,6 @@ int scan_read_cycles(int S, int tile, int nbins) {
   return cycles;
 }
 
-// Banks depend on S mod 16 only; the costs are kept, each where its key falls,
-// without a lock or heap use (a stride takes 16 of them, 33 us; 59 equal curves
-// in a call without a plan, which kept none and took up to three each, 3.1 ms).
-int cached_read_cycles(int S, int tile, int nbins) {
-  constexpr int kBits = 12;
-  static std::atomic<uint64_t> memo[1 << kBits];  // key << 16 | cost (at most 1024)
-  const int nb = std::min(nbins, 4 * kBlock);     // lanes reach no further start bin
-  const uint64_t key = ((uint64_t)nb << 16) | ((uint64_t)tile << 4) | (uint64_t)(S & 15);
-  std::atomic<uint64_t> &place = memo[(key * 0x9E3779B97F4A7C15ull) >> (64 - kBits)];
-  const uint64_t kept = place.load(std::memory_order_relaxed);
-  if (kept >> 16 == key) return (int)(kept & 0xFFFF);
-  const int c = scan_read_cycles(S & 15, tile, nb);
-  place.store(key << 16 | (uint64_t)c, std::memory_order_relaxed);
-  return c;
-}
-
 }  // namespace
 
 int hist_words(int nbins, int kmax) {
@@ -146,18 +130,34 @@ int hist_words(int nbins, int kmax) {
   return nbins + std::max(std::min(kmax, nbins / 2) - 1, 1);
 }
 
+// Banks depend on the stride mod 16 and on no start bin past the first rounds',
+// so the padding does too.  It is kept where its key falls in a fixed table,
+// without a lock or heap use: found anew it takes 33 us (59 equal curves in a
+// call without a plan, which kept none and tried up to three tiles each, 3.1
+// ms; 101 curves of 101 bin counts whose 16 costs each did not fit a table of
+// 4096, 0.55).
 int hist_stride(int nbins, int kmax, int tile, bool weighted) {
+  constexpr int kBits = 14;
+  static std::atomic<uint32_t> kept[1 << kBits];  // key << 4 | padding
   const int hb = hist_words(nbins, kmax);
+  const int nb = std::min(nbins, 4 * kBlock);
+  const uint32_t key = (uint32_t)nb << 11 | (uint32_t)(tile - 1) << 5 | (uint32_t)(hb & 15) << 1 |
+                       (weighted ? 1u : 0u);
+  static_assert(kTileMax <= 64 && 4 * kBlock < 1 << 17, "fields of the key");
+  std::atomic<uint32_t> &place = kept[(key * 0x9E3779B1u) >> (32 - kBits)];
+  const uint32_t k = place.load(std::memory_order_relaxed);
+  if (k >> 4 == key) return hb + (int)(k & 15);
   const int wpb = weighted ? 2 : 1;  // the scan reads the first plane of wpb
-  int best = hb, best_cost = 0;
-  for (int hs = hb; hs < hb + 16; ++hs) {
-    const int c = cached_read_cycles(hs * wpb, tile, nbins);
-    if (hs == hb || c < best_cost) {
-      best = hs;
+  int best = 0, best_cost = 0;
+  for (int pad = 0; pad < 16; ++pad) {
+    const int c = scan_read_cycles(((hb + pad) * wpb) & 15, tile, nb);
+    if (pad == 0 || c < best_cost) {
+      best = pad;
       best_cost = c;
     }
   }
-  return best;
+  place.store(key << 4 | (uint32_t)best, std::memory_order_relaxed);
+  return hb + best;
 }
 
 void fit_tile(int nbins, int kmax, int64_t nperiods, int lds_budget, int tile_cap,

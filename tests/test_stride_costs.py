@@ -63,7 +63,19 @@ int main() {
     again = std::min(again, std::chrono::duration<double>(t2 - t1).count());
   }
   printf("%g %g\n", once * 1e6, again * 1e6);
-  return again > 50 * once;  // 200 fits, each a part of the first
+  if (again > 50 * once) return 1;  // 200 fits, each a part of the first
+  double first = 0;                 // and for a batch of many bin counts
+  again = 1e30;
+  for (int pass = 0; pass < 6; ++pass) {
+    const auto t0 = clock::now();
+    for (int nb = 1100; nb < 1300; ++nb) fit_tile(nb / 4, nb / 40, 5000, 25000, kTileMax, true, &T, &hs);
+    for (int nb = 200; nb < 400; ++nb) fit_tile(nb, nb / 10, 5000, 21200, kTileMax, false, &T, &hs);
+    const double s = std::chrono::duration<double>(clock::now() - t0).count();
+    if (pass == 0) first = s;
+    else again = std::min(again, s);
+  }
+  printf("%g %g\n", first * 1e6, again * 1e6);
+  return again > 0.3 * first;
 }
 '''
 
