@@ -362,8 +362,9 @@ struct PeriodScan {
     // The screens take R and W - R at their least: R less its absolute error
     // where it comes from prefix weights (c0 from the blocks' table, two quanta
     // from the words), W - R with Ws for W; then the rounding of the running
-    // weight, which is relative.
-    Ws = Wt;
+    // weight, which is relative.  (Points are counted exactly, but thrs Ws is
+    // rounded, an error of W - R that is all of it where a box leaves few.)
+    Ws = uniform(Wt * (1.0f - 0x1p-22f));
     if (WEIGHTED) {
       Ws = uniform(Wt - 2.0f * (Wt * eR + c0));
       es = uniform(2.0f * eR);
