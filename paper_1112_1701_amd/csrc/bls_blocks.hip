@@ -438,7 +438,8 @@ struct PeriodScan {
       float4 tn = tp[o0];
       for (int o = o0; o <= o1; o += 2) {
         // Lower value as in lower(); where R (W - R) is not positive the box
-        // holds no signal either, and the quotient is NaN or not above 0.
+        // holds no signal either, and the quotient is NaN or not above 0, or
+        // it holds every point and the remainder of an inexact mean: infinite.
         const float4 t = tn;
         tn = tp[min(o + 2, o1)];
         const float R = t.w - t0.w;
@@ -461,6 +462,7 @@ struct PeriodScan {
     }
     bv *= 1.0f - 0x1p-18f;
     float t = wave_fmax(bv);
+    if (t == __builtin_inff()) t = 0.0f;  // (not a valid box: the sweep finds those)
     if (t > 0.0f) {
       const u64 m = __builtin_amdgcn_ballot_w64(bv == t);
       const int l = (int)__builtin_ctzll(m);
