@@ -47,7 +47,11 @@ namespace {
 typedef unsigned long long u64;
 
 // Prunings of the candidate list after which a sweep is left (on noise it is
-// pruned once at its end), and the error of a difference of two prefix words'
+// pruned once at its end), at least; one per 2^13 boxes where there are more,
+// as scoring every start bin then costs 35 instructions per 64 boxes against
+// 500 a pruning (periods longer than the data, 46 curves x 8267 points x 68
+// periods to 20 d in 10 d x 2271 bins, 0.041 to 0.397: 5.3 ms with eight, 1.3
+// so, 1.2 with every box).  And the error of a difference of two prefix words'
 // weights, in quanta.
 constexpr int kMaxPrunes = 8;
 constexpr float kWordError = 3.0f;
@@ -516,7 +520,7 @@ struct PeriodScan {
         if (ncand > kBlockCand / 2) {
           wave_sync();
           prune();
-          prunes += ncand > kBlockCand / 2 ? kMaxPrunes : 1;
+          prunes = ncand > kBlockCand / 2 ? kMaxPrunes : prunes + 1;
           ncand = min(ncand, kBlockCand / 2);
           qn = prunes >= kMaxPrunes ? 0 : qn;  // (ends the loop over the queue)
         }
@@ -829,7 +833,7 @@ struct PeriodScan {
     do {
       before = theta;
       ncand = 0;
-      prunes = 0;
+      prunes = min(0, kMaxPrunes - (nb * kmax >> 13));
       sweep<false>();
     } while (prunes >= kMaxPrunes && ++tries < 2 && theta > 1.1f * before);
     if (prunes >= kMaxPrunes) {
@@ -882,7 +886,7 @@ struct PeriodScan {
 
 // WIDE: the copy for launches of at most four workgroups per CU, which have
 // the registers of four waves per SIMD to themselves.  In the others' 80 (96
-// weighted) VGPRs a period's set-up spills 31 (35), 12.6 GB of writes for 256
+// weighted) VGPRs a period's set-up spills 31 (35), 21 GB of writes for 256
 // x 50000 points x 100000 periods x 1000 bins; in 121 (128) none does.
 // Narrow / wide: 24 x 50000 x 100000 x 1000 (0.005 to 0.05) 47.9 / 46.5 ms;
 // weighted 24 x 20000 x 20000 x 700 8.5 / 8.3; but where the LDS leaves room

@@ -160,3 +160,34 @@ def test_unbinned_equal_times(bls, n, step, weighted, flags):
             ms.append(min(bls.bls_kernel_times(p.handle)))
     print("[ms] flat, noise:", ms, flush=True)
     assert ms[1] <= 1.25 * ms[0], ms
+
+
+# Periods longer than the data with boxes of much of the cycle: many boxes hold
+# the same points, and a period's best stays in question until the list of
+# candidates has been pruned many times.
+@pytest.mark.parametrize("nc,n,m,nbins,qmin,qmax", [(8, 18000, 500, 1460, 0.046, 0.39),
+                                                    (40, 2000, 500, 1460, 0.046, 0.39),
+                                                    (46, 8000, 70, 2270, 0.041, 0.397)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_periods_beyond_the_data(bls, monkeypatch, nc, n, m, nbins, qmin, qmax, weighted):
+    print("[case] beyond the data", nc, n, m, nbins, weighted, flush=True)
+    rng = np.random.default_rng(n)
+    t = np.sort(rng.uniform(0.0, 10.0, (nc, n)), axis=1).ravel()
+    x = rng.normal(0.0, 1.0, nc * n)
+    w = rng.uniform(0.5, 2.0, nc * n) if weighted else None
+    per = synth.log_period_grid(0.2, 20.0, m)
+    ms, res = [], []
+    for env in ("0", "1"):
+        monkeypatch.setenv("BLS_BLOCK_SEARCH", env)
+        with bls.Plan(max_curves=nc, max_points=nc * n, max_periods=nc * m) as p:
+            t_ = []
+            for _ in range(4):
+                r = bls.bls_search_batch(p.handle, np.arange(nc + 1) * n, t, x, w, per, None,
+                                         nbins, qmin, qmax)
+                t_.append(bls.bls_last_stats(p.handle)["search_ms"])
+            ms.append(min(t_))
+            res.append(r)
+    print("[ms] every box, blocks:", ms, flush=True)
+    for k in res[0]:
+        assert np.array_equal(res[0][k], res[1][k], equal_nan=True), k
+    assert ms[1] <= 2.0 * ms[0], ms
