@@ -243,37 +243,38 @@ int block_tile(int nbins, int kmax, bool weighted, int max_lds, const BlockGeom 
   return best;
 }
 
-// Whether the block search is the faster kernel for a batch, from the kernel
-// times of both over 4000 calls of 1 to 200 curves, 140 to 50000 points, 1000
-// to 60000 periods and 100 to 1000 bins, in instructions per period after the
-// fold, which they share.  Scoring every box: a lane per start bin, three
-// quarters as many again for weights, and twice that where a box that passes
-// the screen has its points counted (weighted, a minimum of two or more); 0.8
-// to 0.9 of it where the call's tiles are tuned or let eight (six) workgroups
-// share a CU (untuned_lds_budget).  The block search: its parts for the curve's
-// geometry, 1.4 times that for weights, more where the LDS holds fewer than 20
-// periods per CU.  The choice costs 1.6% against the faster kernel of each
-// call; the block search always, 7%, never, 18%.  (Beyond 1000 bins it was only
-// checked: 192 calls of 1000 to 4096 bins cost 1% where it takes the block
-// search, but it leaves some of 3000 bins and more to the other kernel that
-// would take half as long, 4 x 2000 points x 4000 periods x 4096 bins, 0.005 to
-// 0.05, 2.0 / 1.0 ms.)  A curve of few points for its bins has boxes
-// that tie over many start bins, each of which is scored: up to several times
-// the other kernel's time, in proportion to the bins per point (weighted curves
-// only with a minimum count that hardly a box reaches; where boxes do, the other
-// kernel's counting of their points costs more).  Over 2383 calls of 3 to 120
-// points and 150 to 3500 bins the choice costs 1.7% (unit) and 2.9% (weighted, a
-// minimum of three); 4 x 4510 periods x 1393 bins, 0.024 to 0.16, of 6, 10, 20
-// and 40 points 1.46 / 2.70 ms, 1.33 / 1.75, 1.13 / 0.94 and 0.95 / 0.46;
-// weighted with a minimum of three, 132 x 244 x 1740, 0.015 to 0.036, of 6 and
-// 30 points 6.1 / 11.7 and 6.5 / 1.9.
+// Whether the block search is the faster kernel for a batch, in instructions
+// per period after the fold, which both share.  Scoring every box: a lane per
+// start bin, three quarters as many again for weights, and twice that where a
+// box that passes the screen has its points counted (weighted, a minimum of two
+// or more); 0.8 to 0.9 of it where the call's tiles are tuned or let eight (six)
+// workgroups share a CU (untuned_lds_budget).  The block search: its parts for
+// the curve's geometry, 1.4 times that for weights, more where the LDS holds
+// fewer than 20 periods per CU (its root: with the power 0.8 that calls of up to
+// 1000 bins had suggested, calls of 1000 to 4096 lost 10% and up to a factor of
+// seven).  The constants are from both kernels' times over some 9000 calls of
+// noise, 1 to 200 curves, 100 to 60000 periods.  On 3042 others, percent above
+// the faster kernel of each call by the choice, by blocks always and by blocks
+// never: 140 to 50000 points, 100 to 1000 bins, unit weights 4.5, 20 and 18,
+// weighted 1.1, 36 and 4, with a minimum of three 3.0, 27 and 25; 1000 to 4096
+// bins 4.3, 3 and 85, 4.0, 10 and 45, 1.5, 3 and 253.
+//
+// A curve of few points for its bins has boxes that tie over many start bins,
+// each of which is scored: up to several times the other kernel's time, in
+// proportion to the bins per point (weighted curves only with a minimum count
+// that hardly a box reaches; where boxes do, the other kernel's counting of their
+// points costs more).  3 to 120 points, 150 to 3500 bins: unit weights 1.7, 85 and
+// 8 percent, weighted 11, 11 and 91, with a minimum of three 5.3, 41 and 90; 4 x
+// 4510 periods x 1393 bins, 0.024 to 0.16, of 6, 10, 20 and 40 points 1.46 / 2.70
+// ms, 1.33 / 1.75, 1.13 / 0.94 and 0.95 / 0.46; weighted with a minimum of three,
+// 132 x 244 x 1740, 0.015 to 0.036, of 6 and 30 points 6.1 / 13.4 and 6.5 / 1.5.
 //
 // The rule sees sizes and not the data, on which the block search's time
 // depends more than the other's: narrow boxes and weights over four decades
 // (105 x 500 points x 192 periods x 2000 bins, 0.0038 to 0.046) 1.03 / 1.76 ms
-// where weights within a factor of four take 0.95 / 0.88; data that cover less
-// than a third of the period (8 x 1120 x 3232 x 1455, 0.011 to 0.21, periods to
-// 20 d in 4 d) 2.0 / 2.35 where 60 d take 1.63 / 0.46; dips alone beside rare
+// where weights within a factor of four take 0.95 / 0.88; periods beyond
+// the data with wide boxes (39 x 215 x 62 x 2235, 0.046 to 0.35, periods to 20 d
+// in 10 d) 0.80 / 2.6 where 60 d take 0.79 / 0.49; dips alone beside rare
 // points far above them (1 x 1214 x 19830 x 743, 0.003 to 0.047, 0.5% of the
 // points 500 sigma up) 0.24 / 0.36 where noise takes 0.20 / 0.18.
 namespace {
@@ -289,7 +290,7 @@ double block_cost(const CurveShape &s, bool weighted, int counts, const BlockGeo
                        batches * (32.0 + 13.5 * g.bsize);
   const bool empty = counts > 1 && 10.0 * s.n * s.kmax < (double)counts * s.nbins;
   const double ties = (!weighted ? 0.012 : empty ? 0.01 : 0.0) * s.nbins / (double)s.n;
-  return instr * (weighted ? 1.4 : 1.0) * std::max(1.0, pow(20.0 / periods_per_cu, 0.8)) +
+  return instr * (weighted ? 1.4 : 1.0) * std::max(1.0, sqrt(20.0 / periods_per_cu)) +
          ties * every;
 }
 }  // namespace

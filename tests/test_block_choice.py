@@ -1,7 +1,7 @@
 """The choice between the two binned kernels (no GPU): curves of far fewer points
 than bins, whose boxes tie, stay with the kernel that scores every box, weighted
 ones only with a minimum count that hardly a box reaches.  The calls are ones
-where the other choice took at least half as long again."""
+where the other choice took at least a quarter as long again."""
 import ctypes as C
 import math
 import os
@@ -26,7 +26,6 @@ class Shape(C.Structure):
     (12, 3640, 2585, 0.01, 0.03, False, 1, False),
     (18, 11558, 2242, 0.0552, 0.49, False, 1, False),
     (22, 2295, 2291, 0.0456, 0.441, False, 1, False),
-    (30, 2192, 1939, 0.0358, 0.4224, False, 3, False),
     (12, 20000, 1740, 0.015, 0.098, True, 1, True),
     (6, 32208, 1740, 0.015, 0.036, True, 3, False),
     (30, 32208, 1740, 0.015, 0.036, True, 3, True),
