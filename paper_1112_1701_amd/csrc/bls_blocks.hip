@@ -366,9 +366,8 @@ struct PeriodScan {
     // The screens take R and W - R at their least: R less its absolute error
     // where it comes from prefix weights (c0 from the blocks' table, two quanta
     // from the words), W - R with Ws for W; then the rounding of the running
-    // weight, which is relative.  (Points are counted exactly, but thrs Ws is
-    // rounded, an error of W - R that is all of it where a box leaves few.)
-    Ws = uniform(Wt * (1.0f - 0x1p-22f));
+    // weight, which is relative.
+    Ws = Wt;
     if (WEIGHTED) {
       Ws = uniform(Wt - 2.0f * (Wt * eR + c0));
       es = uniform(2.0f * eR);
@@ -423,7 +422,9 @@ struct PeriodScan {
     theta = uniform(t);
     thr = uniform(t * (1.0f - 0x1p-17f));
     thrs = WEIGHTED ? uniform(thr * (1.0f - es)) : thr;
-    tW = uniform(thrs * Ws);
+    // (Points are counted exactly, but the product is rounded: an error of
+    // W - R that is all of it where a box leaves few.)
+    tW = uniform(thrs * (WEIGHTED ? Ws : Ws * (1.0f - 0x1p-22f)));
   }
 
   // A first theta: boxes between the blocks' first bins, then the boxes
@@ -466,7 +467,7 @@ struct PeriodScan {
     }
     bv *= 1.0f - 0x1p-18f;
     float t = wave_fmax(bv);
-    if (t == __builtin_inff()) t = 0.0f;  // (not a valid box: the sweep finds those)
+    if (!WEIGHTED && t == __builtin_inff()) t = 0.0f;  // (none is valid: the sweep finds one)
     if (t > 0.0f) {
       const u64 m = __builtin_amdgcn_ballot_w64(bv == t);
       const int l = (int)__builtin_ctzll(m);
