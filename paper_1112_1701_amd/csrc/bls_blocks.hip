@@ -22,7 +22,7 @@
 // VALU instructions per CU and clock (1.15 is what search_kernel reaches at
 // 300 bins), and the share of the clocks in which the LDS is active: 300 bins
 // 0.92 and 0.62, weighted 0.75 and 0.61; 525 bins 0.87 and 0.43, weighted 0.71
-// and 0.43; 1000 bins and 20000 points 0.75 and 0.71, weighted 0.63 and 0.60.
+// and 0.43; 1000 bins and 20000 points 0.74 and 0.71, weighted 0.63 and 0.60.
 // So neither is full: the registers and the LDS leave six to three waves per
 // SIMD, whose latencies (LDS, cross-lane sums) show.
 //
@@ -888,7 +888,7 @@ struct PeriodScan {
 // WIDE: the copy for launches of at most four workgroups per CU, which have
 // the registers of four waves per SIMD to themselves.  In the others' 80 (96
 // weighted) VGPRs a period's set-up spills 31 (35), 21 GB of writes for 256
-// x 50000 points x 100000 periods x 1000 bins; in 121 (128) none does.
+// x 50000 points x 100000 periods x 1000 bins; in 122 (128) none does.
 // Narrow / wide: 24 x 50000 x 100000 x 1000 (0.005 to 0.05) 47.9 / 46.5 ms;
 // weighted 24 x 20000 x 20000 x 700 8.5 / 8.3; but where the LDS leaves room
 // for five or six, weighted 23 x 805 x 9306 x 585 1.53 / 1.74 and 158 x 1346 x
